@@ -124,6 +124,7 @@ static int build_bloch(kaldo_crystal* c, int64_t nnz, const int32_t* fi, const i
     blk_d.push_back(kv.first[2]);
     pair_ptr[kv.first[0] * nb + kv.first[1] + 1]++;
   }
+  c->bloch.max_pair_blk = *std::max_element(pair_ptr.begin(), pair_ptr.end());
   for (int k = 0; k < nb * nb; ++k) pair_ptr[k + 1] += pair_ptr[k];
   for (int d = 0; d < n_d; ++d)
     for (int e = d_ptr[d]; e < d_ptr[d + 1]; ++e) {

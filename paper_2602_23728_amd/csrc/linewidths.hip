@@ -217,13 +217,22 @@ __global__ void lw_finish(int nq, int nb3, int nblk, double scale, const double*
 }
 
 // Which crystal kernel serves a request: the dense MFMA kernel for the split
-// form (and, in FP32, for cells of 9 or more branches, where dense 16-wide
-// tiles beat the pruned VALU path), otherwise the fused pruned kernel, and the
+// form and, in FP32, for cells of 9 or more branches, where dense 16-wide
+// tiles beat the pruned VALU path; otherwise the fused pruned kernel, and the
 // generic kernel when neither fits.  KALDO_CRYSTAL_PATH=fused|mfma|generic
-// overrides the FP32 choice.
+// overrides the FP32 and FP64 choice.
+//
+// In FP64 the dense kernel serves whatever the fused one cannot hold (its
+// tables of all branches must fit the LDS), cells of 12 branches and more, and
+// those of 9 on meshes of up to 512 points.  Random cells, 4^3 / 9^3 mesh,
+// fused (generic where it does not fit) against dense, ms: 2 atoms 0.16 / 1.13
+// against 0.09 / 3.74, 3 atoms 0.38 / 4.39 against 0.12 / 4.61, 4 atoms
+// 56 / 553 (generic) against 0.14 / 6.8, 5 atoms 117 / 1089 (generic) against
+// 0.23 / 13.8: the pruned kernel's work per q grows with the pairs inside the
+// cut, few of them with few branches, the dense one's with all 16 x 16.
 enum class CrystalPath { Generic, Fused, Mfma };
 
-static CrystalPath choose_path(const kaldo_crystal* c, int prec) {
+static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
   const char* env = std::getenv("KALDO_CRYSTAL_PATH");
   const std::string want = env ? env : "";
   if (prec == KALDO_BF16X3) {
@@ -239,8 +248,11 @@ static CrystalPath choose_path(const kaldo_crystal* c, int prec) {
   if (want == "generic") return CrystalPath::Generic;
   if (prec == KALDO_FP32 && mfma_supported(c) && (want == "mfma" || (want.empty() && c->nb3 >= 9)))
     return CrystalPath::Mfma;
-  if (fused_supported(c, prec)) return CrystalPath::Fused;
-  return CrystalPath::Generic;
+  const bool fused = fused_supported(c, prec);
+  const bool dense64 = !fused || c->nb3 >= 12 || (c->nb3 >= 9 && nq <= 512);
+  if (prec == KALDO_FP64 && mfma64_supported(c) && (want == "mfma" || (want.empty() && dense64)))
+    return CrystalPath::Mfma;
+  return fused ? CrystalPath::Fused : CrystalPath::Generic;
 }
 
 // Workspace layout of the path that serves the request (offsets of buffers
@@ -278,14 +290,14 @@ static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, Cryst
     w.off_fpart = take(sizeof(double) * nq * kFusedMaxChunks * nb3);
     w.off_mrec = take(sizeof(double2) * 3 * nq * nb3);
   } else {
-    w.off_phase = take(sizeof(float2) * nq * (size_t)std::max(1, c->bloch.n_d));
+    w.off_phase = take(cs * nq * (size_t)std::max(1, c->bloch.n_d));
   }
   w.total = o;
   return w;
 }
 
 static CrystalWs crystal_ws(const kaldo_crystal* c, long nq, int prec) {
-  return crystal_ws_for(c, nq, prec, choose_path(c, prec));
+  return crystal_ws_for(c, nq, prec, choose_path(c, nq, prec));
 }
 
 template <typename T>
@@ -316,8 +328,7 @@ static int run_crystal(const kaldo_crystal* c, const int32_t* mesh, const double
   LwParams p = make_params(c, mesh, T_k, b);
   const CrystalPath path = w.path;
   if (path == CrystalPath::Mfma) {
-    float2* phase_tab = reinterpret_cast<float2*>(ws + w.off_phase);
-    return launch_mfma(c, p, prec == KALDO_BF16X3, omega, vel, occ, phys, sel, evec, phase_tab,
+    return launch_mfma(c, p, prec, omega, vel, modef, occ, phys, sel, evec, ws + w.off_phase,
                        kPrefactor / (double)nq, gamma, st);
   }
   if (path == CrystalPath::Fused) {
@@ -371,13 +382,13 @@ int linewidths_enqueue(const kaldo_crystal* c, const int32_t* mesh, const double
   if (rc) return rc;
   KALDO_REQUIRE(precision == KALDO_FP64 || precision == KALDO_FP32 || precision == KALDO_BF16X3,
                 "kaldo_linewidths: unknown precision");
-  if (precision == KALDO_BF16X3 && choose_path(c, precision) == CrystalPath::Mfma &&
+  const long nq = (long)mesh[0] * mesh[1] * mesh[2];
+  if (precision == KALDO_BF16X3 && choose_path(c, nq, precision) == CrystalPath::Mfma &&
       !mfma_supported(c)) {
     set_error("kaldo_linewidths: BF16X3 needs the MFMA kernel (nb3 <= 16, tables in LDS)");
     return KALDO_EUNSUPPORTED;
   }
   KALDO_REQUIRE(n_subset >= 0 && (n_subset == 0 || modes_subset), "kaldo_linewidths: bad subset");
-  const long nq = (long)mesh[0] * mesh[1] * mesh[2];
   KALDO_REQUIRE(nq <= 65535L, "kaldo_linewidths: mesh too large (N_q > 65535)");
   CrystalWs w = crystal_ws(c, nq, precision);
   KALDO_REQUIRE(workspace && workspace_bytes >= w.total, "kaldo_linewidths: workspace too small");

@@ -154,6 +154,40 @@ __device__ __forceinline__ double pair_weight(const LwParams& p, double w, doubl
   return pop / (w * (w1 * w2));
 }
 
+// pair_weight of the ordering (q1 s', q2 s'') plus, when dbl, that of its
+// mirror (q2 s'', q1 s'), which has the same widths and its own cut.  Of the
+// four processes an entry passes one or two, so a loop that takes each lane's
+// next one evaluates two exponentials a wave where four guarded blocks, each
+// live in some lane, evaluate four; the widths' and frequencies' reciprocals
+// are shared.
+__device__ __forceinline__ double pair_weight_both(const LwParams& p, int dbl, double w, double w1,
+                                                   double w2, double n1, double n2, double sp,
+                                                   double sm) {
+  const double x0 = (w + w1) - w2, x1 = (w - w1) - w2, x2 = (w + w2) - w1, x3 = (w - w2) - w1;
+  unsigned todo = (fabs(x0) < 2.0 * sp ? 1u : 0u) | (fabs(x1) < 2.0 * sm ? 2u : 0u);
+  if (dbl) todo |= (fabs(x2) < 2.0 * sp ? 4u : 0u) | (fabs(x3) < 2.0 * sm ? 8u : 0u);
+  if (!todo) return 0.0;
+  const double dn = n1 - n2, sn = 0.5 * (n1 + n2 + 1.0);
+  const double r = 1.0 / (sp * sm);
+  const double ip = sm * r, im = sp * r;
+  double sum = 0.0;
+  do {
+    const unsigned t = todo & -todo;
+    const bool decay = t & 10u;
+    todo ^= t;
+    const double x = t == 1u ? x0 : t == 2u ? x1 : t == 4u ? x2 : x3;
+    const double i = decay ? im : ip;
+    const double f = decay ? sn : (t == 1u ? dn : -dn);
+    if (p.shape == KALDO_GAUSS) {
+      const double u = x * i;
+      sum += f * (exp(-(u * u)) * i);
+    } else {
+      sum += f * smear(p.shape, x, decay ? sm : sp);
+    }
+  } while (todo);
+  return sum / ((p.shape == KALDO_GAUSS ? kSqrtPi : 1.0) * (w * (w1 * w2)));
+}
+
 // The temperature-independent factors of one ordered partner pair:
 // ap = g(x+; sigma+)/(w w1 w2) and am = g(x-; sigma-)/(w w1 w2), each zero
 // unless its own process passes |x| < 2 sigma (the cut of pair_weight).
@@ -457,10 +491,11 @@ int launch_fused(const kaldo_crystal* c, const LwParams& p, const double* omega,
                  double scale, double* gamma, hipStream_t st);
 
 // Dense MFMA crystal kernel (lw_mfma.hip).
-bool mfma_supported(const kaldo_crystal* c);
-int launch_mfma(const kaldo_crystal* c, const LwParams& p, bool split, const double* omega,
-                const double* vel, const double* occ, const uint8_t* phys, const uint8_t* sel,
-                const double* evec, float2* phase_tab, double scale, double* gamma,
-                hipStream_t st);
+bool mfma_supported(const kaldo_crystal* c);    // FP32 and BF16x3 forms
+bool mfma64_supported(const kaldo_crystal* c);  // FP64 form
+int launch_mfma(const kaldo_crystal* c, const LwParams& p, int prec, const double* omega,
+                const double* vel, const float4* modef, const double* occ, const uint8_t* phys,
+                const uint8_t* sel, const double* evec, void* phase_ws, double scale,
+                double* gamma, hipStream_t st);
 
 }  // namespace kaldo

@@ -11,13 +11,30 @@
 // A complex 16x16x16 product is two real products with the complex parts
 // stacked along K (K = 32):  Re C = [Re A | -Im A][Re B ; Im B] and
 // Im C = [Im A | Re A][Re B ; Im B].
-//   FP32 form:  v_mfma_f32_16x16x4_f32, 8 per real product.
+//   FP64 form:  v_mfma_f64_16x16x4_f64, FP32 form: v_mfma_f32_16x16x4_f32,
+//               8 per real product.
 //   BF16x3:     v_mfma_f32_16x16x32_bf16 on x = hi + lo splits,
 //               hi*hi + hi*lo + lo*hi per real product, FP32 accumulation.
-// One workgroup per q (8 waves sharing A~_q in LDS, two per SIMD); each wave
-// takes its own q1 values.  With Phi3 symmetric in its last two slots the
+// One workgroup per (q, group of branches), one workgroup a CU; each wave
+// takes its own partners q1.  With Phi3 symmetric in its last two slots the
 // tile of the mirrored partner (q2, q1) is V^T, so only q1 <_lex q2 is swept
 // (q1 == q2 once) and each candidate carries the terms of both orderings.
+//
+// What bounds it: the FP64 and FP32 matrix instructions run at the vector
+// rate and hold the vector unit while they do (a wave of MFMAs beside a wave
+// of fused multiply-adds takes the sum of both times), so a (partner, branch)
+// costs its 32 MFMAs (1024 cycles in FP32, 2048 in FP64) plus every vector
+// instruction around them.  Hence B_s is built in operand order with the
+// table's values loaded a branch ahead and no masks (16 steps of four fused
+// multiply-adds; a padded slot meets a zero phase), partners are decoded 64
+// at a time one per lane, nothing is projected for a branch without a
+// candidate, and the candidates of a partner's branches are weighted together,
+// one exponential a loop trip.  Measured, abx3 cell (15 branches):
+//   FP32, 12^3 mesh:        33.5 -> 21.2 ms (8 waves and a work item per q before);
+//   BF16x3, 11x9x7 mesh:    5.4 -> 4.0 ms;
+//   FP64, 7x6x5 mesh:       126 ms (generic kernel, per-lane gathers) -> 0.78 ms.
+// FP32 runs 12 waves (three a SIMD; 22.7 ms with eight, phases in registers),
+// FP64 and the split form eight (their registers).
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -30,11 +47,6 @@ namespace kaldo {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f4;
 
-constexpr int kMfmaWaves = 8;
-constexpr int kMfmaThreads = 64 * kMfmaWaves;
-constexpr int kMfmaMaxBlocks = 128;  // atom blocks (jb, kb, d) of the FC3 tables
-constexpr int kCandCap = 2 * 64;     // a full batch plus one row's worth
-
 // Order LDS traffic between the lanes of one wave (no workgroup barrier:
 // the waves of a workgroup run different numbers of q1 iterations).
 __device__ __forceinline__ void wave_sync() {
@@ -43,64 +55,129 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Complex K index of element i of a lane's operand fragment (g = lane / 16):
-//   FP32 16x16x4, 8 MFMAs over the stacked K = 32: MFMA t reads stacked
-//     k = 4 t + g, i.e. complex column kc = 4 (t % 4) + g, part t / 4.
-//   BF16 16x16x32: element i reads stacked k = 8 g + i, i.e. complex column
-//   kc = 8 (g % 2) + i, part g / 2.
-// The second product V = eta1^T T takes its K order from the accumulator
-// layout of T instead (lane (n, g) holds T rows 4 g + r, r < 4): FP32 MFMA t
-// pairs K slot g with jc = 4 g + t % 4 (part t / 4), BF16 element i with
-// jc = 4 g + i % 4 (part i / 4), so T goes from registers straight into the
-// next product; eta1's fragments follow the same order.
+enum DenseForm { kF64 = 0, kF32 = 1, kSplit = 2 };
+constexpr int kAccSlots = 16;   // sums a wave keeps per branch: lanes l, l + 16, ... share one in turn
+constexpr int kTileCand = 256;  // queue slots of a wave: one branch's candidates always fit
 
-template <bool SPLIT>
-__global__ __launch_bounds__(kMfmaThreads) void lw_mfma(
-    LwParams p, int n_rep, const int32_t* __restrict__ rep,
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double d4;
+__device__ __forceinline__ d4 mma(double a, double b, d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f4 mma(float a, float b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f4 mma(bf16x8 a, bf16x8 b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// x = hi + lo in bf16, rounded two values an instruction.
+typedef float f8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ void split8(f8 x, bf16x8& hi, bf16x8& lo) {
+  const bf16v8 h = __builtin_convertvector(x, bf16v8);
+  const bf16v8 l = __builtin_convertvector(x - __builtin_convertvector(h, f8), bf16v8);
+  hi = __builtin_bit_cast(bf16x8, h);
+  lo = __builtin_bit_cast(bf16x8, l);
+}
+// kWaves: waves of a workgroup, of which a CU holds one
+template <int FORM>
+struct Dense {
+  using T = float;
+  using V4 = f4;
+  static constexpr int kWaves = FORM == kF32 ? 12 : 8;
+};
+template <>
+struct Dense<kF64> {
+  using T = double;
+  using V4 = d4;
+  static constexpr int kWaves = 8;
+};
+
+// Steps of a B_s entry: the blocks of an atom pair, padded to a multiple of
+// four.  With four (nearest-neighbour tables; the FOUR kernels) a partner's
+// phases are kept per pair, zero past its blocks; otherwise per block, with
+// one zero phase after the last.
+__host__ __device__ inline int tile_slots(int max_pair_blk) { return (max_pair_blk + 3) / 4 * 4; }
+__host__ __device__ inline int tile_phases(int nb, int n_blk, int n_slot) {
+  return n_slot == 4 ? nb * nb * 4 : n_blk + 1;
+}
+
+// LDS of lw_tiles besides the A~ table, in bytes.  Per wave: the phases of
+// the current partner, the mode data of its two q-points, the candidate queue, the sums
+// [branch][kAccSlots] and, in the split form, a B_s tile.
+template <int FORM>
+__host__ __device__ inline size_t tile_wave_lds(int group, int n_ph) {
+  const size_t cs = sizeof(typename Cx<typename Dense<FORM>::T>::type);
+  return n_ph * cs + 2 * 16 * 5 * 8 + kTileCand * (cs + 2) + group * kAccSlots * 8 +
+         (FORM == kSplit ? (16 * 17 + 1) * cs : 0);
+}
+
+template <int FORM, bool FOUR>
+__global__ __launch_bounds__(64 * Dense<FORM>::kWaves)
+__attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
+    LwParams p, int n_rep, int group, int n_group, int n_slot, const int32_t* __restrict__ rep,
     const double* __restrict__ omega, const double* __restrict__ vel,
-    const double* __restrict__ occ, const uint8_t* __restrict__ phys,
-    const uint8_t* __restrict__ sel, const double* __restrict__ evec,
-    const float2* __restrict__ phase_tab, const int32_t* __restrict__ t_ptr,
-    const int32_t* __restrict__ t_i, const int32_t* __restrict__ t_l2,
-    const double* __restrict__ t_coef, const int32_t* __restrict__ e_blk,
-    const int32_t* __restrict__ e_bg, const int32_t* __restrict__ blk_d,
+    const float4* __restrict__ modef, const double* __restrict__ occ,
+    const uint8_t* __restrict__ phys, const uint8_t* __restrict__ sel,
+    const double* __restrict__ evec, const typename Cx<typename Dense<FORM>::T>::type* __restrict__ phase_tab,
+    const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_i,
+    const int32_t* __restrict__ t_l2, const double* __restrict__ t_coef,
+    const int32_t* __restrict__ e_blk, const int32_t* __restrict__ e_bg,
+    const int32_t* __restrict__ blk_d, const int32_t* __restrict__ pair_ptr,
     const int4* __restrict__ bwork, double scale, double* __restrict__ gamma) {
-  const int NB3 = p.nb3;
-  extern __shared__ double2 smem[];
-  float2* at = reinterpret_cast<float2*>(smem);  // [n_blk][9][NB3]
-  __shared__ float2 bsc[kMfmaWaves][16 * 17];         // per-wave B_s tile [row jc][col kc]
-  __shared__ float2 phb[kMfmaWaves][kMfmaMaxBlocks];  // per-wave e^{-i q1.R_d(blk)} per block
-  __shared__ int cq_code[kMfmaWaves][kCandCap];       // per-wave near-shell candidates of the
-  __shared__ double cq_v2[kMfmaWaves][kCandCap];      //   current partner: s | s' << 8 | s'' << 16, |V|^2
-  __shared__ double md[kMfmaWaves][2][16][5];         // per-wave (w, n, v) of the q1 and q2 modes
-  __shared__ double2 phq[64];
-  __shared__ double wq64[16];
-  __shared__ double red[kMfmaThreads];
-  double acc[16];  // this thread's per-branch sums (registers)
-
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  using T = typename Dense<FORM>::T;
+  using V4 = typename Dense<FORM>::V4;
+  using C = typename Cx<T>::type;
+  constexpr int kTileWaves = Dense<FORM>::kWaves, kTileThreads = 64 * kTileWaves;
+  constexpr bool kSpl = FORM == kSplit;
+  constexpr bool kAhead = FOUR && !kSpl;  // the split form has no registers to load ahead
+  const int NB3 = p.nb3, NB = NB3 / 3;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: partner indices stay scalar
   const int lr = lane & 15, lg = lane >> 4;
-  const int q = blockIdx.x;
+  const int q = blockIdx.x / n_group, s_lo = (blockIdx.x - q * n_group) * group;
+  const int n_s = min(group, NB3 - s_lo);
   const int N0 = p.N[0], N1 = p.N[1], N2 = p.N[2];
   const int a0 = q / (N1 * N2), a1 = (q / N2) % N1, a2 = q % N2;
 
-  unsigned live = 0, any_sel = 0;
+  extern __shared__ double2 smem[];
+  const int at_s = p.n_blk * 9;                  // entries of one branch
+  const int at_n = group * at_s + 9 * n_slot;    // and a zero tail a padded range may read
+  const int n_ph = tile_phases(NB, p.n_blk, n_slot);
+  C* at = reinterpret_cast<C*>(smem);            // [branch of the group][n_blk][9]
+  unsigned char* wave_lds = reinterpret_cast<unsigned char*>(smem) +
+                            ((size_t)at_n * sizeof(C) + 15) / 16 * 16 +
+                            wv * tile_wave_lds<FORM>(group, n_ph);
+  C* phb = reinterpret_cast<C*>(wave_lds);       // e^{-i q1.R_d} per phase slot
+  double(*md)[16][5] =
+      reinterpret_cast<double(*)[16][5]>(wave_lds + n_ph * sizeof(C));  // (w, n, v) of q1's and q2's modes
+  C* cq_v = reinterpret_cast<C*>(md + 2);                     // queued candidates: V,
+  double* acc = reinterpret_cast<double*>(cq_v + kTileCand);  // sums [branch of the group][kAccSlots]
+  uint16_t* cq_code = reinterpret_cast<uint16_t*>(acc + group * kAccSlots);  // s - s_lo | s' << 4 | s'' << 8
+  C* bt = reinterpret_cast<C*>(cq_code + kTileCand);  // split form: B_s tile [row jc][17: column kc]
+  int* slot_d = reinterpret_cast<int*>(
+      reinterpret_cast<unsigned char*>(smem) + ((size_t)at_n * sizeof(C) + 15) / 16 * 16 +
+      kTileWaves * tile_wave_lds<FORM>(group, n_ph));           // d of each phase slot, -1: none
+  __shared__ double2 phq[64];
+  __shared__ double wq64[16];
+
+  unsigned live = 0, any_sel = 0;  // branches of the group, bit s - s_lo
   float wq_abs_max = 0.0f;
-  for (int s = 0; s < NB3; ++s) {
-    const bool ph = phys[q * NB3 + s], se = sel[q * NB3 + s];
+  for (int s = 0; s < n_s; ++s) {
+    const int m = q * NB3 + s_lo + s;
+    const bool ph = phys[m], se = sel[m];
     live |= (ph && se) ? (1u << s) : 0u;
     any_sel |= se ? (1u << s) : 0u;
-    wq_abs_max = fmaxf(wq_abs_max, fabsf((float)omega[q * NB3 + s]));
+    wq_abs_max = fmaxf(wq_abs_max, fabsf((float)omega[m]));
   }
   if (live == 0) {
-    if (tid < NB3 && (any_sel >> tid & 1u)) gamma[q * NB3 + tid] = 0.0;
+    if (tid < n_s && (any_sel >> tid & 1u)) gamma[q * NB3 + s_lo + tid] = 0.0;
     return;
   }
-  if (tid < NB3) wq64[tid] = omega[q * NB3 + tid];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) acc[k] = 0.0;
-  for (int k = tid; k < kMfmaWaves * 16 * 17; k += kMfmaThreads) (&bsc[0][0])[k] = make_float2(0.f, 0.f);
-  for (int l = tid; l < n_rep; l += kMfmaThreads) {
+  if (tid < n_s) wq64[tid] = omega[q * NB3 + s_lo + tid];
+  for (int k = lane; k < n_s * kAccSlots; k += 64) acc[k] = 0.0;
+  if constexpr (kSpl)
+    for (int k = lane; k < 16 * 17; k += 64) bt[k] = Cx<T>::make((T)0, (T)0);
+  for (int l = tid; l < n_rep; l += kTileThreads) {
     const int32_t* r = rep + 3 * l;
     int m0 = ((a0 * r[0]) % N0 + N0) % N0, m1 = ((a1 * r[1]) % N1 + N1) % N1,
         m2 = ((a2 * r[2]) % N2 + N2) % N2;
@@ -109,35 +186,54 @@ __global__ __launch_bounds__(kMfmaThreads) void lw_mfma(
     sincospi(2.0 * f, &sn, &cs);
     phq[l] = make_double2(cs, sn);
   }
-  const int n_at = p.n_blk * 9 * NB3;
-  for (int k = tid; k < n_at; k += kMfmaThreads) at[k] = make_float2(0.f, 0.f);
+  for (int k = tid; k < at_n; k += kTileThreads) at[k] = Cx<T>::make((T)0, (T)0);
+  for (int k = tid; k < n_ph; k += kTileThreads) {
+    const int blk = FOUR ? pair_ptr[k >> 2] + (k & 3) : k;
+    slot_d[k] = blk < (FOUR ? pair_ptr[(k >> 2) + 1] : p.n_blk) ? blk_d[blk] : -1;
+  }
   __syncthreads();
-  for (int k = tid; k < p.n_e * NB3; k += kMfmaThreads) {
-    const int e = k / NB3, s = k % NB3;
+  for (int k = tid; k < p.n_e * n_s; k += kTileThreads) {
+    const int e = k / n_s, s = k - e * n_s;
     double re = 0.0, im = 0.0;
     for (int t = t_ptr[e]; t < t_ptr[e + 1]; ++t) {
-      const size_t o = (((size_t)q * NB3 + t_i[t]) * NB3 + s) * 2;
+      const size_t o = (((size_t)q * NB3 + t_i[t]) * NB3 + s_lo + s) * 2;
       const double ex = evec[o], ey = evec[o + 1];
       const double2 f = phq[t_l2[t]];
       const double c = t_coef[t];
       re += c * (ex * f.x - ey * f.y);
       im += c * (ex * f.y + ey * f.x);
     }
-    at[(e_blk[e] * 9 + e_bg[e]) * NB3 + s] = make_float2((float)re, (float)im);
+    at[s * at_s + e_blk[e] * 9 + e_bg[e]] = Cx<T>::make((T)re, (T)im);
   }
   __syncthreads();
 
-  // entries of a lane's operand fragments
-  constexpr int NF = SPLIT ? 8 : 4;
-  auto kc_of = [&](int i) { return SPLIT ? 8 * (lg & 1) + i : 4 * i + lg; };
-  // this lane's share of every B_s tile (fixed for the whole kernel)
-  // packed as pos | lo << 9 | hi << 17 | bg << 25 (pos < 272, block indices
-  // <= 128, bg < 9), -1 for no item
-  int wk[4];
+  // Accumulator item r of a lane is row row_of(r) of its column lr; K slot
+  // (MFMA t, lane group lg) of the first product is column 4 (t % 4) + lg of
+  // B_s (part t / 4 of the stacked complex K), of the second row row_of(t % 4)
+  // of T, so that T goes from the accumulators straight into the next product.
+  // The split form's products take element i of lane group lg as column
+  // 8 (lg % 2) + i of part lg / 2, and row 4 lg + i % 4 of part i / 4.
+  auto row_of = [&](int r) { return FORM == kF64 ? 4 * r + lg : 4 * lg + r; };
+  // this lane's four B_s entries: first table entry and first phase of their
+  // atom pair.  In operand order (row jc = lr, columns kc = 4 i + lg; an entry
+  // outside the cell takes entry 0 and is dropped); in the split form, where
+  // two lanes read each entry, the balanced work list's, handed round through
+  // the tile at position b_pos (no entry: the spare one).
+  int b_at[4], b_ph[4], b_cnt[4], b_pos[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int4 w = bwork[k * 64 + lane];
-    wk[k] = w.x < 0 ? -1 : (w.x | (w.y << 9) | (w.z << 17) | (w.w << 25));
+  for (int i = 0; i < 4; ++i) {
+    int jc = lr, kc = 4 * i + lg;
+    if constexpr (kSpl) {
+      b_pos[i] = bwork[i * 64 + lane].x;
+      if (b_pos[i] < 0) b_pos[i] = 16 * 17;
+      jc = b_pos[i] / 17;
+      kc = b_pos[i] - 17 * jc;
+    }
+    const bool in = kSpl ? b_pos[i] < 16 * 17 : lr < NB3 && kc < NB3;
+    const int pr = in ? (jc / 3) * NB + kc / 3 : 0;
+    b_at[i] = in ? pair_ptr[pr] * 9 + (jc % 3) * 3 + kc % 3 : 0;
+    b_ph[i] = FOUR ? 4 * pr : pair_ptr[pr];
+    b_cnt[i] = pair_ptr[pr + 1] - pair_ptr[pr];
   }
 
   // Exact FP64 cut and weight of queued candidates, one per lane, in queue
@@ -148,40 +244,54 @@ __global__ __launch_bounds__(kMfmaThreads) void lw_mfma(
   auto resolve = [&](int dbl) {
     for (int base = 0; base < n_cand; base += 64) {
       const int e = base + lane;
+      double c = 0.0;
+      int cs_ = 0;
       if (e < n_cand) {
-        const int code = cq_code[wv][e];
-        const int cs_ = code & 255, cs1 = (code >> 8) & 255, cs2 = (code >> 16) & 255;
-        const double* d1 = md[wv][0][cs1];
-        const double* d2 = md[wv][1][cs2];
+        const int code = cq_code[e];
+        cs_ = code & 15;
+        const double* d1 = md[0][(code >> 4) & 15];
+        const double* d2 = md[1][code >> 8];
         double sp, sm;
         widths_v(p, d1 + 2, d2 + 2, sp, sm);
-        double wt = pair_weight(p, wq64[cs_], d1[0], d2[0], d1[1], d2[1], sp, sm);
-        // the mirrored ordering: same |V|^2 and widths, its own cut
-        if (dbl) wt += pair_weight(p, wq64[cs_], d2[0], d1[0], d2[1], d1[1], sp, sm);
-        const double c = wt * cq_v2[wv][e];
-        // register accumulators need a static index: add to the selected one
+        const C v = cq_v[e];
+        c = pair_weight_both(p, dbl, wq64[cs_], d1[0], d2[0], d1[1], d2[1], sp, sm) *
+            ((double)v.x * (double)v.x + (double)v.y * (double)v.y);
+      }
+      double* a = acc + cs_ * kAccSlots + (lane & (kAccSlots - 1));
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc[k] += (k == cs_) ? c : 0.0;
+      for (int k = 0; k < 64; k += kAccSlots) {  // the lanes of one slot in turn
+        if (lane >= k && lane < k + kAccSlots && e < n_cand) *a += c;
+        wave_sync();
       }
     }
     n_cand = 0;
-    wave_sync();
   };
 
   const Partners prt(p.half != 0, a0, a1, a2, N0, N1, N2);
-  for (int pi = wv; pi < prt.n; pi += kMfmaWaves) {
-    int b0, b1, b2;
-    const int dbl = prt.get(pi, N1, N2, b0, b1, b2);  // wave-uniform
-    const int q1 = (b0 * N1 + b1) * N2 + b2;
-    const int c0 = ((-a0 - b0) % N0 + N0) % N0, c1 = ((-a1 - b1) % N1 + N1) % N1,
-              c2 = ((-a2 - b2) % N2 + N2) % N2;
-    const int q2 = (c0 * N1 + c1) * N2 + c2;
+  const float w_lane = lane < n_s ? (float)wq64[lane] : 0.0f;  // branch frequencies, read by readlane
+  unsigned partner = 0;  // lane k: q1 | q2 << 16 of the wave's k-th partner of 64
+  unsigned long long dbl_mask = 0;
+  for (int pi = wv, n_done = 0; pi < prt.n; pi += kTileWaves, ++n_done) {
+    if ((n_done & 63) == 0) {  // the next 64 partners, decoded one per lane
+      const int mine = pi + lane * kTileWaves;
+      int b0 = 0, b1 = 0, b2 = 0, twice = 0;
+      if (mine < prt.n) twice = prt.get(mine, N1, N2, b0, b1, b2);
+      const unsigned c0 = wrap_sub(prt.h[0].t, b0, N0), c1 = wrap_sub(prt.h[1].t, b1, N1),
+                     c2 = wrap_sub(prt.h[2].t, b2, N2);
+      partner = (unsigned)((b0 * N1 + b1) * N2 + b2) | ((c0 * N1 + c1) * N2 + c2) << 16;
+      dbl_mask = __ballot(twice);
+    }
+    const unsigned pk = __builtin_amdgcn_readlane(partner, n_done & 63);
+    const int dbl = (int)(dbl_mask >> (n_done & 63) & 1ull);  // all wave-uniform
+    const int q1 = pk & 0xffff, q2 = pk >> 16;
     wave_sync();
-    for (int blk = lane; blk < p.n_blk; blk += 64)
-      phb[wv][blk] = phase_tab[(size_t)q1 * p.n_d + blk_d[blk]];
+    for (int k = lane; k < n_ph; k += 64) {
+      const int d = slot_d[k];
+      phb[k] = d >= 0 ? phase_tab[(size_t)q1 * p.n_d + d] : Cx<T>::make((T)0, (T)0);
+    }
     if ((lane & 15) < NB3 && lane < 32) {
       const int m = (lane < 16 ? q1 : q2) * NB3 + (lane & 15);
-      double* d = md[wv][lane >> 4][lane & 15];
+      double* d = md[lane >> 4][lane & 15];
       d[0] = omega[m];
       d[1] = occ[m];
       d[2] = vel[3 * (size_t)m];
@@ -189,265 +299,314 @@ __global__ __launch_bounds__(kMfmaThreads) void lw_mfma(
       d[4] = vel[3 * (size_t)m + 2];
     }
     wave_sync();
-    // eta(q2)[kc][s''] as the B operand of T = B_s eta2 (column n = lr)
-    // and eta(q1)[jc][s'] (jc = 4 lg + i) as A = eta1^T (row m = lr) of
-    // V = eta1^T T.
-    float2 e2[NF], e1[4];
+    // The branches of the group, in runs as long as the queue takes whole
+    // branches (one run, as a rule): a run ends with its candidates resolved,
+    // where none of its operand registers is live.
+    int s = 0;
+    do {
+      // eta(q2)[kc][s''] as the B operand of T = B_s eta2 (column n = lr) and
+      // eta(q1)[jc][s'] as A = eta1^T (row m = lr) of V = eta1^T T; zero
+      // outside the cell, which also drops what B_s and T hold there
+      const double* v2 = evec + (size_t)q2 * NB3 * NB3 * 2;
+      const double* v1 = evec + (size_t)q1 * NB3 * NB3 * 2;
+      C e2[4], e1[4];
+      bf16x8 e2h, e2l, e1ah, e1al, e1bh, e1bl;  // split form: x = hi + lo
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      const int k = kc_of(i);
-      e2[i] = make_float2(0.f, 0.f);
-      if (k < NB3 && lr < NB3) {
-        const size_t o2 = (((size_t)q2 * NB3 + k) * NB3 + lr) * 2;
-        if constexpr (SPLIT) {
-          // B' stacks Re eta2 over Im eta2: lane groups 0, 1 take the real
-          // part, 2, 3 the imaginary one.  The lane loads only its own
-          // component; a run-time choice between the two halves of a
-          // register pair would send the whole array to scratch memory.
-          e2[i].x = (float)evec[o2 + (lg < 2 ? 0 : 1)];
-        } else {
-          e2[i] = make_float2((float)evec[o2], (float)evec[o2 + 1]);
+      for (int i = 0; i < 4; ++i) {
+        const unsigned k2 = 4 * i + lg, k1 = row_of(i);
+        e2[i] = e1[i] = Cx<T>::make((T)0, (T)0);
+        if (!kSpl && k2 < (unsigned)NB3 && lr < NB3) {
+          const unsigned o = (k2 * NB3 + lr) * 2;
+          e2[i] = Cx<T>::make((T)v2[o], (T)v2[o + 1]);
+        }
+        if (k1 < (unsigned)NB3 && lr < NB3) {
+          const unsigned o = (k1 * NB3 + lr) * 2;
+          e1[i] = Cx<T>::make((T)v1[o], (T)v1[o + 1]);
         }
       }
-    }
+      if constexpr (kSpl) {
+        f8 b, a1, a2;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = 4 * lg + i;
-      e1[i] = make_float2(0.f, 0.f);
-      if (k < NB3 && lr < NB3) {
-        const size_t o1 = (((size_t)q1 * NB3 + k) * NB3 + lr) * 2;
-        e1[i] = make_float2((float)evec[o1], (float)evec[o1 + 1]);
+        for (int i = 0; i < 8; ++i) {
+          // B' = [Re eta2 ; Im eta2]; A'(eta1^T) = [Re | -Im], A'' = [Im | Re]
+          const unsigned k = 8 * (lg & 1) + i;
+          b[i] = 0.0f;
+          if (k < (unsigned)NB3 && lr < NB3) b[i] = (float)v2[(k * NB3 + lr) * 2 + (lg < 2 ? 0 : 1)];
+          a1[i] = (i < 4) ? e1[i & 3].x : -e1[i & 3].y;
+          a2[i] = (i < 4) ? e1[i & 3].y : e1[i & 3].x;
+        }
+        split8(b, e2h, e2l);
+        split8(a1, e1ah, e1al);
+        split8(a2, e1bh, e1bl);
       }
-    }
-    // this lane's epilogue pairs: s' = 4 lg + r, s'' = lr.  Only the FP32
-    // pre-classification data stay in registers; the exact FP64 decision and
-    // weight reload their inputs (rare: candidates near the energy shell).
-    const int s2 = lr;
-    unsigned pr_ok = 0;
-    float bhi_p[4], bhi_m[4], cpv[4], cmv[4];
-    const bool s2_ok = s2 < NB3 && phys[q2 * NB3 + s2];
-    const double w2 = s2_ok ? omega[q2 * NB3 + s2] : 0.0;
+      // this lane's epilogue pairs: s' = row_of(r), s'' = lr.  FP32
+      // pre-classification from the mode copies (a mode below the floor carries
+      // a NaN frequency and fails every comparison); the exact FP64 decision
+      // and weight are the queue's.
+      float bhi_p[4], bhi_m[4], cpv[4], cmv[4];
+      const float4 none = make_float4(0.f, 0.f, 0.f, __builtin_nanf(""));
+      const float4 f2 = lr < NB3 ? modef[q2 * NB3 + lr] : none;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int s1 = 4 * lg + r;
-      bhi_p[r] = bhi_m[r] = cpv[r] = cmv[r] = 0.f;
-      if (s2_ok && s1 < NB3 && phys[q1 * NB3 + s1]) {
-        pr_ok |= 1u << r;
-        const int m1 = q1 * NB3 + s1;
-        const double w1 = omega[m1];
-        double s2p, s2m, Sp, Sm;
-        widths2(p, vel + 3 * (size_t)m1, vel + 3 * (size_t)(q2 * NB3 + s2), s2p, s2m, Sp, Sm);
-        const float scl = wq_abs_max + fabsf((float)w1) + fabsf((float)w2);
-        const float d = 4e-7f * scl + 1e-9f;
-        bhi_p[r] = 2.0f * band_sqrt((float)s2p) * (1.0f + 1e-6f) + d;
-        bhi_m[r] = 2.0f * band_sqrt((float)s2m) * (1.0f + 1e-6f) + d;
+      for (int r = 0; r < 4; ++r) {
+        const float4 f1 = row_of(r) < NB3 ? modef[q1 * NB3 + row_of(r)] : none;
+        float s2p, s2m, e_sig;
+        widths2_f(p, f1, f2, s2p, s2m, e_sig);
+        const float scl = wq_abs_max + fabsf(f1.w) + fabsf(f2.w);
+        bhi_p[r] = make_band_f(s2p, scl, e_sig).hi;
+        bhi_m[r] = make_band_f(s2m, scl, e_sig).hi;
         // with the mirrored ordering, |w + cp| and |w - cp| share the edge
         // bhi_p, and for w >= 0 the smaller is |w - |cp|| (bitwise in FP32):
         // one test covers both
-        cpv[r] = dbl ? -fabsf((float)(w1 - w2)) : (float)(w1 - w2);
-        cmv[r] = (float)(-w1 - w2);
+        const float cp = f1.w - f2.w;
+        cpv[r] = dbl ? -fabsf(cp) : cp;
+        cmv[r] = -f1.w - f2.w;
       }
-    }
-    // operand fragments of eta that do not depend on s
-    bf16x8 e2h, e2l, e1ah, e1al, e1bh, e1bl;  // BF16 form
-    float e2f[8], e1af[8], e1bf[8];            // FP32 form
-    if constexpr (SPLIT) {
+      // the A~ values of a branch, loaded while the branch before is projected
+      C an[kAhead ? 16 : 1];
+      auto fetch = [&](int sb) {
+        const C* as = at + min(sb, n_s - 1) * at_s;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        // B' = [Re eta2 ; Im eta2]; A'(eta1^T) = [Re | -Im], A'' = [Im | Re]
-        const float b = e2[i].x;
-        const float a1 = (i < 4) ? e1[i & 3].x : -e1[i & 3].y;
-        const float a2 = (i < 4) ? e1[i & 3].y : e1[i & 3].x;
-        e2h[i] = (__bf16)b;
-        e2l[i] = (__bf16)(b - (float)e2h[i]);
-        e1ah[i] = (__bf16)a1;
-        e1al[i] = (__bf16)(a1 - (float)e1ah[i]);
-        e1bh[i] = (__bf16)a2;
-        e1bl[i] = (__bf16)(a2 - (float)e1bh[i]);
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int i = t & 3;
-        e2f[t] = (t < 4) ? e2[i].x : e2[i].y;
-        e1af[t] = (t < 4) ? e1[i].x : -e1[i].y;
-        e1bf[t] = (t < 4) ? e1[i].y : e1[i].x;
-      }
-    }
+        for (int k = 0; k < 16; ++k) an[k] = as[b_at[k >> 2] + 9 * (k & 3)];
+      };
+      if constexpr (kAhead) fetch(s);
 #pragma unroll 1
-    for (int s = 0; s < NB3; ++s) {
-      if (!(live >> s & 1u)) continue;  // uniform
-      // B_s tile built cooperatively into LDS, then read as operand fragments
-      float2* Bt = bsc[wv];
+      for (; s < n_s; ++s) {
+        // the candidates of this branch, before anything is projected:
+        // coalescence of either ordering, or decay (w > 0: s is live)
+        const float wsf = __builtin_bit_cast(
+            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w_lane), s));
+        bool near[4];
+        unsigned long long mask[4];
+        int n_new = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (wk[k] < 0) continue;
-        const int pos = wk[k] & 511, lo = (wk[k] >> 9) & 255, end = (wk[k] >> 17) & 255,
-                  bg = (wk[k] >> 25) & 15;
-        float2 v = make_float2(0.f, 0.f);
-        const int stride = 9 * NB3;
-        const float2* ap = at + (lo * 9 + bg) * NB3 + s;
-        int blk = lo;
-        // four blocks per round: their LDS loads are issued together
-        for (; blk + 4 <= end; blk += 4, ap += 4 * stride) {
-          float2 a[4], f[4];
+        for (int r = 0; r < 4; ++r) {
+          const bool np = fabsf(wsf + cpv[r]) < bhi_p[r], nm = fabsf(wsf + cmv[r]) < bhi_m[r];
+          near[r] = np || nm;
+          mask[r] = __ballot(np) | __ballot(nm);
+          n_new += __popcll(mask[r]);
+        }
+        const bool skip = n_new == 0 || !(live >> s & 1u);         // uniform
+        if (!skip && n_cand + n_new > kTileCand) break;  // uniform: n_new <= 256 fits an empty queue
+        if (skip) {
+          if constexpr (kAhead) fetch(s + 1);
+          continue;
+        }
+        // B_s in operand order; a pair's slots past its blocks have a zero phase
+        T br[4] = {0, 0, 0, 0}, bi[4] = {0, 0, 0, 0};
+        auto quad = [&](int i, const C* a, const C* f) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            a[j] = ap[j * stride];
-            f[j] = phb[wv][blk + j];
+            br[i] = fma(f[j].x, a[j].x, br[i]);
+            br[i] = fma(-f[j].y, a[j].y, br[i]);
+            bi[i] = fma(f[j].x, a[j].y, bi[i]);
+            bi[i] = fma(f[j].y, a[j].x, bi[i]);
           }
-          // complex multiply-adds as fused multiply-adds into v (four per
-          // product instead of two multiplies, two fused and two adds)
+        };
+        if constexpr (kAhead) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            v.x = fmaf(f[j].x, a[j].x, v.x);
-            v.x = fmaf(-f[j].y, a[j].y, v.x);
-            v.y = fmaf(f[j].x, a[j].y, v.y);
-            v.y = fmaf(f[j].y, a[j].x, v.y);
+          for (int i = 0; i < 4; ++i) {
+            C f[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[j] = phb[b_ph[i] + j];
+            quad(i, an + 4 * i, f);
+          }
+          fetch(s + 1);
+        } else {
+          const C* as = at + s * at_s;
+          for (int j0 = 0; j0 < (FOUR ? 4 : n_slot); j0 += 4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              C a[4], f[4];
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                a[j] = as[b_at[i] + 9 * (j0 + j)];
+                f[j] = phb[FOUR || j0 + j < b_cnt[i] ? b_ph[i] + j0 + j : p.n_blk];
+              }
+              quad(i, a, f);
+            }
           }
         }
-        for (; blk < end; ++blk, ap += stride) {
-          const float2 a = *ap;
-          const float2 f = phb[wv][blk];
-          v.x = fmaf(f.x, a.x, v.x);
-          v.x = fmaf(-f.y, a.y, v.x);
-          v.y = fmaf(f.x, a.y, v.y);
-          v.y = fmaf(f.y, a.x, v.y);
-        }
-        Bt[pos] = v;
-      }
-      wave_sync();
-      float2 bv[NF];
-#pragma unroll
-      for (int i = 0; i < NF; ++i) bv[i] = Bt[lr * 17 + kc_of(i)];
-      f4 tr = {0, 0, 0, 0}, ti = {0, 0, 0, 0};
-      if constexpr (SPLIT) {
-        bf16x8 a1h, a1l, a2h, a2l;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float a1 = (lg < 2) ? bv[i].x : -bv[i].y;
-          const float a2 = (lg < 2) ? bv[i].y : bv[i].x;
-          a1h[i] = (__bf16)a1;
-          a1l[i] = (__bf16)(a1 - (float)a1h[i]);
-          a2h[i] = (__bf16)a2;
-          a2l[i] = (__bf16)(a2 - (float)a2h[i]);
-        }
-        tr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1l, e2h, tr, 0, 0, 0);
-        tr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1h, e2l, tr, 0, 0, 0);
-        tr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1h, e2h, tr, 0, 0, 0);
-        ti = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2l, e2h, ti, 0, 0, 0);
-        ti = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2h, e2l, ti, 0, 0, 0);
-        ti = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2h, e2h, ti, 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int i = t & 3;
-          const float a1 = (t < 4) ? bv[i].x : -bv[i].y;
-          const float a2 = (t < 4) ? bv[i].y : bv[i].x;
-          tr = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, e2f[t], tr, 0, 0, 0);
-          ti = __builtin_amdgcn_mfma_f32_16x16x4f32(a2, e2f[t], ti, 0, 0, 0);
-        }
-      }
-      // T (rows 4 lg + r of column lr, in registers) is the B operand of V
-      f4 vr = {0, 0, 0, 0}, vi = {0, 0, 0, 0};
-      if constexpr (SPLIT) {
-        bf16x8 th, tl;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float b = (i < 4) ? tr[i & 3] : ti[i & 3];
-          th[i] = (__bf16)b;
-          tl[i] = (__bf16)(b - (float)th[i]);
-        }
-        vr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e1al, th, vr, 0, 0, 0);
-        vr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e1ah, tl, vr, 0, 0, 0);
-        vr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e1ah, th, vr, 0, 0, 0);
-        vi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e1bl, th, vi, 0, 0, 0);
-        vi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e1bh, tl, vi, 0, 0, 0);
-        vi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e1bh, th, vi, 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const float b = (t < 4) ? tr[t & 3] : ti[t & 3];
-          vr = __builtin_amdgcn_mfma_f32_16x16x4f32(e1af[t], b, vr, 0, 0, 0);
-          vi = __builtin_amdgcn_mfma_f32_16x16x4f32(e1bf[t], b, vi, 0, 0, 0);
-        }
-      }
-      // epilogue: V[s' = 4 lg + r][s'' = lr].  The FP32 pre-classification
-      // drops candidates certainly outside the cut; the rest are queued with
-      // their |V|^2 for the exact FP64 decision and weight.
-      const float wsf = (float)wq64[s];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        bool near = false;
-        if (pr_ok >> r & 1u) {
-          // coalescence of either ordering, or decay (w > 0: s is live)
-          near = fabsf(wsf + cpv[r]) < bhi_p[r] || fabsf(wsf + cmv[r]) < bhi_m[r];
-        }
-        const unsigned long long mask = __ballot(near);
-        if (near) {
-          const unsigned lo = (unsigned)mask, hi = (unsigned)(mask >> 32);
-          const int off = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-          const int slot = n_cand + off;
-          cq_code[wv][slot] = s | ((4 * lg + r) << 8) | (s2 << 16);
-          cq_v2[wv][slot] = (double)vr[r] * (double)vr[r] + (double)vi[r] * (double)vi[r];
-        }
-        n_cand += __popcll(mask);
-        if (n_cand >= 64) {
+        // T (rows row_of(r) of column lr, in registers) is the B operand of V
+        V4 tr = {0, 0, 0, 0}, ti = {0, 0, 0, 0}, vr = {0, 0, 0, 0}, vi = {0, 0, 0, 0};
+        if constexpr (kSpl) {
           wave_sync();
-          resolve(dbl);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            bt[b_pos[i]] = Cx<T>::make(br[i], bi[i]);
+          wave_sync();
+          f8 a1, a2;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const C b = bt[lr * 17 + 8 * (lg & 1) + i];
+            a1[i] = (lg < 2) ? b.x : -b.y;
+            a2[i] = (lg < 2) ? b.y : b.x;
+          }
+          bf16x8 a1h, a1l, a2h, a2l;
+          split8(a1, a1h, a1l);
+          split8(a2, a2h, a2l);
+          tr = mma(a1l, e2h, tr);
+          ti = mma(a2l, e2h, ti);
+          tr = mma(a1h, e2l, tr);
+          ti = mma(a2h, e2l, ti);
+          tr = mma(a1h, e2h, tr);
+          ti = mma(a2h, e2h, ti);
+          f8 b;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) b[i] = (i < 4) ? tr[i & 3] : ti[i & 3];
+          bf16x8 th, tl;
+          split8(b, th, tl);
+          vr = mma(e1al, th, vr);
+          vi = mma(e1bl, th, vi);
+          vr = mma(e1ah, tl, vr);
+          vi = mma(e1bh, tl, vi);
+          vr = mma(e1ah, th, vr);
+          vi = mma(e1bh, th, vi);
+        } else {
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            const int i = t & 3;
+            const T x = (t < 4) ? br[i] : -bi[i];
+            const T y = (t < 4) ? bi[i] : br[i];
+            const T e = (t < 4) ? e2[i].x : e2[i].y;
+            tr = mma(x, e, tr);
+            ti = mma(y, e, ti);
+          }
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            const int i = t & 3;
+            const T x = (t < 4) ? e1[i].x : -e1[i].y;
+            const T y = (t < 4) ? e1[i].y : e1[i].x;
+            const T b = (t < 4) ? tr[i] : ti[i];
+            vr = mma(x, b, vr);
+            vi = mma(y, b, vi);
+          }
+        }
+        // the candidates' V[s' = row_of(r)][s'' = lr], queued for the exact FP64
+        // decision and weight
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (near[r]) {
+            const unsigned lo = (unsigned)mask[r], hi = (unsigned)(mask[r] >> 32);
+            const int slot = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, n_cand));
+            cq_code[slot] = (uint16_t)(s | (row_of(r) << 4) | (lr << 8));
+            cq_v[slot] = Cx<T>::make(vr[r], vi[r]);
+          }
+          n_cand += __popcll(mask[r]);
         }
       }
       wave_sync();
-    }
-    resolve(dbl);  // the queue never carries candidates past their partner
+      resolve(dbl);  // the queue never carries candidates past their partner
+    } while (s < n_s);
   }
-#pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    if (s >= NB3) break;
-    __syncthreads();
-    red[tid] = acc[s];
-    __syncthreads();
-    for (int w = kMfmaThreads / 2; w > 0; w >>= 1) {
-      if (tid < w) red[tid] += red[tid + w];
-      __syncthreads();
-    }
-    if (tid == 0 && (any_sel >> s & 1u))
-      gamma[q * NB3 + s] = (live >> s & 1u) ? scale * red[0] : 0.0;
+  // fixed order: a branch's 32 sums of every wave in turn, then a butterfly
+  __syncthreads();
+  for (int s = wv; s < n_s; s += kTileWaves) {
+    double sum = 0.0;
+    if (lane < kAccSlots)
+      for (int w = 0; w < kTileWaves; ++w)
+        sum += reinterpret_cast<const double*>(
+            reinterpret_cast<const unsigned char*>(acc + s * kAccSlots + lane) +
+            (ptrdiff_t)(w - wv) * (ptrdiff_t)tile_wave_lds<FORM>(group, n_ph))[0];
+    sum = wave_sum_fixed(sum);
+    if (lane == 0 && (any_sel >> s & 1u))
+      gamma[q * NB3 + s_lo + s] = (live >> s & 1u) ? scale * sum : 0.0;
   }
 }
 
+// Static LDS of lw_tiles, and the dynamic part with `group` branches a workgroup.
+constexpr size_t kTileStatic = 64 * 16 + 16 * 8;
+template <int FORM>
+static size_t tile_lds(const kaldo_crystal* c, int group) {
+  const size_t cs = sizeof(typename Cx<typename Dense<FORM>::T>::type);
+  const int n_slot = tile_slots(c->bloch.max_pair_blk);
+  const int n_ph = tile_phases(c->nb, c->bloch.n_blk, n_slot);
+  const size_t at_n = (size_t)group * c->bloch.n_blk * 9 + 9 * n_slot;
+  return (at_n * cs + 15) / 16 * 16 + Dense<FORM>::kWaves * tile_wave_lds<FORM>(group, n_ph) + sizeof(int) * n_ph;
+}
+
+// Branches a workgroup of lw_tiles takes, 0 when the tables of one branch do
+// not fit.  A CU holds one workgroup, which per partner pays a set-up of
+// about half a branch's projection: the group count that minimises rounds of
+// 256 workgroups x (set-up + branches).
+template <int FORM>
+static int tile_group(const kaldo_crystal* c, int nq) {
+  int dev = 0, lds_max = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+    return 0;
+  int best = 0;
+  double cost = 0.0;
+  for (int n = 1; n <= c->nb3; ++n) {
+    const int g = (c->nb3 + n - 1) / n;
+    if (tile_lds<FORM>(c, g) + kTileStatic > (size_t)lds_max) continue;
+    const double t = std::ceil((double)nq * n / 256.0) * (g + 0.5);
+    if (!best || t < cost) best = g, cost = t;
+  }
+  return best;
+}
+
+bool mfma64_supported(const kaldo_crystal* c) {
+  return c->nb3 <= 16 && c->n_rep <= 64 && tile_group<kF64>(c, 1) > 0;
+}
+
+template <int FORM>
+static int launch_tiles(const char* name, const kaldo_crystal* c, const LwParams& p,
+                        const double* omega, const double* vel, const float4* modef,
+                        const double* occ, const uint8_t* phys, const uint8_t* sel,
+                        const double* evec, void* phase_ws, double scale, double* gamma,
+                        hipStream_t st) {
+  using T = typename Dense<FORM>::T;
+  using C = typename Cx<T>::type;
+  C* phase_tab = static_cast<C*>(phase_ws);
+  const int nq = p.nq;
+  const long nph = (long)nq * std::max(1, p.n_d);
+  KALDO_LAUNCH("lw_phase_table", lw_phase_table<T>, dim3((nph + 255) / 256), dim3(256), 0, st, nq,
+               p.n_d, p.N[0], p.N[1], p.N[2], c->bloch.dvec, phase_tab);
+  const Fc3Bloch& b = c->bloch;
+  const int group = tile_group<FORM>(c, nq), n_group = (c->nb3 + group - 1) / group;
+  const int n_slot = tile_slots(b.max_pair_blk);
+  auto run = [&](auto kernel) {
+    KALDO_LAUNCH(name, kernel, dim3((unsigned)nq * n_group),
+                 dim3(64 * Dense<FORM>::kWaves),
+                 tile_lds<FORM>(c, group), st, p, c->n_rep, group, n_group, n_slot, c->d_rep, omega,
+                 vel, modef, occ, phys, sel, evec, phase_tab, b.t_ptr, b.t_i, b.t_l2, b.t_coef,
+                 b.e_blk, b.e_bg, b.blk_d, b.pair_ptr, b.bwork, scale, gamma);
+  };
+  if (n_slot == 4)
+    run(lw_tiles<FORM, true>);
+  else
+    run(lw_tiles<FORM, false>);
+  KALDO_HIP(hipGetLastError());
+  return KALDO_OK;
+}
+
+// The FP32 and split forms serve the cells whose A~ tables of all branches
+// fit the LDS with kMfmaBeside bytes to spare (the FP32 form leaves larger
+// cells to the pruned kernel).
+constexpr int kMfmaMaxBlocks = 128;
+constexpr size_t kMfmaBeside = 53376;
 bool mfma_supported(const kaldo_crystal* c) {
   if (c->nb3 > 16 || c->n_rep > 64 || c->bloch.n_blk > kMfmaMaxBlocks) return false;
   int dev = 0, lds_max = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
   if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
     return false;
-  const size_t dyn = (size_t)c->bloch.n_blk * 9 * c->nb3 * 8;
-  const size_t stat = kMfmaWaves * 16 * 17 * 8 + kMfmaWaves * kMfmaMaxBlocks * 8 +
-                      kMfmaWaves * kCandCap * 12 + kMfmaWaves * 2 * 16 * 5 * 8 + 64 * 16 + 16 * 8 + kMfmaThreads * 8;
-  return dyn + stat <= (size_t)lds_max;
+  return (size_t)c->bloch.n_blk * 9 * c->nb3 * 8 + kMfmaBeside <= (size_t)lds_max &&
+         tile_group<kF32>(c, 1) > 0 && tile_group<kSplit>(c, 1) > 0;
 }
 
-int launch_mfma(const kaldo_crystal* c, const LwParams& p, bool split, const double* omega,
-                const double* vel, const double* occ, const uint8_t* phys, const uint8_t* sel,
-                const double* evec, float2* phase_tab, double scale, double* gamma,
-                hipStream_t st) {
-  const int nq = p.nq;
-  const long nph = (long)nq * std::max(1, p.n_d);
-  KALDO_LAUNCH("lw_phase_table", lw_phase_table<float>, dim3((nph + 255) / 256), dim3(256), 0, st,
-               nq, p.n_d, p.N[0], p.N[1], p.N[2], c->bloch.dvec, phase_tab);
-  const size_t lds = (size_t)c->bloch.n_blk * 9 * c->nb3 * 8;
-  const Fc3Bloch& b = c->bloch;
-  if (split)
-    KALDO_LAUNCH("lw_mfma_bf16x3", lw_mfma<true>, dim3(nq), dim3(kMfmaThreads), lds, st, p,
-                 c->n_rep, c->d_rep, omega, vel, occ, phys, sel, evec, phase_tab, b.t_ptr, b.t_i,
-                 b.t_l2, b.t_coef, b.e_blk, b.e_bg, b.blk_d, b.bwork, scale, gamma);
-  else
-    KALDO_LAUNCH("lw_mfma_fp32", lw_mfma<false>, dim3(nq), dim3(kMfmaThreads), lds, st, p,
-                 c->n_rep, c->d_rep, omega, vel, occ, phys, sel, evec, phase_tab, b.t_ptr, b.t_i,
-                 b.t_l2, b.t_coef, b.e_blk, b.e_bg, b.blk_d, b.bwork, scale, gamma);
-  KALDO_HIP(hipGetLastError());
-  return KALDO_OK;
+int launch_mfma(const kaldo_crystal* c, const LwParams& p, int prec, const double* omega,
+                const double* vel, const float4* modef, const double* occ, const uint8_t* phys,
+                const uint8_t* sel, const double* evec, void* phase_ws, double scale,
+                double* gamma, hipStream_t st) {
+  if (prec == KALDO_FP64)
+    return launch_tiles<kF64>("lw_mfma_fp64", c, p, omega, vel, modef, occ, phys, sel, evec,
+                              phase_ws, scale, gamma, st);
+  if (prec == KALDO_BF16X3)
+    return launch_tiles<kSplit>("lw_mfma_bf16x3", c, p, omega, vel, modef, occ, phys, sel, evec,
+                                phase_ws, scale, gamma, st);
+  return launch_tiles<kF32>("lw_mfma_fp32", c, p, omega, vel, modef, occ, phys, sel, evec, phase_ws,
+                            scale, gamma, st);
 }
 
 }  // namespace kaldo

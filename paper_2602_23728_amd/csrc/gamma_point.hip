@@ -6,7 +6,9 @@
 // A_mu[b][c] = sum_a Phi3_abc E_a,mu / sqrt(m_a m_b m_c); Eq. gamma, Eq. bose,
 // Eq. broadening with the 2-sigma cut, as on the crystal path with N_q = 1.
 //
-// Kernels per batch of modes:
+// The matrix-core pipeline of gp_mfma.hip serves every precision whose SpMM
+// rows fit the LDS; otherwise the generic kernels below do (FP32 and FP64), per
+// batch of modes:
 //   gp_avals   A_mu values on the fixed (b, c) pattern        (sparse x E)
 //   gp_spmm    W_mu = A_mu E, row b of W from the ~15 entries of row b of A_mu
 //   gp_gemm    V tile = E^T W_mu on a 64 x 64 (mu', mu'') tile, K = 3N, and the
@@ -213,7 +215,7 @@ int run_gm(const kaldo_crystal* c, const LwParams& p, const double* omega, const
 bool gm_supported(const kaldo_crystal* c);
 
 static bool use_mfma(const kaldo_crystal* c, int prec) {
-  if (prec == KALDO_FP64 || !gm_supported(c)) return false;
+  if (!gm_supported(c)) return false;
   if (prec == KALDO_BF16X3) return true;
   const char* f = std::getenv("KALDO_FORCE_GENERIC");
   return !(f && f[0] == '1');
@@ -239,7 +241,7 @@ static GammaWs gamma_ws(const kaldo_crystal* c, int prec) {
   w.off_w = take(es * n * n * kGpBatch);
   w.off_partial = take(8 * n * nt * nt);
   w.total = o;
-  if (prec != KALDO_FP64 && gm_supported(c))
+  if (gm_supported(c))
     w.total = std::max(w.total, w.off_rest + gm_workspace_bytes(c, prec));
   return w;
 }

@@ -260,7 +260,7 @@ static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
 struct CrystalWs {
   CrystalPath path;
   size_t off_occ, off_phys, off_sel, off_eta, off_at, off_partial, off_phase, off_modef, off_qlist,
-      off_fpart, off_mrec, total;
+      off_fpart, off_mrec, off_window, off_bsum, total;
 };
 
 static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, CrystalPath path) {
@@ -287,7 +287,11 @@ static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, Cryst
     w.off_eta = take(cs * nq * nb3 * nb3);
     w.off_phase = take(cs * nq * (size_t)std::max(1, c->bloch.n_d));
     w.off_qlist = take(sizeof(int32_t) * (2 * nq + 1));
-    w.off_fpart = take(sizeof(double) * nq * kFusedMaxChunks * nb3);
+    // per work item the partial sums, or the cache's counts (four waves, int32) and
+    // the 960 block totals of its row pointers
+    w.off_fpart = take(2 * sizeof(double) * fused_max_items(c, nq) * nb3);
+    w.off_window = take(sizeof(float4) * nq * nb3);
+    w.off_bsum = take(sizeof(long long) * ((nq * nb3 + 1023) / 1024));
     w.off_mrec = take(sizeof(double2) * 3 * nq * nb3);
   } else {
     w.off_phase = take(cs * nq * (size_t)std::max(1, c->bloch.n_d));
@@ -335,8 +339,9 @@ static int run_crystal(const kaldo_crystal* c, const int32_t* mesh, const double
     C* phase_tab = reinterpret_cast<C*>(ws + w.off_phase);
     int32_t* qlist = reinterpret_cast<int32_t*>(ws + w.off_qlist);
     double* fpart = reinterpret_cast<double*>(ws + w.off_fpart);
-    return launch_fused<T>(c, p, omega, vel, modef, occ, mrec, phys, sel, evec, eta, phase_tab, qlist,
-                           fpart, subset ? n_subset : 0, kPrefactor / (double)nq, gamma, st);
+    return launch_fused<T>(c, p, omega, modef, mrec, phys, sel, evec, eta, phase_tab,
+                           reinterpret_cast<float4*>(ws + w.off_window), qlist, fpart,
+                           subset ? n_subset : 0, kPrefactor / (double)nq, gamma, st);
   }
   long ne = nq * nb3 * nb3;
   KALDO_LAUNCH("lw_round_evec", lw_round_evec<T>, dim3((ne + 255) / 256), dim3(256), 0, st, ne, evec, eta);
@@ -478,17 +483,21 @@ extern "C" int kaldo_tcache_build(const kaldo_crystal* c, const int32_t* mesh, c
     KALDO_LAUNCH("lw_select", lw_select, dim3((n_subset + 255) / 256), dim3(256), 0, st,
                  modes_subset, (long)n_subset, n_modes, sel, c->d_flags);
   const LwParams p = make_params(c, mesh, 300.0, b);
-  TcOut tc{reinterpret_cast<long long*>(ws + w.off_fpart), reinterpret_cast<long long*>(row_ptr),
+  float4* window = reinterpret_cast<float4*>(ws + w.off_window);
+  TcOut tc{reinterpret_cast<int32_t*>(ws + w.off_fpart),
+           reinterpret_cast<long long*>(ws + w.off_bsum), reinterpret_cast<long long*>(row_ptr),
            reinterpret_cast<uint2*>(pairs), reinterpret_cast<double2*>(factors), c->d_flags};
   const int64_t ns = modes_subset ? n_subset : 0;
   auto pass = [&](int mode) {
     if (precision == KALDO_FP64)
-      return launch_fused_cache<double>(c, p, mode, omega, vel, modef, mrec, phys, sel, evec,
+      return launch_fused_cache<double>(c, p, mode, omega, modef, mrec, phys, sel, evec,
                                         reinterpret_cast<double2*>(ws + w.off_eta),
-                                        reinterpret_cast<double2*>(ws + w.off_phase), qlist, ns, tc, st);
-    return launch_fused_cache<float>(c, p, mode, omega, vel, modef, mrec, phys, sel, evec,
+                                        reinterpret_cast<double2*>(ws + w.off_phase), window, qlist,
+                                        ns, tc, st);
+    return launch_fused_cache<float>(c, p, mode, omega, modef, mrec, phys, sel, evec,
                                      reinterpret_cast<float2*>(ws + w.off_eta),
-                                     reinterpret_cast<float2*>(ws + w.off_phase), qlist, ns, tc, st);
+                                     reinterpret_cast<float2*>(ws + w.off_phase), window, qlist, ns,
+                                     tc, st);
   };
   rc = pass(kModeCount);
   if (rc) return rc;

@@ -268,6 +268,14 @@ __device__ __forceinline__ double wave_sum_fixed(double v) {
   return v;
 }
 
+// Orders LDS traffic between the lanes of one wave (no workgroup barrier: the
+// waves of a workgroup run different numbers of iterations).
+__device__ __forceinline__ void lds_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // e^{-i q1.R_d} for every mesh point q1 and replica difference d, in T.
 template <typename T>
 __global__ void lw_phase_table(int nq, int n_d, int N0, int N1, int N2,
@@ -453,8 +461,8 @@ __global__ void lw_all_q(int nq, int32_t* __restrict__ list, int32_t* __restrict
   if (q == 0) *count = nq;
 }
 
-// Fused crystal kernel (lw_fused.hip): one workgroup per (q, chunk) work
-// item, at most kFusedMaxChunks chunks per q, about `target` items in all.
+// Work items (q, chunk) of the fused crystal kernel (lw_fused.hip) and of the
+// JDOS: at most kFusedMaxChunks chunks per q, about `target` items in all.
 constexpr int kFusedMaxChunks = 16;
 constexpr int kWorkItems = 4096;  // (q, chunk) items a launch aims for
 __host__ __device__ inline int fused_chunks(int n_live, int target) {
@@ -471,24 +479,26 @@ bool fused_record_supported(const kaldo_crystal* c, int prec);  // the cache's r
 // (record).
 enum FusedMode { kModeGamma = 0, kModeCount = 1, kModeRecord = 2 };
 struct TcOut {
-  long long* count;    // [n_live][kFusedMaxChunks][nb3], written by count, read by record
-  long long* row_ptr;  // [n_modes + 1] row offsets per mode, written by count
-  uint2* pairs;        // (m1, m2) of each entry, written by record
-  double2* factors;    // (c, d) of each entry, written by record
-  int32_t* flags;      // the handle's status word
+  int32_t* count;        // [work item][wave][nb3], written by count, read by record
+  long long* block_sum;  // totals of blocks of 1024 modes (scratch of the row pointers)
+  long long* row_ptr;    // [n_modes + 1] row offsets per mode, written by count
+  uint2* pairs;          // (m1, m2) of each entry, written by record
+  double2* factors;      // (c, d) of each entry, written by record
+  int32_t* flags;        // the handle's status word
 };
+size_t fused_max_items(const kaldo_crystal* c, long nq);  // (q, chunk) work items of a request
 template <typename T>
 int launch_fused_cache(const kaldo_crystal* c, const LwParams& p, int mode, const double* omega,
-                       const double* vel, const float4* modef, const double2* mrec,
-                       const uint8_t* phys, const uint8_t* sel, const double* evec,
-                       typename Cx<T>::type* eta, typename Cx<T>::type* phase_tab, int32_t* qlist,
+                       const float4* modef, const double2* mrec, const uint8_t* phys,
+                       const uint8_t* sel, const double* evec, typename Cx<T>::type* eta,
+                       typename Cx<T>::type* phase_tab, float4* window, int32_t* qlist,
                        int64_t n_subset, TcOut tc, hipStream_t st);
 template <typename T>
-int launch_fused(const kaldo_crystal* c, const LwParams& p, const double* omega, const double* vel,
-                 const float4* modef, const double* occ, const double2* mrec, const uint8_t* phys,
-                 const uint8_t* sel, const double* evec, typename Cx<T>::type* eta,
-                 typename Cx<T>::type* phase_tab, int32_t* qlist, double* part, int64_t n_subset,
-                 double scale, double* gamma, hipStream_t st);
+int launch_fused(const kaldo_crystal* c, const LwParams& p, const double* omega, const float4* modef,
+                 const double2* mrec, const uint8_t* phys, const uint8_t* sel, const double* evec,
+                 typename Cx<T>::type* eta, typename Cx<T>::type* phase_tab, float4* window,
+                 int32_t* qlist, double* part, int64_t n_subset, double scale, double* gamma,
+                 hipStream_t st);
 
 // Dense MFMA crystal kernel (lw_mfma.hip).
 bool mfma_supported(const kaldo_crystal* c);    // FP32 and BF16x3 forms

@@ -47,14 +47,6 @@ namespace kaldo {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f4;
 
-// Order LDS traffic between the lanes of one wave (no workgroup barrier:
-// the waves of a workgroup run different numbers of q1 iterations).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 enum DenseForm { kF64 = 0, kF32 = 1, kSplit = 2 };
 constexpr int kAccSlots = 16;   // sums a wave keeps per branch: lanes l, l + 16, ... share one in turn
 constexpr int kTileCand = 256;  // queue slots of a wave: one branch's candidates always fit
@@ -261,7 +253,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
 #pragma unroll
       for (int k = 0; k < 64; k += kAccSlots) {  // the lanes of one slot in turn
         if (lane >= k && lane < k + kAccSlots && e < n_cand) *a += c;
-        wave_sync();
+        lds_wave_sync();
       }
     }
     n_cand = 0;
@@ -284,7 +276,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
     const unsigned pk = __builtin_amdgcn_readlane(partner, n_done & 63);
     const int dbl = (int)(dbl_mask >> (n_done & 63) & 1ull);  // all wave-uniform
     const int q1 = pk & 0xffff, q2 = pk >> 16;
-    wave_sync();
+    lds_wave_sync();
     for (int k = lane; k < n_ph; k += 64) {
       const int d = slot_d[k];
       phb[k] = d >= 0 ? phase_tab[(size_t)q1 * p.n_d + d] : Cx<T>::make((T)0, (T)0);
@@ -298,7 +290,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
       d[3] = vel[3 * (size_t)m + 1];
       d[4] = vel[3 * (size_t)m + 2];
     }
-    wave_sync();
+    lds_wave_sync();
     // The branches of the group, in runs as long as the queue takes whole
     // branches (one run, as a rule): a run ends with its candidates resolved,
     // where none of its operand registers is live.
@@ -429,11 +421,11 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
         // T (rows row_of(r) of column lr, in registers) is the B operand of V
         V4 tr = {0, 0, 0, 0}, ti = {0, 0, 0, 0}, vr = {0, 0, 0, 0}, vi = {0, 0, 0, 0};
         if constexpr (kSpl) {
-          wave_sync();
+          lds_wave_sync();
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             bt[b_pos[i]] = Cx<T>::make(br[i], bi[i]);
-          wave_sync();
+          lds_wave_sync();
           f8 a1, a2;
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
@@ -494,7 +486,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
           n_cand += __popcll(mask[r]);
         }
       }
-      wave_sync();
+      lds_wave_sync();
       resolve(dbl);  // the queue never carries candidates past their partner
     } while (s < n_s);
   }

@@ -90,6 +90,9 @@ struct Fc3Bloch {
   int32_t* e_bg = nullptr;      // [n_e] 3*beta + gamma of entry e
   int32_t* blk_d = nullptr;     // [n_blk] d index of each block
   int32_t* pair_ptr = nullptr;  // [N_b*N_b + 1] block ranges per (jb, kb)
+  int n_f = 0;                  // distinct +-d
+  int32_t* fvec = nullptr;      // [n_f][3] one of each pair
+  int32_t* blk_f = nullptr;     // [n_blk] 2 * its index, + 1 where the block's d is minus it
   int max_pair_blk = 0;         // the longest of them
   // Work list for building one 16x16 B_s tile with a wave (3N_b <= 16):
   // slot k of lane l is entry k*64 + l of the (jc, kc) entries sorted by

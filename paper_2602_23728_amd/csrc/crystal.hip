@@ -131,6 +131,18 @@ static int build_bloch(kaldo_crystal* c, int64_t nnz, const int32_t* fi, const i
       e_blk[e] = blocks[{e_jc[e] / 3, e_kc[e] / 3, d}];
       e_bg[e] = (e_jc[e] % 3) * 3 + e_kc[e] % 3;
     }
+  // d and -d share a phase factor up to conjugation
+  std::vector<int32_t> fvec, f_of_d(n_d), blk_f;
+  for (int d = 0; d < n_d; ++d) {
+    int f = 0;
+    const int n_f = static_cast<int>(fvec.size() / 3);
+    while (f < n_f && !(fvec[3 * f] == -dvec[3 * d] && fvec[3 * f + 1] == -dvec[3 * d + 1] &&
+                        fvec[3 * f + 2] == -dvec[3 * d + 2]))
+      ++f;
+    f_of_d[d] = 2 * f + (f < n_f ? 1 : 0);
+    if (f == n_f) fvec.insert(fvec.end(), dvec.begin() + 3 * d, dvec.begin() + 3 * d + 3);
+  }
+  for (int32_t d : blk_d) blk_f.push_back(f_of_d[d]);
   // balanced work list for the 16x16 B_s tiles of the MFMA kernel
   std::vector<int4> bwork(256, int4{-1, 0, 0, 0});
   if (3 * nb <= 16) {
@@ -158,6 +170,9 @@ static int build_bloch(kaldo_crystal* c, int64_t nnz, const int32_t* fi, const i
   b.n_t = static_cast<int>(t_i.size());
   int rc;
   if ((rc = upload(c, &b.dvec, dvec))) return rc;
+  b.n_f = static_cast<int>(fvec.size() / 3);
+  if ((rc = upload(c, &b.fvec, fvec))) return rc;
+  if ((rc = upload(c, &b.blk_f, blk_f))) return rc;
   if ((rc = upload(c, &b.d_ptr, d_ptr))) return rc;
   if ((rc = upload(c, &b.e_jc, e_jc))) return rc;
   if ((rc = upload(c, &b.e_kc, e_kc))) return rc;

@@ -29,18 +29,18 @@
 
 namespace kaldo {
 
-// modef[m] = (v, omega) in FP32 for the sweep's pre-classification, omega
+// modef = (v, omega) in FP32 per mode for the sweep's pre-classification,
+// [q][branch]; with `freq` given (a sweep whose lanes run over q) [branch][q],
+// and omega alone in freq; omega
 // NaN below the frequency floor so that every comparison against the mode
 // fails, as the physical mask demands.  Also validates the mode's inputs:
 // a non-finite omega, v or eigenvector column raises kFlagNonFinite, an
 // imaginary mode (omega < 0) with |nu| >= nu_min raises kFlagImaginary.
-// mrec (when given): the FP64 record (w, n), (vx, vy), (vz, 0) the fused
-// kernel reads per partner, three 16-byte loads instead of six scattered ones.
 __global__ void lw_prepare(int n_modes, int nb3, const double* __restrict__ omega,
                            const double* __restrict__ vel, const double* __restrict__ evec,
                            double inv_kt_hbar, double nu_min, double* __restrict__ occ,
                            uint8_t* __restrict__ phys, uint8_t* __restrict__ sel,
-                           float4* __restrict__ modef, double2* __restrict__ mrec, int sel_all,
+                           float4* __restrict__ modef, float* __restrict__ freq, int sel_all,
                            int32_t* __restrict__ flags) {
   int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n_modes) return;
@@ -50,15 +50,13 @@ __global__ void lw_prepare(int n_modes, int nb3, const double* __restrict__ omeg
   occ[m] = p ? 1.0 / expm1(w * inv_kt_hbar) : 0.0;
   sel[m] = sel_all ? 1 : 0;
   const double v0 = vel[3 * (size_t)m], v1 = vel[3 * (size_t)m + 1], v2 = vel[3 * (size_t)m + 2];
-  modef[m] = make_float4((float)v0, (float)v1, (float)v2, p ? (float)w : __builtin_nanf(""));
-  if (mrec) {
-    mrec[3 * (size_t)m] = make_double2(w, occ[m]);
-    mrec[3 * (size_t)m + 1] = make_double2(v0, v1);
-    mrec[3 * (size_t)m + 2] = make_double2(v2, 0.0);
-  }
+  const int q = m / nb3, s = m - q * nb3;
+  const int at = freq ? s * (n_modes / nb3) + q : m;
+  const float wf = p ? (float)w : __builtin_nanf("");
+  modef[at] = make_float4((float)v0, (float)v1, (float)v2, wf);
+  if (freq) freq[at] = wf;
   // x - x is 0 for every finite x and NaN otherwise
   double chk = (w - w) + (v0 - v0) + (v1 - v1) + (v2 - v2);
-  const int q = m / nb3, s = m - q * nb3;
   const double* col = evec + ((size_t)q * nb3 * nb3 + s) * 2;
   for (int j = 0; j < nb3; ++j) chk += (col[2 * j * nb3] - col[2 * j * nb3]) + (col[2 * j * nb3 + 1] - col[2 * j * nb3 + 1]);
   if (!(chk == 0.0)) raise_flag(flags, kFlagNonFinite);
@@ -260,7 +258,7 @@ static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
 struct CrystalWs {
   CrystalPath path;
   size_t off_occ, off_phys, off_sel, off_eta, off_at, off_partial, off_phase, off_modef, off_qlist,
-      off_fpart, off_mrec, off_window, off_bsum, total;
+      off_fpart, off_rec, off_freq, off_window, off_bsum, total;
 };
 
 static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, CrystalPath path) {
@@ -284,15 +282,15 @@ static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, Cryst
     w.off_at = take(cs * nq * (size_t)c->bloch.n_e * nb3);
     w.off_partial = take(sizeof(double) * nq * nblk * nb3);
   } else if (w.path == CrystalPath::Fused) {
-    w.off_eta = take(cs * nq * nb3 * nb3);
-    w.off_phase = take(cs * nq * (size_t)std::max(1, c->bloch.n_d));
+    w.off_rec = take(fused_record_bytes(nb3, cs) * nq * nb3);
+    w.off_phase = take(fused_phase_bytes(nb3, c->bloch.n_f, cs) * nq);
     w.off_qlist = take(sizeof(int32_t) * (2 * nq + 1));
     // per work item the partial sums, or the cache's counts (four waves, int32) and
     // the 960 block totals of its row pointers
     w.off_fpart = take(2 * sizeof(double) * fused_max_items(c, nq) * nb3);
     w.off_window = take(sizeof(float4) * nq * nb3);
+    w.off_freq = take(sizeof(float) * nq * nb3);
     w.off_bsum = take(sizeof(long long) * ((nq * nb3 + 1023) / 1024));
-    w.off_mrec = take(sizeof(double2) * 3 * nq * nb3);
   } else {
     w.off_phase = take(cs * nq * (size_t)std::max(1, c->bloch.n_d));
   }
@@ -302,6 +300,12 @@ static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, Cryst
 
 static CrystalWs crystal_ws(const kaldo_crystal* c, long nq, int prec) {
   return crystal_ws_for(c, nq, prec, choose_path(c, nq, prec));
+}
+
+static FusedWs fused_ws(unsigned char* ws, const CrystalWs& w) {
+  return {ws + w.off_rec, ws + w.off_phase, reinterpret_cast<const float*>(ws + w.off_freq),
+          reinterpret_cast<float4*>(ws + w.off_window),
+          reinterpret_cast<int32_t*>(ws + w.off_qlist), reinterpret_cast<double*>(ws + w.off_fpart)};
 }
 
 template <typename T>
@@ -321,10 +325,10 @@ static int run_crystal(const kaldo_crystal* c, const int32_t* mesh, const double
   C* at = reinterpret_cast<C*>(ws + w.off_at);
   double* partial = reinterpret_cast<double*>(ws + w.off_partial);
   float4* modef = reinterpret_cast<float4*>(ws + w.off_modef);
-  double2* mrec = w.path == CrystalPath::Fused ? reinterpret_cast<double2*>(ws + w.off_mrec) : nullptr;
   const double inv_kt_hbar = kHbar / (kKb * T_k);
   KALDO_LAUNCH("lw_prepare", lw_prepare, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes,
-               nb3, omega, vel, evec, inv_kt_hbar, b->nu_min_thz, occ, phys, sel, modef, mrec,
+               nb3, omega, vel, evec, inv_kt_hbar, b->nu_min_thz, occ, phys, sel, modef,
+               w.path == CrystalPath::Fused ? reinterpret_cast<float*>(ws + w.off_freq) : nullptr,
                subset ? 0 : 1, c->d_flags);
   if (subset && n_subset > 0)
     KALDO_LAUNCH("lw_select", lw_select, dim3((n_subset + 255) / 256), dim3(256), 0, st, subset,
@@ -336,11 +340,7 @@ static int run_crystal(const kaldo_crystal* c, const int32_t* mesh, const double
                        kPrefactor / (double)nq, gamma, st);
   }
   if (path == CrystalPath::Fused) {
-    C* phase_tab = reinterpret_cast<C*>(ws + w.off_phase);
-    int32_t* qlist = reinterpret_cast<int32_t*>(ws + w.off_qlist);
-    double* fpart = reinterpret_cast<double*>(ws + w.off_fpart);
-    return launch_fused<T>(c, p, omega, modef, mrec, phys, sel, evec, eta, phase_tab,
-                           reinterpret_cast<float4*>(ws + w.off_window), qlist, fpart,
+    return launch_fused<T>(c, p, omega, occ, vel, modef, phys, sel, evec, fused_ws(ws, w),
                            subset ? n_subset : 0, kPrefactor / (double)nq, gamma, st);
   }
   long ne = nq * nb3 * nb3;
@@ -473,31 +473,23 @@ extern "C" int kaldo_tcache_build(const kaldo_crystal* c, const int32_t* mesh, c
   uint8_t* phys = ws + w.off_phys;
   uint8_t* sel = ws + w.off_sel;
   float4* modef = reinterpret_cast<float4*>(ws + w.off_modef);
-  double2* mrec = reinterpret_cast<double2*>(ws + w.off_mrec);
-  int32_t* qlist = reinterpret_cast<int32_t*>(ws + w.off_qlist);
   // the populations lw_prepare writes are not used: any temperature will do
   KALDO_LAUNCH("lw_prepare", lw_prepare, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes, nb3,
-               omega, vel, evec, kHbar / (kKb * 300.0), b->nu_min_thz, occ, phys, sel, modef, mrec,
-               modes_subset ? 0 : 1, c->d_flags);
+               omega, vel, evec, kHbar / (kKb * 300.0), b->nu_min_thz, occ, phys, sel, modef,
+               reinterpret_cast<float*>(ws + w.off_freq), modes_subset ? 0 : 1, c->d_flags);
   if (modes_subset)
     KALDO_LAUNCH("lw_select", lw_select, dim3((n_subset + 255) / 256), dim3(256), 0, st,
                  modes_subset, (long)n_subset, n_modes, sel, c->d_flags);
   const LwParams p = make_params(c, mesh, 300.0, b);
-  float4* window = reinterpret_cast<float4*>(ws + w.off_window);
+  const FusedWs fws = fused_ws(ws, w);
   TcOut tc{reinterpret_cast<int32_t*>(ws + w.off_fpart),
            reinterpret_cast<long long*>(ws + w.off_bsum), reinterpret_cast<long long*>(row_ptr),
            reinterpret_cast<uint2*>(pairs), reinterpret_cast<double2*>(factors), c->d_flags};
   const int64_t ns = modes_subset ? n_subset : 0;
   auto pass = [&](int mode) {
     if (precision == KALDO_FP64)
-      return launch_fused_cache<double>(c, p, mode, omega, modef, mrec, phys, sel, evec,
-                                        reinterpret_cast<double2*>(ws + w.off_eta),
-                                        reinterpret_cast<double2*>(ws + w.off_phase), window, qlist,
-                                        ns, tc, st);
-    return launch_fused_cache<float>(c, p, mode, omega, modef, mrec, phys, sel, evec,
-                                     reinterpret_cast<float2*>(ws + w.off_eta),
-                                     reinterpret_cast<float2*>(ws + w.off_phase), window, qlist, ns,
-                                     tc, st);
+      return launch_fused_cache<double>(c, p, mode, omega, occ, vel, modef, phys, sel, evec, fws, ns, tc, st);
+    return launch_fused_cache<float>(c, p, mode, omega, occ, vel, modef, phys, sel, evec, fws, ns, tc, st);
   };
   rc = pass(kModeCount);
   if (rc) return rc;

@@ -400,51 +400,64 @@ struct Partners {
 };
 
 // Live q-points (a selected physical mode) in increasing order, the inverse
-// map (-1 for the others) and their number.  One workgroup: thread t reads
-// the flags of q = t + 1024 r for every round r first (coalesced, all loads
-// in flight), then one block-wide scan per round orders the list.
-// (A template only so that every translation unit that launches it may
-// instantiate it from this header.)
-template <int kUnused = 0>
+// map (-1 for the others) and their number.  One workgroup: the flags of up to
+// 65536 q as 64-bit words in LDS, one scan over the words' bit counts (with a
+// scan per 1024 q the 24^3 mesh took 32 us).  kFlags: idx_of_q holds the flags
+// on entry (else they are read from the modes' masks).
+template <bool kFlags>
 __global__ __launch_bounds__(1024) void lw_live_q(int nq, int nb3, const uint8_t* __restrict__ phys,
                                                   const uint8_t* __restrict__ sel,
-                                                  int32_t* __restrict__ list,
-                                                  int32_t* __restrict__ idx_of_q,
+                                                  int32_t* __restrict__ list, int32_t* idx_of_q,
                                                   int32_t* __restrict__ count) {
-  __shared__ int wave_tot[2][16];
+  __shared__ unsigned long long live[1024];
+  __shared__ int first[1024];
+  __shared__ int wave_tot[16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int rounds = (nq + 1023) / 1024;  // <= 64 for N_q <= 65535
-  unsigned long long live = 0;
-  for (int r = 0; r < rounds; ++r) {
-    const int q = tid + 1024 * r;
-    int f = 0;
-    if (q < nq)
-      for (int s = 0; s < nb3; ++s) f |= phys[q * nb3 + s] & sel[q * nb3 + s];  // 0/1 bytes, no branch
-    live |= (unsigned long long)f << r;
-  }
-  int carry = 0;
-  for (int r = 0; r < rounds; ++r) {
-    const int q = tid + 1024 * r;
-    const int f = (int)(live >> r & 1ull);
-    int incl = f;
+  int done = 0;  // live q of the earlier 65536s
+  for (int q0 = 0; q0 < nq; q0 += 65536) {
+    const int n_w = (min(65536, nq - q0) + 63) / 64;
+#pragma unroll 4
+    for (int k = wv; k < n_w; k += 16) {
+      const int q = q0 + 64 * k + lane;
+      int f = 0;
+      if (q < nq) {
+        if constexpr (kFlags) {
+          f = idx_of_q[q];
+        } else {
+          for (int s = 0; s < nb3; ++s) f |= phys[q * nb3 + s] && sel[q * nb3 + s];
+        }
+      }
+      const unsigned long long m = __ballot(f != 0);
+      if (lane == 0) live[k] = m;
+    }
+    __syncthreads();
+    const int own = tid < n_w ? __popcll(live[tid]) : 0;
+    int incl = own;
     for (int off = 1; off < 64; off <<= 1) {
       const int v = __shfl_up(incl, off, 64);
       if (lane >= off) incl += v;
     }
-    if (lane == 63) wave_tot[r & 1][wv] = incl;  // double-buffered: one barrier per round
+    if (lane == 63) wave_tot[wv] = incl;
     __syncthreads();
-    int off = carry, tot = 0;
+    int at = done + incl - own;
     for (int k = 0; k < 16; ++k) {
-      off += (k < wv) ? wave_tot[r & 1][k] : 0;
-      tot += wave_tot[r & 1][k];
+      at += k < wv ? wave_tot[k] : 0;
+      done += wave_tot[k];
     }
-    if (q < nq) {
-      idx_of_q[q] = f ? off + incl - 1 : -1;
-      if (f) list[off + incl - 1] = q;
+    first[tid] = at;
+    __syncthreads();
+    for (int k = wv; k < n_w; k += 16) {
+      const int q = q0 + 64 * k + lane;
+      const unsigned long long m = live[k];
+      const int to = first[k] + __popcll(m & ((1ull << lane) - 1));
+      if (q < nq) {
+        idx_of_q[q] = m >> lane & 1 ? to : -1;
+        if (m >> lane & 1) list[to] = q;
+      }
     }
-    carry += tot;
+    __syncthreads();
   }
-  if (tid == 0) *count = carry;
+  if (tid == 0) *count = done;
 }
 
 // Every q taken as live (all modes selected): identity list and map.  A q
@@ -487,17 +500,24 @@ struct TcOut {
   int32_t* flags;        // the handle's status word
 };
 size_t fused_max_items(const kaldo_crystal* c, long nq);  // (q, chunk) work items of a request
+size_t fused_record_bytes(int nb3, size_t cs);            // of a mode's record, cs = bytes of a complex
+size_t fused_phase_bytes(int nb3, int n_f, size_t cs);    // of a mesh point's row of phases
+struct FusedWs {
+  unsigned char *rec, *phase_tab;  // mode records, phases
+  const float* freq;               // FP32 frequencies [branch][q], NaN below the floor
+  float4* window;                  // frequency ranges per box position and branch
+  int32_t* qlist;                  // live q, inverse map, number
+  double* part;                    // partial sums per work item
+};
 template <typename T>
 int launch_fused_cache(const kaldo_crystal* c, const LwParams& p, int mode, const double* omega,
-                       const float4* modef, const double2* mrec, const uint8_t* phys,
-                       const uint8_t* sel, const double* evec, typename Cx<T>::type* eta,
-                       typename Cx<T>::type* phase_tab, float4* window, int32_t* qlist,
-                       int64_t n_subset, TcOut tc, hipStream_t st);
+                       const double* occ, const double* vel, const float4* modef, const uint8_t* phys,
+                       const uint8_t* sel, const double* evec, const FusedWs& ws, int64_t n_subset,
+                       TcOut tc, hipStream_t st);
 template <typename T>
-int launch_fused(const kaldo_crystal* c, const LwParams& p, const double* omega, const float4* modef,
-                 const double2* mrec, const uint8_t* phys, const uint8_t* sel, const double* evec,
-                 typename Cx<T>::type* eta, typename Cx<T>::type* phase_tab, float4* window,
-                 int32_t* qlist, double* part, int64_t n_subset, double scale, double* gamma,
+int launch_fused(const kaldo_crystal* c, const LwParams& p, const double* omega, const double* occ,
+                 const double* vel, const float4* modef, const uint8_t* phys, const uint8_t* sel,
+                 const double* evec, const FusedWs& ws, int64_t n_subset, double scale, double* gamma,
                  hipStream_t st);
 
 // Dense MFMA crystal kernel (lw_mfma.hip).

@@ -12,24 +12,35 @@
 //  2. Each wave sweeps tiles of at most 64 partners q1, compact in q-space (a
 //     box of d0 x d1 x d2 mesh points, a lane per point); q2 = -q - q1 then
 //     runs over a box of the same shape.  The frequency ranges of both boxes,
-//     kept for every box position and branch (lw_windows), tell which (s', s'')
+//     kept for every box position and branch (lw_tables), tell which (s', s'')
 //     and which s of them can hold a pair inside the cut: 12 % of the (s', s'')
 //     and 4 % of the triples on the diamond 24^3 mesh with boxes of 4 x 4 x 4.
-//     Only those are classified per pair, in FP32 against a conservative band
-//     from the FP32 mode copies, and the near ones join the wave's queue in LDS
-//     in a fixed order.  When Phi3 is symmetric in its last two slots the
-//     ordered pair (q1 s', q2 s'') and its mirror (q2 s'', q1 s') have the same
-//     V, so only q1 <_lex q2 is swept (and q1 == q2 once) and an entry carries
-//     the terms of both orderings, each with its own cut.
-//  3. Full batches of 64 queued entries are weighted (exact FP64 cut) and
+//     Of those the pairs nearer than the boxes' widest cut, from the two
+//     frequencies alone, join the wave's first queue in LDS; a queue of 192 is
+//     classified in FP32 against a conservative band from the FP32 mode
+//     copies, 64 at a time, and the candidates join the second, in the same
+//     fixed order.  When Phi3 is symmetric in its last two slots the ordered
+//     pair (q1 s', q2 s'') and its mirror (q2 s'', q1 s') have the same V, so
+//     only q1 <_lex q2 is swept (and q1 == q2 once) and an entry carries the
+//     terms of both orderings, each with its own cut.
+//  3. Full batches of 64 candidates are weighted (exact FP64 cut) and
 //     projected, one per lane: V = sum_blocks e^{-i q1.R_d} sum_{beta,gamma}
 //     A~[blk][beta gamma][s] eta_{3jb+beta}(q1,s') eta_{3kb+gamma}(q2,s''),
 //     in the contraction type T, and w |V|^2 (FP64) added to the lane's
-//     per-branch sum.
+//     per-branch sum.  Cells of one and two atoms pull a batch's records and
+//     phases through LDS (pull_rows).
 //  4. A fixed butterfly per wave and the waves in order give this work item's
 //     partial sum; lw_fused_finish adds the chunks of a q in order.
 // Every order above depends on the inputs only, so results are bitwise
 // reproducible.  Waves never wait for each other between 1 and 4.
+//
+// What bounds it: the return path of the vector memory, 90 % busy, and beside it
+// the vector ALU, 62 % (diamond 24^3, FP64).  Of 5.6 ms there the projection
+// takes 3.4, the sweep 1.8, the classification 0.3, A~ 0.1.  One partner q1 per
+// lane in mesh order without ranges took 14.2 ms, boxes with ranges 8.4 (28
+// divergent loads a batch, and the classification at full (s', s'') cost);
+// records and phases through LDS, one phase per +-d and the two queues
+// 5.6 (FP32, diamond 15^3: 1.02, 0.69 and 0.57 ms).
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -41,11 +52,14 @@ namespace kaldo {
 
 constexpr int kFusedThreads = 256;
 constexpr int kFusedWaves = kFusedThreads / 64;
-constexpr int kQueue = 256;           // queue slots of a wave
-constexpr int kFlush = kQueue - 64;   // entries projected when it holds at least that many
+constexpr int kQueue = 256;           // slots of a wave's queue of near pairs
+constexpr int kFlush = kQueue - 64;   // classified when it holds at least that many
+constexpr int kPairs = 128;           // slots of its queue of candidates, projected 64 at a time
 
 // Waves per SIMD the register allocation targets: four for the small FP32
-// cells, three for the small FP64 cells, the compiler's choice otherwise.
+// cells (three 671 us against 565 on the diamond 15^3 mesh), three for the small
+// FP64 cells (two 8.1 ms against 6.3 on 24^3, four spill the vectors), the
+// compiler's choice otherwise.
 template <int NB, typename T>
 constexpr int fused_waves_per_eu() {
   return (NB <= 2 && sizeof(T) == 4) ? 4 : (NB <= 2 ? 3 : 1);
@@ -75,35 +89,6 @@ static Boxes choose_boxes(const int* N) {
   return best;
 }
 
-// Per box position (its lowest corner, any mesh point; boxes wrap) and branch:
-// the range of the physical frequencies (FP32, as the sweep classifies them;
-// lo > hi without any) and an upper bound of |v| h / sqrt(12), the speed's
-// share of the adaptive width (0 for a fixed width).
-__global__ void lw_windows(int n_modes, int nb3, int N0, int N1, int N2, Boxes box, float hs,
-                           const float4* __restrict__ modef, float4* __restrict__ window) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= n_modes) return;
-  const int q = m / nb3, s = m - q * nb3;
-  const int a0 = q / (N1 * N2), a1 = (q / N2) % N1, a2 = q % N2;
-  float lo = __builtin_inff(), hi = -__builtin_inff(), v2 = 0.0f;
-  for (int i = 0; i < box.d[0]; ++i) {
-    const int b0 = a0 + i < N0 ? a0 + i : a0 + i - N0;
-    for (int j = 0; j < box.d[1]; ++j) {
-      const int b1 = a1 + j < N1 ? a1 + j : a1 + j - N1;
-      for (int k = 0; k < box.d[2]; ++k) {
-        const int b2 = a2 + k < N2 ? a2 + k : a2 + k - N2;
-        const float4 f = modef[((b0 * N1 + b1) * N2 + b2) * nb3 + s];
-        if (f.w == f.w) {  // NaN: below the floor
-          lo = fminf(lo, f.w);
-          hi = fmaxf(hi, f.w);
-          v2 = fmaxf(v2, f.x * f.x + f.y * f.y + f.z * f.z);
-        }
-      }
-    }
-  }
-  window[m] = make_float4(lo, hi, sqrtf(v2) * hs * 1.000001f, 0.0f);
-}
-
 // Gamma of the selected modes: the chunk sums of their q in chunk order.
 __global__ void lw_fused_finish(int n_modes, int nb3, const uint8_t* __restrict__ phys,
                                 const uint8_t* __restrict__ sel, const int32_t* __restrict__ idx_of_q,
@@ -121,6 +106,180 @@ __global__ void lw_fused_finish(int n_modes, int nb3, const uint8_t* __restrict_
   gamma[m] = scale * acc;
 }
 
+// Record of a mode: FP64 w, n, v_x, v_y, v_z, then its eigenvector.  An FP64
+// eigenvector is turned so that its first component is real (|V| does not
+// depend on it) and that component takes eight bytes; so does the first
+// component of an FP32 one.  The record of a two-atom cell is then 128 bytes
+// in FP64, one cache line, and 88 in FP32, kept in one.
+template <int NB, typename T>
+__host__ __device__ constexpr int record_used() {  // whole 16-byte pieces
+  return (48 + (3 * NB - 1) * 2 * (int)sizeof(T) + 15) / 16 * 16;
+}
+__host__ __device__ constexpr int record_stride(int used) { return used > 64 && used < 128 ? 128 : used; }
+size_t fused_record_bytes(int nb3, size_t cs) {
+  return record_stride((int)((48 + (nb3 - 1) * cs + 15) / 16 * 16));
+}
+// Row of a q-point's phases e^{-i q.R_f}, one per +-d (n_f complex T), padded
+// to a size that a kernel may stage where records are staged.
+size_t fused_phase_bytes(int nb3, int n_f, size_t cs) {
+  const size_t need = n_f * cs;
+  return nb3 > 6 || need > 64 ? need : 64;
+}
+
+// Everything the sweep reads beside the FC3 tables, one launch, a job a range
+// of blocks (first[k] .. first[k + 1]):
+//   0  mode records
+//   1  phases e^{-i q1.R_f} of every mesh point, FP64 rounded to T
+//   2  per box position (its lowest corner, any mesh point; boxes wrap) and
+//      branch, four lanes each: the range of the physical frequencies (FP32, as
+//      the sweep classifies them; lo > hi without any) and an upper bound of
+//      |v| h / sqrt(12), the speed's share of the adaptive width (0 when fixed)
+//   3  the list of every q; given a subset, the flags lw_live_q makes it from
+struct TableJobs {
+  unsigned first[5];
+};
+template <typename T>
+__global__ __launch_bounds__(256) void lw_tables(
+    TableJobs jobs, LwParams p, Boxes box, float hs, int rb, int phase_bytes, int subset,
+    const double* __restrict__ evec, const double* __restrict__ omega, const double* __restrict__ occ,
+    const double* __restrict__ vel, const float4* __restrict__ modef, const uint8_t* __restrict__ phys,
+    const uint8_t* __restrict__ sel, const int32_t* __restrict__ fvec, int n_f,
+    unsigned char* __restrict__ rec, unsigned char* __restrict__ phase_tab,
+    float4* __restrict__ window, int32_t* __restrict__ list, int32_t* __restrict__ idx_of_q,
+    int32_t* __restrict__ count) {
+  using C = typename Cx<T>::type;
+  const int nb3 = p.nb3, N0 = p.N[0], N1 = p.N[1], N2 = p.N[2];
+  constexpr bool kTurned = sizeof(T) == 8;
+  const unsigned blk = blockIdx.x;
+  if (blk < jobs.first[1]) {
+    const unsigned k = (blk - jobs.first[0]) * 256 + threadIdx.x;
+    const unsigned m = k / nb3, j = k - m * nb3;
+    if (m >= (unsigned)(p.nq * nb3)) return;
+    unsigned char* r = rec + (size_t)m * rb;
+    const unsigned q = m / nb3, s = m - q * nb3;
+    const double2* e = reinterpret_cast<const double2*>(evec) + (size_t)q * nb3 * nb3 + s;
+    double2 x = e[j * nb3], turn = make_double2(1.0, 0.0);
+    const double2 x0 = e[0];
+    const double a0 = hypot(x0.x, x0.y);
+    if (kTurned && a0 > 1e-200) turn = make_double2(x0.x / a0, -x0.y / a0);
+    if (j == 0) {
+      double2* d = reinterpret_cast<double2*>(r);
+      const double* v = vel + 3 * (size_t)m;
+      d[0] = make_double2(omega[m], occ[m]);
+      d[1] = make_double2(v[0], v[1]);
+      double first = a0;
+      if constexpr (!kTurned) {
+        const C f = Cx<T>::make((T)x0.x, (T)x0.y);
+        first = __builtin_bit_cast(double, f);
+      }
+      d[2] = make_double2(v[2], first);
+    } else {
+      if constexpr (kTurned) x = make_double2(x.x * turn.x - x.y * turn.y, x.x * turn.y + x.y * turn.x);
+      reinterpret_cast<C*>(r + 48)[j - 1] = Cx<T>::make((T)x.x, (T)x.y);
+    }
+  } else if (blk < jobs.first[2]) {
+    const unsigned k = (blk - jobs.first[1]) * 256 + threadIdx.x;
+    if (n_f == 0 || k >= (unsigned)p.nq * (unsigned)n_f) return;
+    const int q1 = k / n_f, d = k - q1 * n_f;
+    const int b0 = q1 / (N1 * N2), b1 = (q1 / N2) % N1, b2 = q1 % N2;
+    const int32_t* r = fvec + 3 * d;
+    const int m0 = ((b0 * r[0]) % N0 + N0) % N0, m1 = ((b1 * r[1]) % N1 + N1) % N1,
+              m2 = ((b2 * r[2]) % N2 + N2) % N2;
+    const double f = (double)m0 / N0 + (double)m1 / N1 + (double)m2 / N2;
+    double sn, cs;
+    sincospi(-2.0 * f, &sn, &cs);
+    reinterpret_cast<C*>(phase_tab + (size_t)q1 * phase_bytes)[d] = Cx<T>::make((T)cs, (T)sn);
+  } else if (blk < jobs.first[3]) {
+    const unsigned k = (blk - jobs.first[2]) * 256 + threadIdx.x;
+    const int s_of = (k >> 2) / p.nq, q_of = (k >> 2) - s_of * p.nq, m = q_of * nb3 + s_of;
+    float lo = __builtin_inff(), hi = -__builtin_inff(), v2 = 0.0f;
+    const bool in = s_of < nb3;
+    if (in) {
+      const int q = q_of, s = s_of;
+      const int a0 = q / (N1 * N2), a1 = (q / N2) % N1, a2 = q % N2;
+      for (int ij = k & 3; ij < box.d[0] * box.d[1]; ij += 4) {
+        const int i = ij / box.d[1], j = ij - i * box.d[1];
+        const int b0 = a0 + i < N0 ? a0 + i : a0 + i - N0, b1 = a1 + j < N1 ? a1 + j : a1 + j - N1;
+        const float4* row = modef + s * p.nq + (b0 * N1 + b1) * N2;
+        for (int c = 0; c < box.d[2]; ++c) {
+          const float4 f = row[a2 + c < N2 ? a2 + c : a2 + c - N2];
+          if (f.w == f.w) {  // NaN: below the floor
+            lo = fminf(lo, f.w);
+            hi = fmaxf(hi, f.w);
+            v2 = fmaxf(v2, f.x * f.x + f.y * f.y + f.z * f.z);
+          }
+        }
+      }
+    }
+    for (int off = 1; off < 4; off <<= 1) {
+      lo = fminf(lo, __shfl_xor(lo, off, 64));
+      hi = fmaxf(hi, __shfl_xor(hi, off, 64));
+      v2 = fmaxf(v2, __shfl_xor(v2, off, 64));
+    }
+    if (in && (k & 3) == 0) window[m] = make_float4(lo, hi, sqrtf(v2) * hs * 1.000001f, 0.0f);
+  } else {
+    const int q = (blk - jobs.first[3]) * 256 + threadIdx.x;
+    if (q < p.nq && subset) {
+      int f = 0;
+      for (int s = 0; s < nb3; ++s) f |= phys[q * nb3 + s] && sel[q * nb3 + s];
+      idx_of_q[q] = f;
+    } else if (q < p.nq) {
+      list[q] = q;
+      idx_of_q[q] = q;
+      if (q == 0) *count = p.nq;
+    }
+  }
+}
+
+// 16 CH bytes of each lane's row (tab + idx * stride) into LDS.  CH
+// neighbouring lanes fetch a row's 16-byte pieces side by side, so that an
+// instruction covers 64 / CH rows with whole cache lines: a lane fetching its
+// own row piece by piece holds the return path for 64 cycles an instruction,
+// and that path bounded the kernel (96 % busy on the diamond 24^3 mesh in
+// FP64).  The pieces go to LDS directly, 64 consecutive ones an instruction:
+// CH instructions, no registers.  Row l lies at st + 16 CH l, its pieces
+// exchanged by pull_swap(l) where rows of a power of two of bytes would put
+// every lane's on the same banks; pulled() gives a byte of the lane's own row.
+// `st` is the wave's own; returns when the rows are there.
+template <int CH>
+__device__ __forceinline__ int pull_swap(int row) {
+  return CH == 8 ? (row >> 1) & 7 : CH == 4 ? (row >> 2) & 3 : 0;
+}
+template <int CH>
+__device__ __forceinline__ void pull_rows(const unsigned char* tab, int stride, int idx,
+                                          unsigned char* st, int lane) {
+  auto piece = [&](int k, int row, int byte) {  // row's index from the lane that holds it
+    const unsigned off = (unsigned)__builtin_amdgcn_ds_bpermute(row, idx) * stride + byte;
+    __builtin_amdgcn_global_load_lds(
+        (const __attribute__((address_space(1))) void*)(tab + (size_t)off),
+        (__attribute__((address_space(3))) void*)(st + 1024 * k), 16, 0, 0);
+  };
+  if constexpr (CH == 8 || CH == 4) {
+    // 64 / CH rows on, pull_swap flips bit 2 (eight pieces) or nothing (four)
+    int row = lane / CH * 4, byte = 16 * (lane % CH ^ pull_swap<CH>(lane / CH));
+    asm volatile("" : "+v"(row), "+v"(byte));  // not kept in registers from batch to batch
+#pragma unroll
+    for (int k = 0; k < CH; ++k) piece(k, row + 4 * (64 / CH) * k, CH == 8 && k & 1 ? byte ^ 64 : byte);
+  } else {
+    int row = lane / CH * 4, part = lane % CH;
+    asm volatile("" : "+v"(row), "+v"(part));
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      piece(k, row, 16 * part);
+      part += 64 % CH;
+      row += 4 * (64 / CH) + (part >= CH ? 4 : 0);
+      part -= part >= CH ? CH : 0;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  lds_wave_sync();
+}
+template <int CH>
+__device__ __forceinline__ const unsigned char* pulled(const unsigned char* st, int lane, int byte) {
+  const int row = lane * (16 * CH) + 16 * pull_swap<CH>(lane);
+  return st + (CH == 8 || CH == 4 ? row ^ byte : row + byte);
+}
+
 // MODE (FusedMode): kModeGamma sums the linewidth terms into `part`;
 // kModeCount makes only the cut decisions and writes the number of passing
 // entries per wave and branch to tc.count; kModeRecord makes the same
@@ -128,19 +287,18 @@ __global__ void lw_fused_finish(int n_modes, int nb3, const uint8_t* __restrict_
 // temperature-independent factors at a fixed place of its mode's row: the row
 // start, plus the counts of the earlier waves of its q, plus its rank among
 // the wave's entries of that branch in queue order.
-template <int NB, typename T, int MODE = kModeGamma>
+template <int NB, typename T, int MODE, int STAGE>
 __global__ __launch_bounds__(kFusedThreads)
 __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
     LwParams p, Boxes box, int n_rep, const int32_t* __restrict__ rep,
-    const double* __restrict__ omega, const float4* __restrict__ modef,
-    const double2* __restrict__ mrec, const uint8_t* __restrict__ phys,
-    const uint8_t* __restrict__ sel, const double* __restrict__ evec,
-    const typename Cx<T>::type* __restrict__ etaT,
-    const typename Cx<T>::type* __restrict__ phase_tab, const float4* __restrict__ window,
+    const double* __restrict__ omega, const float4* __restrict__ modef, const float* __restrict__ freq,
+    const uint8_t* __restrict__ phys, const uint8_t* __restrict__ sel,
+    const double* __restrict__ evec, const unsigned char* __restrict__ rec,
+    const unsigned char* __restrict__ phase_tab, int phase_bytes, const float4* __restrict__ window,
     const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_i,
     const int32_t* __restrict__ t_l2, const double* __restrict__ t_coef,
     const int32_t* __restrict__ e_blk, const int32_t* __restrict__ e_bg,
-    const int32_t* __restrict__ blk_d, const int32_t* __restrict__ pair_ptr,
+    const int32_t* __restrict__ blk_f, const int32_t* __restrict__ pair_ptr,
     const int32_t* __restrict__ live_list, const int32_t* __restrict__ n_live_ptr, int n_chunk,
     double* __restrict__ part, TcOut tc) {
   constexpr int NB3 = 3 * NB;
@@ -148,13 +306,23 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
   constexpr bool kRecord = MODE == kModeRecord;
   using C = typename Cx<T>::type;
   extern __shared__ double2 smem[];
-  C* at = reinterpret_cast<C*>(smem);  // [n_blk][9][NB3]
+  // STAGE: a batch's records (1), its rows of phases too (2) are pulled through
+  // LDS, one buffer a wave; 0: each lane fetches its own
+  constexpr int RB = record_used<NB, T>(), kStride = record_stride(RB);
+  constexpr int kPullBytes = MODE == kModeCount ? 48 : RB;  // >= 64 where phases are staged
+  unsigned char* st = reinterpret_cast<unsigned char*>(smem) +
+                      __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (64 * kPullBytes);
+  C* at = reinterpret_cast<C*>(reinterpret_cast<unsigned char*>(smem) +
+                               (STAGE ? kFusedWaves * 64 * kPullBytes : 0));  // [n_blk][9][NB3]
   __shared__ uint32_t wq_q[kFusedWaves][kQueue];     // q1 | q2 << 16
   __shared__ uint16_t wq_code[kFusedWaves][kQueue];  // s | s' << 4 | s'' << 8 | both orderings << 12
+  __shared__ uint32_t cq_q[kFusedWaves][kPairs];
+  __shared__ uint16_t cq_code[kFusedWaves][kPairs];
   __shared__ long long rbase[kRecord ? kFusedWaves : 1][NB3];  // where the wave's entries of a branch start
   __shared__ int rlim[kRecord ? kFusedWaves : 1][NB3];         // and how many the count pass found
   __shared__ double2 phq[64];
   __shared__ double wq64[NB3];
+  __shared__ float wq32[NB3];
   __shared__ double red[kFusedWaves][NB3];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -183,7 +351,10 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
     live |= on ? (1u << s) : 0u;
     if (lane == s && on) w_lane = w;
   }
-  if (tid < NB3) wq64[tid] = omega[q * NB3 + tid];
+  if (tid < NB3) {
+    wq64[tid] = omega[q * NB3 + tid];
+    wq32[tid] = (float)omega[q * NB3 + tid];
+  }
   const int sub = wk * kFusedWaves + wv;  // this wave's place among the counts
   if constexpr (kRecord) {
     if (lane < NB3) {
@@ -225,6 +396,7 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
     __syncthreads();
   }
 
+  constexpr int kPhaseCh = 4;
   double acc[NB3];
   int run[NB3];  // cache passes: entries of each branch so far (wave-uniform)
 #pragma unroll
@@ -234,20 +406,57 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
   }
 
   // 3. entries [0, n) of the wave's queue
-  auto process = [&](int n) {
-    for (int base = 0; base < n; base += 64) {
-      const int r = base + lane;
+  auto project = [&](int n) {
+    {
+      const int r = lane;
       const bool on = r < n;
-      const uint32_t qq = on ? wq_q[wv][r] : 0u;
-      const int code = on ? wq_code[wv][r] : 0;
+      const uint32_t qq = on ? cq_q[wv][r] : 0u;
+      const int code = on ? cq_code[wv][r] : 0;
       const int q1 = qq & 0xffff, q2 = qq >> 16;
       const int s = code & 15, s1 = (code >> 4) & 15, s2 = (code >> 8) & 15, dbl = code >> 12;
       const int m1 = q1 * NB3 + s1, m2 = q2 * NB3 + s2;
-      // the partners' packed (w, n, v) records
-      const double2 ra1 = mrec[3 * (size_t)m1], rb1 = mrec[3 * (size_t)m1 + 1],
-                    rc1 = mrec[3 * (size_t)m1 + 2];
-      const double2 ra2 = mrec[3 * (size_t)m2], rb2 = mrec[3 * (size_t)m2 + 1],
-                    rc2 = mrec[3 * (size_t)m2 + 2];
+      // the partners' eigenvectors and (w, n, v)
+      C x[NB3], y[NB3];
+      double2 ra1, rb1, rc1, ra2, rb2, rc2;
+      constexpr int CH = kPullBytes / 16;
+      auto tail = [&](auto at_byte, double2& a, double2& b, double2& c) {
+        a = *reinterpret_cast<const double2*>(at_byte(0));
+        b = *reinterpret_cast<const double2*>(at_byte(16));
+        c = *reinterpret_cast<const double2*>(at_byte(32));
+      };
+      auto vector = [&](auto at_byte, double first, C* e) {
+        if constexpr (sizeof(T) == 8)
+          e[0] = Cx<T>::make((T)first, (T)0);
+        else
+          e[0] = Cx<T>::make(__int_as_float(__double2loint(first)), __int_as_float(__double2hiint(first)));
+        constexpr int kPer = 16 / sizeof(C);
+#pragma unroll
+        for (int j = 1; j < NB3; j += kPer) {
+          typedef T Piece __attribute__((ext_vector_type(16 / sizeof(T))));
+          const Piece v = *reinterpret_cast<const Piece*>(at_byte(48 + (j - 1) * (int)sizeof(C)));
+          e[j] = Cx<T>::make(v[0], v[1]);
+          if constexpr (kPer == 2) {
+            if (j + 1 < NB3) e[j + 1] = Cx<T>::make(v[kPer], v[kPer + 1]);
+          }
+        }
+      };
+      int own_lane = lane;
+      asm volatile("" : "+v"(own_lane));  // its addresses are not kept from batch to batch
+      auto own = [&](int byte) { return pulled<CH>(st, own_lane, byte); };
+      const unsigned char *r1 = rec + (size_t)m1 * kStride, *r2 = rec + (size_t)m2 * kStride;
+      auto far1 = [&](int byte) { return r1 + byte; };
+      auto far2 = [&](int byte) { return r2 + byte; };
+      if constexpr (STAGE) {
+        pull_rows<CH>(rec, kStride, m1, st, lane);
+        tail(own, ra1, rb1, rc1);
+        if constexpr (MODE != kModeCount) vector(own, rc1.y, x);
+        lds_wave_sync();
+        pull_rows<CH>(rec, kStride, m2, st, lane);
+        tail(own, ra2, rb2, rc2);
+      } else {
+        tail(far1, ra1, rb1, rc1);
+        tail(far2, ra2, rb2, rc2);
+      }
       const double w1 = ra1.x, w2 = ra2.x, w = wq64[s];
       const double v1[3] = {rb1.x, rb1.y, rc1.x}, v2[3] = {rb2.x, rb2.y, rc2.x};
       // cache passes: the exact decision, and the entry's place in its row
@@ -267,22 +476,54 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
                                                       __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
           run[k] += __popcll(m);
         }
-        if constexpr (MODE == kModeCount) continue;
       }
-      if (!pass) continue;
-      double sp, sm;
-      widths_v(p, v1, v2, sp, sm);
-      C x[NB3], y[NB3];
-      const C* xs = etaT + ((size_t)q1 * NB3 + s1) * NB3;
-      const C* ys = etaT + ((size_t)q2 * NB3 + s2) * NB3;
-#pragma unroll
-      for (int j = 0; j < NB3; ++j) {
-        x[j] = xs[j];
-        y[j] = ys[j];
+      if constexpr (MODE == kModeCount) {
+        if constexpr (STAGE) lds_wave_sync();
+        return;
       }
-      double wt = 0.0;
-      if constexpr (MODE == kModeGamma) wt = pair_weight_both(p, dbl, w, w1, w2, ra1.y, ra2.y, sp, sm);
-      const C* ph = phase_tab + (size_t)q1 * p.n_d;
+      // the weight before the second eigenvector and the phases arrive: what
+      // it needs and what V needs are then not live together
+      double wt = 0.0, am = 0.0;
+      if (pass) {
+        double sp, sm;
+        widths_v(p, v1, v2, sp, sm);
+        if constexpr (kRecord) {
+          // a+ (n1 - n2) + 1/2 a- (n1 + n2 + 1) of this ordering plus, when
+          // the entry stands for both, the mirrored one's a+r (n2 - n1) +
+          // 1/2 a-r (n1 + n2 + 1): stored as c (n1 - n2) + d (n1 + n2 + 1)
+          pair_factors(p, w, w1, w2, sp, sm, wt, am);
+          if (dbl) {
+            double apr, amr;
+            pair_factors(p, w, w2, w1, sp, sm, apr, amr);
+            wt -= apr;
+            am += amr;
+          }
+        } else {
+          wt = pair_weight_both(p, dbl, w, w1, w2, ra1.y, ra2.y, sp, sm);
+        }
+      }
+      if constexpr (STAGE) {
+        asm volatile("" : "+v"(own_lane) : "v"(wt));  // after the weight
+        vector(own, rc2.y, y);
+        lds_wave_sync();
+        if constexpr (STAGE == 2) pull_rows<kPhaseCh>(phase_tab, 16 * kPhaseCh, q1, st, lane);
+      } else {
+        vector(far1, rc1.y, x);
+        vector(far2, rc2.y, y);
+      }
+      if (pass) {
+      const C* ph = reinterpret_cast<const C*>(phase_tab + (size_t)q1 * phase_bytes);
+      auto phase = [&](int blk) {
+        const int f = blk_f[blk];
+        const int byte = (f >> 1) * (int)sizeof(C);
+        C v;
+        if constexpr (STAGE == 2)
+          v = *reinterpret_cast<const C*>(pulled<kPhaseCh>(st, own_lane, byte));
+        else
+          v = ph[f >> 1];
+        if (f & 1) v.y = -v.y;
+        return v;
+      };
       T vr = 0, vi = 0;
       // V = sum_blk f_blk sum_beta x_beta (sum_gamma A~[blk][beta gamma] y_gamma):
       // complex multiply-adds as chains of fused multiply-adds into the
@@ -290,12 +531,12 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
       // costs a multiply, a fused one and an add per component), and no
       // x (x) y table (nine complex values a block would have to keep or
       // recompute)
-      // One block's term f_blk x_jb^T A~_blk y_kb into (vr, vi).  The FP64
-      // Gamma pass loads the three values of a row of the block together
-      // and fetches each block's phase one block ahead, so that the
-      // latencies fall under arithmetic; the FP32 form and the record pass
-      // have no registers left for either.
-      constexpr bool kAhead = sizeof(T) == 8 && MODE == kModeGamma;
+      // One block's term f_blk x_jb^T A~_blk y_kb into (vr, vi).  With phases
+      // from memory the FP64 Gamma pass loads the three values of a row of
+      // the block together and fetches each block's phase one block ahead, so
+      // that the latencies fall under arithmetic; the other forms have no
+      // registers left for either.
+      constexpr bool kAhead = sizeof(T) == 8 && MODE == kModeGamma && STAGE == 0;
       auto block_term = [&](const C* ab, const C f, int jb, int kb) {
         T ur = 0, ui = 0;
 #pragma unroll
@@ -310,16 +551,22 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
           for (int ga = 0; ga < 3; ++ga) {
             if constexpr (!kAhead) a[ga] = ab[(be * 3 + ga) * NB3];
             const C v = y[3 * kb + ga];
+            const bool real = sizeof(T) == 8 && 3 * kb + ga == 0;  // a turned eigenvector's first component
             tr = fma(a[ga].x, v.x, tr);
-            tr = fma(-a[ga].y, v.y, tr);
-            ti = fma(a[ga].x, v.y, ti);
+            if (!real) {
+              tr = fma(-a[ga].y, v.y, tr);
+              ti = fma(a[ga].x, v.y, ti);
+            }
             ti = fma(a[ga].y, v.x, ti);
           }
           const C u = x[3 * jb + be];
+          const bool real = sizeof(T) == 8 && 3 * jb + be == 0;
           ur = fma(u.x, tr, ur);
-          ur = fma(-u.y, ti, ur);
           ui = fma(u.x, ti, ui);
-          ui = fma(u.y, tr, ui);
+          if (!real) {
+            ur = fma(-u.y, ti, ur);
+            ui = fma(u.y, tr, ui);
+          }
         }
         vr = fma(f.x, ur, vr);
         vr = fma(-f.y, ui, vr);
@@ -333,37 +580,26 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
           const int b_lo = pair_ptr[jb * NB + kb], b_hi = pair_ptr[jb * NB + kb + 1];
           if constexpr (kAhead) {
             C f_next = Cx<T>::make((T)0, (T)0);
-            if (b_lo < b_hi) f_next = ph[blk_d[b_lo]];
+            if (b_lo < b_hi) f_next = phase(b_lo);
             for (int blk = b_lo; blk < b_hi; ++blk) {
               const C f = f_next;
-              if (blk + 1 < b_hi) f_next = ph[blk_d[blk + 1]];
+              if (blk + 1 < b_hi) f_next = phase(blk + 1);
               block_term(at + (size_t)blk * 9 * NB3 + s, f, jb, kb);
             }
           } else {
             for (int blk = b_lo; blk < b_hi; ++blk)
-              block_term(at + (size_t)blk * 9 * NB3 + s, ph[blk_d[blk]], jb, kb);
+              block_term(at + (size_t)blk * 9 * NB3 + s, phase(blk), jb, kb);
           }
         }
       }
       const double vv = (double)vr * (double)vr + (double)vi * (double)vi;
       if constexpr (kRecord) {
-        // a+ (n1 - n2) + 1/2 a- (n1 + n2 + 1) of this ordering plus, when
-        // the entry stands for both, the mirrored one's a+r (n2 - n1) +
-        // 1/2 a-r (n1 + n2 + 1): stored as c (n1 - n2) + d (n1 + n2 + 1)
-        double ap, am;
-        pair_factors(p, w, w1, w2, sp, sm, ap, am);
-        if (dbl) {
-          double apr, amr;
-          pair_factors(p, w, w2, w1, sp, sm, apr, amr);
-          ap -= apr;
-          am += amr;
-        }
         // both passes take the same decisions, so the rank is below the
         // count; a write outside this wave's share is refused
         if (rank < rlim[wv][s]) {
           const long long dst = rbase[wv][s] + rank;
           tc.pairs[dst] = make_uint2((unsigned)m1, (unsigned)m2);
-          tc.factors[dst] = make_double2(vv * ap, 0.5 * (vv * am));
+          tc.factors[dst] = make_double2(vv * wt, 0.5 * (vv * am));
         } else {
           raise_flag(tc.flags, kFlagCache);
         }
@@ -371,6 +607,56 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
         const double c = wt * vv;
 #pragma unroll
         for (int k = 0; k < NB3; ++k) acc[k] += (k == s) ? c : 0.0;
+      }
+      }
+      if constexpr (STAGE) lds_wave_sync();  // the buffer is free again
+    }
+  };
+
+  // FP32 classification of the first n near pairs from the mode copies: a
+  // candidate is any process with |x| < hi, the band's upper edge.  The
+  // coalescence |x+| = |w + cp| and that of the mirrored ordering, |w - cp|
+  // (= (w + w2) - w1), share the edge bp, and for w >= 0 the smaller of the two
+  // is |w - |cp||, bitwise in FP32 (w + cp and w - cp round monotonically); so
+  // one test covers both, with cpe = -|cp| on mirrored entries and cp
+  // otherwise.  The decay |x-| is the same FP32 number for both.
+  int n_cand = 0;  // wave-uniform
+  auto classify = [&](int n, bool last) {
+    for (int base = 0; base < n || (last && base == 0); base += 64) {
+      const int r = base + lane;
+      const bool on = r < n;
+      const uint32_t qq = on ? wq_q[wv][r] : 0u;
+      const int code = on ? wq_code[wv][r] : 0;
+      const bool dbl = code >> 12;
+      const float4 f1 = modef[((code >> 4) & 15) * p.nq + (qq & 0xffff)];
+      const float4 f2 = modef[((code >> 8) & 15) * p.nq + (qq >> 16)];
+      const float w = wq32[code & 15];
+      float s2p, s2m, e_sig;
+      widths2_f(p, f1, f2, s2p, s2m, e_sig);
+      const float scl = wq_abs_max + fabsf(f1.w) + fabsf(f2.w);
+      const float bp = make_band_f(s2p, scl, e_sig).hi, bm = make_band_f(s2m, scl, e_sig).hi;
+      const float cp = f1.w - f2.w, cm = -f1.w - f2.w;
+      const float cpe = dbl ? -fabsf(cp) : cp;
+      const bool near = on && (fabsf(w + cpe) < bp || fabsf(w + cm) < bm);
+      const unsigned long long m = __ballot(near);
+      if (near) {
+        const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((unsigned)m, n_cand));
+        cq_q[wv][slot] = qq;
+        cq_code[wv][slot] = (uint16_t)code;
+      }
+      n_cand += __popcll(m);
+      lds_wave_sync();
+      while (n_cand >= 64 || (last && base + 64 >= n && n_cand > 0)) {
+        project(min(n_cand, 64));
+        // the rest, fewer than 64, moves to the front
+        n_cand = max(n_cand - 64, 0);
+        const uint32_t mq = cq_q[wv][64 + lane];
+        const uint16_t mc = cq_code[wv][64 + lane];
+        lds_wave_sync();
+        cq_q[wv][lane] = mq;
+        cq_code[wv][lane] = mc;
+        lds_wave_sync();
       }
     }
   };
@@ -412,11 +698,12 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
       // 1e-6 of the frequencies) covers the bands' own margins and the rounding
       // of these tests, so no pair that passes its exact cut is dropped.
       unsigned bits = 0;
+      float reach = 0.0f;
       const int cb = g + lane;
       if (cb < NB3 * NB3) {
         const float4 u = win1[cb / NB3], v = win2[cb % NB3];
         if (u.x <= u.y && v.x <= v.y) {
-          const float reach = fmaxf(r_min, hr * (u.z + v.z)) + 1e-6f * (wq_abs_max + u.y + v.y) + 1e-8f;
+          reach = fmaxf(r_min, hr * (u.z + v.z)) + 1e-6f * (wq_abs_max + u.y + v.y) + 1e-8f;
           const float dlo = u.x - v.y, dhi = u.y - v.x;  // w1 - w2
           const float slo = u.x + v.x, shi = u.y + v.y;  // w1 + w2
 #pragma unroll
@@ -432,40 +719,35 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
       }
       unsigned long long todo = __ballot(bits != 0);
       if (!todo) continue;
-      // the mode copies one (s', s'') ahead
-      int l = __ffsll((long long)todo) - 1;
-      float4 f1n = modef[q1 * NB3 + (g + l) / NB3], f2n = modef[q2 * NB3 + (g + l) % NB3];
+      // the frequencies of the lane's points, w2 one (s', s'') ahead; the
+      // same reach holds point by point, so a pair outside it fails its
+      // classification too
+      int l = __ffsll((long long)todo) - 1, row = -1;
+      float w1 = 0.0f, w2n = freq[(g + l) % NB3 * p.nq + q2];
       while (todo) {
         const int cur = g + l;
         unsigned sb = (unsigned)__builtin_amdgcn_readlane((int)bits, l);
+        const float rc = __builtin_bit_cast(
+            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, reach), l));
         todo &= todo - 1;
-        const float4 f1 = f1n, f2 = f2n;
+        const float w2 = w2n;
+        if (cur / NB3 != row) {
+          row = cur / NB3;
+          w1 = valid ? freq[row * p.nq + q1] : __builtin_nanf("");
+        }
         if (todo) {
           l = __ffsll((long long)todo) - 1;
-          f1n = modef[q1 * NB3 + (g + l) / NB3];
-          f2n = modef[q2 * NB3 + (g + l) % NB3];
+          w2n = freq[(g + l) % NB3 * p.nq + q2];
         }
-        // FP32 classification from the mode copies (a mode below the floor
-        // carries a NaN frequency and fails every comparison): a candidate is
-        // any process with |x| < hi, the band's upper edge.  The coalescence
-        // |x+| = |w + cp| and that of the mirrored ordering, |w - cp| (= (w +
-        // w2) - w1), share the edge bp, and for w >= 0 the smaller of the two is
-        // |w - |cp||, bitwise in FP32 (w + cp and w - cp round monotonically);
-        // so one test covers both, with cpe = -|cp| on mirrored entries and cp
-        // otherwise.  The decay |x-| is the same FP32 number for both.
-        float s2p, s2m, e_sig;
-        widths2_f(p, f1, f2, s2p, s2m, e_sig);
-        const float scl = wq_abs_max + fabsf(f1.w) + fabsf(f2.w);
-        const float bp = make_band_f(s2p, scl, e_sig).hi, bm = make_band_f(s2m, scl, e_sig).hi;
-        const float cp = f1.w - f2.w, cm = -f1.w - f2.w;
+        const float cp = w1 - w2, cm = -w1 - w2;  // NaN below the floor: fails every comparison
         const float cpe = dbl ? -fabsf(cp) : cp;
-        const int code = (cur / NB3) << 4 | (cur % NB3) << 8 | (dbl ? 1 << 12 : 0);
+        const int code = row << 4 | (cur % NB3) << 8 | (dbl ? 1 << 12 : 0);
         while (sb) {  // uniform
           const int s = __ffs(sb) - 1;
           sb &= sb - 1;
           const float w =
               __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w_lane), s));
-          const bool near = valid && (fabsf(w + cpe) < bp || fabsf(w + cm) < bm);
+          const bool near = fabsf(w + cpe) < rc || fabsf(w + cm) < rc;
           const unsigned long long m = __ballot(near);
           if (!m) continue;
           if (near) {
@@ -477,7 +759,7 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
           fill += __popcll(m);
           if (fill >= kFlush) {
             lds_wave_sync();
-            process(kFlush);
+            classify(kFlush, false);
             // the rest, fewer than 64, moves to the front
             const uint32_t mq = wq_q[wv][kFlush + lane];
             const uint16_t mc = wq_code[wv][kFlush + lane];
@@ -491,7 +773,7 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
     }
   }
   lds_wave_sync();
-  process(fill);
+  classify(fill, true);
 
   if constexpr (MODE == kModeCount) {
 #pragma unroll
@@ -572,26 +854,15 @@ __global__ void tc_rows_add(int n_modes, const long long* __restrict__ block_sum
   if (m < n_modes) row_ptr[m] += block_sum[m / 1024];
 }
 
-// eta rounded to T and transposed to [q][mode][component].
-template <typename T>
-__global__ void lw_eta_transpose(long nq, int nb3, const double* __restrict__ evec,
-                                 typename Cx<T>::type* __restrict__ etaT) {
-  const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= nq * nb3 * nb3) return;
-  const int j = k % nb3, s = (k / nb3) % nb3;
-  const long q = k / ((long)nb3 * nb3);
-  const size_t src = ((q * nb3 + j) * nb3 + s) * 2;
-  etaT[k] = Cx<T>::make((T)evec[src], (T)evec[src + 1]);
-}
-
 size_t fused_lds_bytes(const kaldo_crystal* c, int prec) {
   const size_t cs = prec == KALDO_FP64 ? 16 : 8;
   return (size_t)c->bloch.n_blk * 9 * c->nb3 * cs;
 }
 
-// What the requests the kernel serves leave of the LDS beside the A~ tables
-// (its own queues and sums take 6 KB and some).
+// What the requests the kernel serves leave of the LDS beside the A~ tables;
+// its own queues and sums take kFusedOwnLds at most.
 static size_t fused_static_lds(bool record) { return 27968 + (record ? 8192 : 0); }
+constexpr size_t kFusedOwnLds = 11264;
 
 static bool fused_fits(const kaldo_crystal* c, int prec, bool record) {
   if (c->nb < 1 || c->nb > 5 || c->n_rep > 64) return false;
@@ -639,61 +910,79 @@ size_t fused_max_items(const kaldo_crystal* c, long nq) {
 // and chunk count, so they make the same cut decisions in the same order.
 template <typename T, int MODE>
 static int launch_fused_impl(const kaldo_crystal* c, const LwParams& p, const double* omega,
-                             const float4* modef, const double2* mrec, const uint8_t* phys,
-                             const uint8_t* sel, const double* evec, typename Cx<T>::type* eta,
-                             typename Cx<T>::type* phase_tab, float4* window, int32_t* qlist,
-                             double* part, int64_t n_subset, double scale, double* gamma, TcOut tc,
+                             const double* occ, const double* vel, const float4* modef,
+                             const uint8_t* phys, const uint8_t* sel, const double* evec,
+                             const FusedWs& ws, int64_t n_subset, double scale, double* gamma, TcOut tc,
                              hipStream_t st) {
+  using C = typename Cx<T>::type;
   const int nq = p.nq;
   const int n_modes = nq * c->nb3;
-  const long ne = (long)n_modes * c->nb3;
-  int32_t* live_list = qlist;
-  int32_t* idx_of_q = qlist + nq;
-  int32_t* n_live = qlist + 2 * nq;
+  int32_t* live_list = ws.qlist;
+  int32_t* idx_of_q = ws.qlist + nq;
+  int32_t* n_live = ws.qlist + 2 * nq;
   const Boxes box = choose_boxes(p.N);
   const float hs = p.adaptive ? (float)std::sqrt(p.h2 / 12.0) : 0.0f;
-  KALDO_LAUNCH("lw_windows", lw_windows, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes, c->nb3,
-               p.N[0], p.N[1], p.N[2], box, hs, modef, window);
-  if (MODE != kModeCount) {
-    KALDO_LAUNCH("lw_eta_transpose", lw_eta_transpose<T>, dim3((ne + 255) / 256), dim3(256), 0, st,
-                 (long)nq, c->nb3, evec, eta);
-    const long nph = (long)nq * std::max(1, p.n_d);
-    KALDO_LAUNCH("lw_phase_table", lw_phase_table<T>, dim3((nph + 255) / 256), dim3(256), 0, st, nq,
-                 p.n_d, p.N[0], p.N[1], p.N[2], c->bloch.dvec, phase_tab);
-  }
+  const int rb = (int)fused_record_bytes(c->nb3, sizeof(C));
+  const int phase_bytes = (int)fused_phase_bytes(c->nb3, c->bloch.n_f, sizeof(C));
+  auto blocks = [](long n) { return (unsigned)((n + 255) / 256); };
+  TableJobs jobs{};
+  jobs.first[1] = blocks((long)n_modes * c->nb3);
+  jobs.first[2] = jobs.first[1] + (MODE == kModeCount ? 0u : blocks((long)nq * c->bloch.n_f));
+  jobs.first[3] = jobs.first[2] + blocks(4l * n_modes);
+  jobs.first[4] = jobs.first[3] + blocks(nq);
+  KALDO_LAUNCH("lw_tables", lw_tables<T>, dim3(jobs.first[4]), dim3(256), 0, st, jobs, p, box, hs, rb,
+               phase_bytes, n_subset > 0, evec, omega, occ, vel, modef, phys, sel, c->bloch.fvec, c->bloch.n_f, ws.rec, ws.phase_tab, ws.window,
+               live_list, idx_of_q, n_live);
   if (n_subset > 0)
-    KALDO_LAUNCH("lw_live_q", lw_live_q<>, dim3(1), dim3(1024), 0, st, nq, c->nb3, phys, sel, live_list,
+    KALDO_LAUNCH("lw_live_q", lw_live_q<true>, dim3(1), dim3(1024), 0, st, nq, c->nb3, phys, sel, live_list,
                  idx_of_q, n_live);
-  else
-    KALDO_LAUNCH("lw_all_q", lw_all_q<>, dim3((nq + 255) / 256), dim3(256), 0, st, nq, live_list,
-                 idx_of_q, n_live);
-  // the count pass builds no A~ tables: no dynamic LDS
-  const size_t lds =
-      MODE == kModeCount ? 0 : fused_lds_bytes(c, sizeof(T) == 8 ? KALDO_FP64 : KALDO_FP32);
   const Fc3Bloch& b = c->bloch;
   const int n_chunk = fused_n_chunk(c, p.N, box, n_subset);
   const unsigned grid = (unsigned)fused_upper(nq, n_subset) * n_chunk;
-#define KALDO_FUSED_CASE(NBV)                                                                     \
-  case NBV:                                                                                       \
-    KALDO_LAUNCH("lw_fused", (lw_fused<NBV, T, MODE>), dim3(grid), dim3(kFusedThreads), lds, st,  \
-                 p, box, c->n_rep, c->d_rep, omega, modef, mrec, phys, sel, evec, eta, phase_tab, \
-                 window, b.t_ptr, b.t_i, b.t_l2, b.t_coef, b.e_blk, b.e_bg, b.blk_d, b.pair_ptr,  \
-                 live_list, n_live, n_chunk, part, tc);                                           \
-    break;
-  switch (c->nb) {
-    KALDO_FUSED_CASE(1)
-    KALDO_FUSED_CASE(2)
-    KALDO_FUSED_CASE(3)
-    KALDO_FUSED_CASE(4)
-    KALDO_FUSED_CASE(5)
-    default:
-      set_error("lw_fused: unsupported basis size");
-      return KALDO_EUNSUPPORTED;
+  // the count pass builds no A~ tables and stages the records' tails only
+  const size_t at = MODE == kModeCount ? 0 : fused_lds_bytes(c, sizeof(T) == 8 ? KALDO_FP64 : KALDO_FP32);
+  const size_t staged = (size_t)kFusedWaves * 64 * (MODE == kModeCount ? 48 : std::max(64, (int)((48 + (c->nb3 - 1) * sizeof(C) + 15) / 16 * 16)));
+  // staging (cells of up to two atoms) where it leaves room for the tables:
+  // 5.6 against 12.3 ms for lanes that fetch their own records (diamond 24^3,
+  // FP64; 0.57 against 0.63, 15^3, FP32).  Larger cells' records leave too few
+  // workgroups a CU.
+  int dev = 0, lds_max = 0;
+  KALDO_HIP(hipGetDevice(&dev));
+  KALDO_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+  const bool stage = c->nb <= 2 && at + staged + kFusedOwnLds <= (size_t)lds_max;
+  auto run = [&](auto kernel) {
+    KALDO_LAUNCH("lw_fused", kernel, dim3(grid), dim3(kFusedThreads), at + (stage ? staged : 0), st, p,
+                 box, c->n_rep, c->d_rep, omega, modef, ws.freq, phys, sel, evec, ws.rec, ws.phase_tab,
+                 phase_bytes, ws.window, b.t_ptr, b.t_i, b.t_l2, b.t_coef, b.e_blk, b.e_bg, b.blk_f,
+                 b.pair_ptr, live_list, n_live, n_chunk, ws.part, tc);
+  };
+  constexpr int kBoth = MODE == kModeCount ? 1 : 2;
+  const bool both = stage && (MODE == kModeCount || phase_bytes == 64);
+  if (c->nb == 1 && both)
+    run(lw_fused<1, T, MODE, kBoth>);
+  else if (c->nb == 1 && stage)
+    run(lw_fused<1, T, MODE, 1>);
+  else if (c->nb == 1)
+    run(lw_fused<1, T, MODE, 0>);
+  else if (c->nb == 2 && both)
+    run(lw_fused<2, T, MODE, kBoth>);
+  else if (c->nb == 2 && stage)
+    run(lw_fused<2, T, MODE, 1>);
+  else if (c->nb == 2)
+    run(lw_fused<2, T, MODE, 0>);
+  else if (c->nb == 3)
+    run(lw_fused<3, T, MODE, 0>);
+  else if (c->nb == 4)
+    run(lw_fused<4, T, MODE, 0>);
+  else if (c->nb == 5)
+    run(lw_fused<5, T, MODE, 0>);
+  else {
+    set_error("lw_fused: unsupported basis size");
+    return KALDO_EUNSUPPORTED;
   }
-#undef KALDO_FUSED_CASE
   if (MODE == kModeGamma)
     KALDO_LAUNCH("lw_fused_finish", lw_fused_finish, dim3((n_modes + 255) / 256), dim3(256), 0, st,
-                 n_modes, c->nb3, phys, sel, idx_of_q, n_chunk, part, scale, gamma);
+                 n_modes, c->nb3, phys, sel, idx_of_q, n_chunk, ws.part, scale, gamma);
   if (MODE == kModeCount) {
     const int n_block = (n_modes + 1023) / 1024;
     KALDO_LAUNCH("tc_rows", tc_rows, dim3(n_block), dim3(1024), 0, st, n_modes, c->nb3, idx_of_q,
@@ -708,39 +997,37 @@ static int launch_fused_impl(const kaldo_crystal* c, const LwParams& p, const do
 }
 
 template <typename T>
-int launch_fused(const kaldo_crystal* c, const LwParams& p, const double* omega, const float4* modef,
-                 const double2* mrec, const uint8_t* phys, const uint8_t* sel, const double* evec,
-                 typename Cx<T>::type* eta, typename Cx<T>::type* phase_tab, float4* window,
-                 int32_t* qlist, double* part, int64_t n_subset, double scale, double* gamma,
+int launch_fused(const kaldo_crystal* c, const LwParams& p, const double* omega, const double* occ,
+                 const double* vel, const float4* modef, const uint8_t* phys, const uint8_t* sel,
+                 const double* evec, const FusedWs& ws, int64_t n_subset, double scale, double* gamma,
                  hipStream_t st) {
-  return launch_fused_impl<T, kModeGamma>(c, p, omega, modef, mrec, phys, sel, evec, eta, phase_tab,
-                                          window, qlist, part, n_subset, scale, gamma, TcOut{}, st);
+  return launch_fused_impl<T, kModeGamma>(c, p, omega, occ, vel, modef, phys, sel, evec, ws, n_subset,
+                                          scale, gamma, TcOut{}, st);
 }
 
 template <typename T>
 int launch_fused_cache(const kaldo_crystal* c, const LwParams& p, int mode, const double* omega,
-                       const float4* modef, const double2* mrec, const uint8_t* phys,
-                       const uint8_t* sel, const double* evec, typename Cx<T>::type* eta,
-                       typename Cx<T>::type* phase_tab, float4* window, int32_t* qlist,
-                       int64_t n_subset, TcOut tc, hipStream_t st) {
+                       const double* occ, const double* vel, const float4* modef, const uint8_t* phys,
+                       const uint8_t* sel, const double* evec, const FusedWs& ws, int64_t n_subset,
+                       TcOut tc, hipStream_t st) {
   if (mode == kModeCount)
-    return launch_fused_impl<T, kModeCount>(c, p, omega, modef, mrec, phys, sel, evec, eta, phase_tab,
-                                            window, qlist, nullptr, n_subset, 0.0, nullptr, tc, st);
-  return launch_fused_impl<T, kModeRecord>(c, p, omega, modef, mrec, phys, sel, evec, eta, phase_tab,
-                                           window, qlist, nullptr, n_subset, 0.0, nullptr, tc, st);
+    return launch_fused_impl<T, kModeCount>(c, p, omega, occ, vel, modef, phys, sel, evec, ws, n_subset,
+                                            0.0, nullptr, tc, st);
+  return launch_fused_impl<T, kModeRecord>(c, p, omega, occ, vel, modef, phys, sel, evec, ws, n_subset,
+                                           0.0, nullptr, tc, st);
 }
 
-#define KALDO_FUSED_FOR(T, C)                                                                      \
-  template int launch_fused<T>(const kaldo_crystal*, const LwParams&, const double*, const float4*, \
-                               const double2*, const uint8_t*, const uint8_t*, const double*, C*,  \
-                               C*, float4*, int32_t*, double*, int64_t, double, double*,           \
-                               hipStream_t);                                                       \
-  template int launch_fused_cache<T>(const kaldo_crystal*, const LwParams&, int, const double*,    \
-                                     const float4*, const double2*, const uint8_t*,                \
-                                     const uint8_t*, const double*, C*, C*, float4*, int32_t*,     \
-                                     int64_t, TcOut, hipStream_t);
-KALDO_FUSED_FOR(float, float2)
-KALDO_FUSED_FOR(double, double2)
+#define KALDO_FUSED_FOR(T)                                                                          \
+  template int launch_fused<T>(const kaldo_crystal*, const LwParams&, const double*, const double*, \
+                               const double*, const float4*, const uint8_t*, const uint8_t*,        \
+                               const double*, const FusedWs&, int64_t, double, double*,             \
+                               hipStream_t);                                                        \
+  template int launch_fused_cache<T>(const kaldo_crystal*, const LwParams&, int, const double*,     \
+                                     const double*, const double*, const float4*, const uint8_t*,   \
+                                     const uint8_t*, const double*, const FusedWs&, int64_t, TcOut, \
+                                     hipStream_t);
+KALDO_FUSED_FOR(float)
+KALDO_FUSED_FOR(double)
 #undef KALDO_FUSED_FOR
 
 }  // namespace kaldo

@@ -1218,7 +1218,7 @@ extern "C" int kaldo_jdos(const kaldo_crystal* c, const int32_t* mesh, const dou
     KALDO_LAUNCH("jdos_select", jdos_select, dim3((unsigned)((n_subset + 255) / 256)), dim3(256), 0,
                  st, modes_subset, (long)n_subset, nm, sel, c->d_flags);
   if (modes_subset)
-    KALDO_LAUNCH("lw_live_q", lw_live_q<>, dim3(1), dim3(1024), 0, st, nq, c->nb3, phys, sel,
+    KALDO_LAUNCH("lw_live_q", lw_live_q<false>, dim3(1), dim3(1024), 0, st, nq, c->nb3, phys, sel,
                  live_list, idx_of_q, n_live);
   else
     KALDO_LAUNCH("lw_all_q", lw_all_q<>, dim3((nq + 255) / 256), dim3(256), 0, st, nq, live_list,

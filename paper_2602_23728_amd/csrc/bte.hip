@@ -35,10 +35,10 @@
 //   bte_compact_index, bte_compact_cols, bte_gather3, bte_scatter3   the
 //                  solve's restriction to the coupled modes (row map, coupled
 //                  columns moved to the front of each coupled row)
-//   lu_diag, lu_panels, lu_update, lu_gemm   blocked LU without pivoting of
+//   lu_left, lu_panels, lu_gemm   blocked LU without pivoting of
 //                  the coupled block (64 x 64 blocks, panels of eight; the
 //                  panels and updates on the FP64 matrix cores)
-//   lu_step<FORWARD>   the two triangular sweeps for the 3 RHS, one launch per block
+//   lu_solve<FORWARD>, lu_solve_rest   the two triangular sweeps for the 3 RHS, panel by panel
 //   bte_gemv, bte_sc_init, bte_sc_update   the iteration of Eq. sc_iter
 //   bte_kappa      Eq. kappa_general, fixed-order reduction
 // Every reduction and every sequence of additions into one matrix element
@@ -56,6 +56,8 @@ constexpr int kLuB = 64;     // LU block edge
 constexpr int kLuPanel = 8;  // blocks per panel of the blocked LU
 
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double d4;
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 
 // ------------------------------------------------------------------ tables
 
@@ -511,9 +513,6 @@ __global__ __launch_bounds__(1024) void bte_kappa(long n, const double* __restri
 
 // ------------------------------------------------------------------ LU
 
-// Factor the diagonal block k (no pivoting) in LDS; write L\U back, and the
-// inverses of the unit lower L and of the upper U to linv/uinv [64][64].
-// Padding rows past n act as identity rows.
 // The coupled block of the matrix as the LU sees it: element (i, j) of the
 // n x n coupled system sits at row rows[i] of the stored matrix (leading
 // dimension ld), column j (the coupled columns of each stored row are moved
@@ -525,108 +524,13 @@ struct MatRows {
   __device__ double* row(long i) const { return mat + (long)rows[i] * ld; }
 };
 
-__global__ __launch_bounds__(256) void lu_diag(long n, int k, MatRows A,
-                                               double* __restrict__ linv,
-                                               double* __restrict__ uinv,
-                                               int32_t* __restrict__ flags) {
-  // Thread (ty, tx) = (tid / 16, tid % 16) keeps in registers the 16
-  // elements of rows ty + 16 a and columns tx + 16 b (a, b < 4) of the block
-  // D, of X_L = L^-1 and of X_U = U^-1: the strided split keeps every thread
-  // busy as the active corner shrinks.  Step j publishes through LDS the
-  // rows and columns it needs (two buffers by step parity, so one barrier
-  // per step); then, with r = 1 / D[j][j] and l_i = D[i][j] r:
-  //   factorisation        D[i][c] -= l_i D[j][c]          (i, c > j), D[i][j] = l_i
-  //   unit lower inverse   X_L[i][:] -= l_i X_L[j][:]      (i > j; row j of X_L is final)
-  //   upper inverse        X_U[:][j] *= r, then X_U[:][c] -= X_U[:][j] U[j][c]   (c > j)
-  // Row j of D is row j of U from step j on, and column j of X_U has then
-  // taken every earlier step, so all three run in the same 64 steps.
-  constexpr int B = kLuB;
-  static_assert(B == 64, "16 x 16 threads, 4 x 4 elements each");
-  __shared__ double pub_row[2][B];    // row j of D
-  __shared__ double pub_col[2][B];    // column j of D
-  __shared__ double pub_xrow[2][B];   // row j of X_L
-  __shared__ double pub_xucol[2][B];  // column j of X_U
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const long r0 = (long)k * B;
-  double d[4][4], xl[4][4], xu[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int i = ty + 16 * a, c = tx + 16 * b;
-      const long gi = r0 + i, gc = r0 + c;
-      d[a][b] = (gi < n && gc < n) ? A.row(gi)[gc] : (i == c ? 1.0 : 0.0);
-      xl[a][b] = xu[a][b] = (i == c) ? 1.0 : 0.0;
-    }
-#pragma unroll
-  for (int ja = 0; ja < 4; ++ja) {
-    for (int jy = 0; jy < 16; ++jy) {
-      const int j = 16 * ja + jy, pb = j & 1;
-      if (ty == jy) {
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          pub_row[pb][tx + 16 * b] = d[ja][b];
-          pub_xrow[pb][tx + 16 * b] = xl[ja][b];
-        }
-      }
-      if (tx == jy) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          pub_col[pb][ty + 16 * a] = d[a][ja];
-          pub_xucol[pb][ty + 16 * a] = xu[a][ja];
-        }
-      }
-      __syncthreads();
-      const double piv = pub_row[pb][j];
-      if (tid == 0 && !(fabs(piv) > 1e-300)) raise_flag(flags, kFlagSingular);
-      const double r = 1.0 / piv;
-      double uc[4], xc[4];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        uc[b] = pub_row[pb][tx + 16 * b];
-        xc[b] = pub_xrow[pb][tx + 16 * b];
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int i = ty + 16 * a;
-        const double xj = pub_xucol[pb][i] * r;
-        const double li = pub_col[pb][i] * r;
-        const bool below = i > j;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int c = tx + 16 * b;
-          if (c > j) {
-            if (below) d[a][b] = fma(-li, uc[b], d[a][b]);
-            xu[a][b] = fma(-xj, uc[b], xu[a][b]);
-          }
-          if (b == ja && c == j) {
-            if (below) d[a][b] = li;
-            xu[a][b] = xj;
-          }
-          if (below) xl[a][b] = fma(-li, xc[b], xl[a][b]);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int i = ty + 16 * a, c = tx + 16 * b;
-      const long gi = r0 + i, gc = r0 + c;
-      if (gi < n && gc < n) A.row(gi)[gc] = d[a][b];
-      linv[i * B + c] = xl[a][b];
-      uinv[i * B + c] = xu[a][b];
-    }
-}
-
 // 64 x 64 x 64 product P Q from two LDS blocks, four waves of 32 x 32 on
 // v_mfma_f64_16x16x4f64; wave wv holds rows wm = 32 (wv / 2) and columns
 // wn = 32 (wv % 2) of the result in acc[a][b] (16 x 16 tiles).
 struct BlockProduct {
   int wm, wn, lr, lg;
   d4 acc[2][2];
-  __device__ void run(const double (*P)[kLuB + 1], const double (*Q)[kLuB + 1], int tid) {
+  __device__ void clear(int tid) {
     const int lane = tid & 63, wv = tid >> 6;
     wm = (wv >> 1) * 32;
     wn = (wv & 1) * 32;
@@ -634,6 +538,8 @@ struct BlockProduct {
     lg = lane >> 4;
     for (int a = 0; a < 2; ++a)
       for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  }
+  __device__ void add(const double (*P)[kLuB + 1], const double (*Q)[kLuB + 1]) {
     for (int kk = 0; kk < kLuB; kk += 4) {
 #pragma unroll
       for (int a = 0; a < 2; ++a)
@@ -663,18 +569,33 @@ __global__ __launch_bounds__(256) void lu_panels(long n, int nb, int k, MatRows 
   const bool row = (int)blockIdx.x < m;
   const int other = k + 1 + (row ? blockIdx.x : blockIdx.x - m);
   const long bi = row ? k : other, bj = row ? other : k;
-  for (int idx = tid; idx < B * B; idx += 256) {
-    const int i = idx / B, j = idx % B;
-    const long gi = bi * B + i, gj = bj * B + j;
-    M[i][j] = (gi < n && gj < n) ? A.row(gi)[gj] : 0.0;
-    T[i][j] = row ? linv[idx] : uinv[idx];
+  const int pc = 2 * (tid & 31), pr = tid >> 5;  // pair tid % 32 of the rows tid / 32 + 8 i
+  const double* inv = (row ? linv : uinv) + pr * B + pc;
+  const long c = bj * B + pc;
+  d2 pm[8], pt[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const double* r = A.row(min(bi * B + pr + 8 * i, n - 1));
+    if (c + 1 < n)
+      pm[i] = *reinterpret_cast<const d2u*>(r + c);
+    else
+      pm[i] = d2{c < n ? r[c] : 0.0, 0.0};
+    pt[i] = *reinterpret_cast<const d2*>(inv + 8 * i * B);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    M[pr + 8 * i][pc] = pm[i].x;
+    M[pr + 8 * i][pc + 1] = pm[i].y;
+    T[pr + 8 * i][pc] = pt[i].x;
+    T[pr + 8 * i][pc + 1] = pt[i].y;
   }
   __syncthreads();
   BlockProduct bp;
+  bp.clear(tid);
   if (row)
-    bp.run(T, M, tid);
+    bp.add(T, M);
   else
-    bp.run(M, T, tid);
+    bp.add(M, T);
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -686,92 +607,290 @@ __global__ __launch_bounds__(256) void lu_panels(long n, int nb, int k, MatRows 
       }
 }
 
-// Update of step k on two rectangles of blocks: A_ij -= A_ik A_kj for i in
-// [i0, i0 + ni), j in [j0, j0 + nj) (the first n1 workgroups), then for i in
-// [i0b, ...), j in [j0b, j0b + njb); one 64 x 64 block per workgroup.  The
-// rectangles are disjoint and read only row and column k.
-__global__ __launch_bounds__(256) void lu_update(long n, int k, int i0, int j0, int nj, int n1,
-                                                 int i0b, int j0b, int njb, MatRows A) {
+// The factorisation (no pivoting) of a 64 x 64 block D in LDS to L\U, and the
+// inverses of the unit lower L (strictly lower part of X) and of the upper U
+// (the rest of X).  Wave w keeps columns 16 w .. 16 w + 15 in registers, a lane
+// per row.  In turn each wave factors its own columns, every row, and
+// publishes the multipliers, which the waves to the right apply; the pivot
+// row is read lane to scalar, so a step has no barrier and no LDS round trip.
+// Then the inverses: of each 16 x 16 diagonal block by its wave (L in sixteen
+// lanes, U turned about in sixteen others: the same substitution), and the
+// other blocks X_ij = -X_ii sum_t L_it X_tj (and U alike) by distance from the
+// diagonal, a wave per block, on the matrix cores: an accumulator's items are
+// the next product's second operand as they lie.
+// One workgroup is the serial part of every step, so this is latency alone:
+// 64 steps over the whole block with a barrier each took a launch of 51 us,
+// this 33.
+typedef double (*Block)[kLuB + 1];
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const unsigned lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __builtin_bit_cast(double, (long long)((unsigned long long)hi << 32 | lo));
+}
+__device__ __forceinline__ void factor_block(Block D, Block X, int tid, int32_t* flags) {
+  constexpr int Q = 16;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  double a[Q];
+#pragma unroll
+  for (int c = 0; c < Q; ++c) a[c] = D[lane][Q * wv + c];
+  bool singular = false;
+#pragma unroll 1
+  for (int w = 0; w < kLuB / Q; ++w) {
+    const int o = Q * w;
+    Block mul = X + (w & 1) * Q;  // the multipliers l_i of its 16 steps, in two places in turn
+    if (wv == w) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) {
+        const double piv = lane_value(a[j], o + j);
+        singular |= !(fabs(piv) > 1e-300);
+        const double r = 1.0 / piv, q = a[j] * r;
+        const bool below = lane > o + j;
+        const double l = below ? q : 0.0;
+        a[j] = below ? q : a[j];
+        mul[j][lane] = l;
+#pragma unroll
+        for (int c = j + 1; c < Q; ++c) a[c] = fma(-l, lane_value(a[c], o + j), a[c]);
+      }
+    }
+    __syncthreads();
+    if (wv > w) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) {
+        const double l = mul[j][lane];
+#pragma unroll
+        for (int c = 0; c < Q; ++c) a[c] = fma(-l, lane_value(a[c], o + j), a[c]);
+      }
+    }
+  }
+  if (singular && lane == 0) raise_flag(flags, kFlagSingular);
+#pragma unroll
+  for (int c = 0; c < Q; ++c) D[lane][Q * wv + c] = a[c];
+  __syncthreads();
+  {
+    const int o = Q * wv;
+    const bool up = lane & Q;
+    const double* corner = &D[o + (up ? Q - 1 : 0)][o + (up ? Q - 1 : 0)];
+    const int dir = up ? -1 : 1;
+    auto at = [&](int i, int j) { return corner[dir * (i * (kLuB + 1) + j)]; };
+    const double own = up ? 1.0 / at(lr, lr) : 1.0;
+    double x[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) x[i] = i == lr ? 1.0 : 0.0;
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      x[j] *= __shfl(own, (lane & Q) + j, 64);
+#pragma unroll
+      for (int i = j + 1; i < Q; ++i) x[i] = fma(-at(i, j), x[j], x[i]);
+      if (j % 4 == 3) asm volatile("" ::: "memory");  // the reads of four columns in flight, not of all
+    }
+    if (lane < 2 * Q) {
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        if (up && i >= lr) X[o + Q - 1 - i][o + Q - 1 - lr] = x[i];
+        if (!up && i > lr) X[o + i][o + lr] = x[i];
+      }
+    }
+  }
+  __syncthreads();
+  // element (i, j) of the inverse of L, of U
+  auto inv_l = [&](int i, int j) { return i > j ? X[i][j] : i == j ? 1.0 : 0.0; };
+  auto inv_u = [&](int i, int j) { return i <= j ? X[i][j] : 0.0; };
+  for (int dist = 1; dist < kLuB / Q; ++dist) {
+    const int per = kLuB / Q - dist;
+    for (int t = wv; t < 2 * per; t += 4) {
+      const bool low = t < per;
+      const int lo = low ? t : t - per, hi = lo + dist;  // L: block (hi, lo); U: (lo, hi)
+      const int bi = low ? hi : lo, bj = low ? lo : hi;
+      d4 sum = {0.0, 0.0, 0.0, 0.0}, x = {0.0, 0.0, 0.0, 0.0};
+      for (int b = low ? lo : lo + 1; b < (low ? hi : hi + 1); ++b)
+#pragma unroll
+        for (int k = 0; k < Q; k += 4) {
+          const int kk = Q * b + k + lg, c = Q * bj + lr;
+          sum = __builtin_amdgcn_mfma_f64_16x16x4f64(-D[Q * bi + lr][kk], low ? inv_l(kk, c) : inv_u(kk, c), sum,
+                                                     0, 0, 0);
+        }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int i = Q * bi + lr, kk = Q * bi + 4 * k + lg;
+        x = __builtin_amdgcn_mfma_f64_16x16x4f64(low ? inv_l(i, kk) : inv_u(i, kk), sum[k], x, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) X[Q * bi + 4 * r + lg][Q * bj + lr] = x[r];
+    }
+    __syncthreads();
+  }
+}
+
+// Step k of a panel that starts at block k0: the blocks of row and column k
+// take the panel's earlier steps, A_ij -= sum_{k0 <= t < k} A_it A_tj (one
+// product over all of them, so that a block is read and written once), and
+// workgroup 0, which has the diagonal block, factors it meanwhile; its L\U is
+// written back, the inverses of L and U to linv / uinv [64][64].  Workgroups 1
+// .. m have the blocks (k + 1 ..., k), the next m the blocks (k, k + 1 ...).
+// Rows and columns past n read as others' and are not written; the diagonal
+// block's act as identity.  Updating every block of the panel at every step, as
+// a third launch, the factorisation's steps took 26.9 ms of 13,500 equations,
+// now 13.4.  Panels of four and six blocks: 9.4 and 10.2 ms here against 10.0,
+// but 32.6 and 30.2 in the product against 28.7.
+__global__ __launch_bounds__(256) void lu_left(long n, int nb, int k0, int k, MatRows A,
+                                               double* __restrict__ linv, double* __restrict__ uinv,
+                                               int32_t* __restrict__ flags) {
   constexpr int B = kLuB;
   __shared__ double L[B][B + 1];
   __shared__ double U[B][B + 1];
-  const int tid = threadIdx.x;
-  const int wb = (int)blockIdx.x;
-  const long bi = wb < n1 ? i0 + wb / nj : i0b + (wb - n1) / njb,
-             bj = wb < n1 ? j0 + wb % nj : j0b + (wb - n1) % njb;
-  for (int idx = tid; idx < B * B; idx += 256) {
-    const int i = idx / B, j = idx % B;
-    const long li = bi * B + i, lj = (long)k * B + j;
-    L[i][j] = (li < n && lj < n) ? A.row(li)[lj] : 0.0;
-    const long ui = (long)k * B + i, uj = bj * B + j;
-    U[i][j] = (ui < n && uj < n) ? A.row(ui)[uj] : 0.0;
-  }
-  __syncthreads();
+  const int tid = threadIdx.x, m = nb - k - 1, wb = (int)blockIdx.x;
+  const int bi = wb <= m ? k + wb : k, bj = wb <= m ? k : k + wb - m;
+  // pair tid % 32 of the rows tid / 32 + 8 i of a block
+  const int pc = 2 * (tid & 31), pr = tid >> 5;
   BlockProduct bp;
-  bp.run(L, U, tid);
+  bp.clear(tid);
+  const bool whole = (long)bj * B + B <= n;
+  // (the rows' places in the matrix one block ahead of their elements)
+  d2 pl[8], pu[8];
+  int rl[8], ru[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    rl[i] = A.rows[min((long)bi * B + pr + 8 * i, n - 1)];
+    ru[i] = A.rows[(long)k0 * B + pr + 8 * i];
+  }
+  auto fetch = [&](int t) {
+    const long c = (long)bj * B + pc;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      pl[i] = *reinterpret_cast<const d2u*>(A.mat + rl[i] * A.ld + (long)t * B + pc);
+      const double* u = A.mat + ru[i] * A.ld;
+      if (whole)
+        pu[i] = *reinterpret_cast<const d2u*>(u + c);
+      else
+        pu[i] = d2{u[min(c, n - 1)], u[min(c + 1, n - 1)]};
+      ru[i] = A.rows[min((long)(t + 1) * B + pr + 8 * i, n - 1)];
+    }
+  };
+  if (k0 < k) fetch(k0);
+  for (int t = k0; t < k; ++t) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      L[pr + 8 * i][pc] = pl[i].x;
+      L[pr + 8 * i][pc + 1] = pl[i].y;
+      U[pr + 8 * i][pc] = pu[i].x;
+      U[pr + 8 * i][pc + 1] = pu[i].y;
+    }
+    __syncthreads();
+    if (t + 1 < k) fetch(t + 1);
+    bp.add(L, U);
+    __syncthreads();
+  }
+  // the block itself, every load unconditional (rows and columns past n read
+  // the last one): under conditions they would wait for each other
+  double* row[2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) row[a][r] = A.row(min((long)bi * B + bp.row(a, r), n - 1));
+  double old[2][2][4];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const long gi = bi * B + bp.row(a, r), gj = bj * B + bp.col(b);
-        if (gi < n && gj < n) A.row(gi)[gj] -= bp.acc[a][b][r];
-      }
+      for (int r = 0; r < 4; ++r) old[a][b][r] = row[a][r][min((long)bj * B + bp.col(b), n - 1)];
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = bp.row(a, r), j = bp.col(b);
+          const long gj = (long)bj * B + j;
+          f(i, j, (long)bi * B + i < n && gj < n, row[a][r] + gj, old[a][b][r] - bp.acc[a][b][r]);
+        }
+  };
+  if (wb != 0) {
+    each([&](int, int, bool in, double* to, double v) {
+      if (in) *to = v;
+    });
+    return;
+  }
+  each([&](int i, int j, bool in, double*, double v) { L[i][j] = in ? v : (i == j ? 1.0 : 0.0); });
+  __syncthreads();
+  factor_block(L, U, tid, flags);
+  each([&](int i, int j, bool in, double* to, double) {
+    if (in) *to = L[i][j];
+  });
+  for (int idx = tid; idx < B * B; idx += 256) {
+    const int i = idx / B, j = idx % B;
+    linv[idx] = i > j ? U[i][j] : i == j ? 1.0 : 0.0;
+    uinv[idx] = i <= j ? U[i][j] : 0.0;
+  }
 }
 
 // Deferred update of a panel: A_ij -= sum_k A_ik A_kj over the panel's
 // columns k in [kc, kc + kw) for the trailing elements i, j >= r0 (blocked
-// right-looking LU: the panel's own steps update only the panel's columns
-// and rows, this one product the rest).  128 x 128 tile per workgroup, four
-// waves of 64 x 64 as 4 x 4 v_mfma_f64_16x16x4f64 accumulators; K in slices
-// of 16 staged k-major in LDS (two buffers, the next slice fetched into
-// registers while the current one is multiplied).  Elements past n read as
-// zero and are not written.
-constexpr int kLgT = 128;  // tile edge
-constexpr int kLgK = 16;   // K slice
-constexpr int kLgLd = kLgT + 2;  // LDS row stride (doubles)
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void lu_gemm(long n, long r0, long kc, int kw, int ntl,
-                                               MatRows A) {
-  __shared__ double As[2][kLgK][kLgLd];  // [k][row]
-  __shared__ double Bs[2][kLgK][kLgLd];  // [k][col]
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// LU: the panel's own steps update only the panel's columns and rows, this one
+// product the rest).  128 x 128 tile per workgroup, four waves of 64 x 64 as
+// 4 x 4 v_mfma_f64_16x16x4f64 accumulators, which start as the tile itself
+// (the rows are staged negated); K in slices of 16 staged in LDS (two buffers,
+// the next slice fetched into registers while the current one is multiplied).
+// Every load is 16 bytes without a condition: rows past n repeat the last one
+// and are not written, the last tile of columns is moved back to end at n and
+// writes its own columns only (n >= 128 wherever a panel is full, and the
+// panel's columns are all below n).  Rows are read by pairs of k: lane group
+// lg of an instruction holds k = 2 lg (+ 1 for the next instruction) of both
+// operands.  Bound by the matrix cores, with conditions on every element of a
+// fetch 50 % busy: the products of 13,500 equations took 41.1 ms, now 28.7 (52
+// TFLOP/s).  Workgroups in 2 x 2 to 8 x 8 groups per XCD measured 29.0 to 31.1.
+constexpr int kLgT = 128;        // tile edge
+constexpr int kLgK = 16;         // K slice
+constexpr int kLgLd = kLgT + 8;  // LDS stride of a k (doubles): the rows two lane groups read, 2 k apart, share no bank
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void lu_gemm(
+    long n, long r0, long kc, int kw, int ntl, MatRows A) {
+  __shared__ d2 As[2][kLgT * 8];        // row r, pair p at 8 r + (p ^ (r / 2 % 8)): conflict-free
+  __shared__ double Bs[2][kLgK][kLgLd];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const long row0 = r0 + (long)(blockIdx.x / ntl) * kLgT, col0 = r0 + (long)(blockIdx.x % ntl) * kLgT;
   if (row0 >= n || col0 >= n) return;
-  // staging: A rows row0 + (tid >> 1), k = 8 (tid & 1) .. + 8; B row k =
-  // tid >> 4, columns col0 + 8 (tid & 15) .. + 8
-  const int ar = tid >> 1, ak = 8 * (tid & 1);
-  const int bk = tid >> 4, bc = 8 * (tid & 15);
-  const long ga = row0 + ar, gbc = col0 + bc;
-  const double* arow = A.row(ga < n ? ga : 0);  // row ga (a valid row when ga >= n)
-  double pa[8], pb[8];
-  // slice k0: eight consecutive elements per operand and thread, from one
-  // base address (constant offsets)
+  const long cs = min(col0, n - kLgT);
+  // staging: pair tid % 8 of the rows tid / 8 + 32 i; k = wv + 4 i, columns 2 lane, + 1
+  const int ap = tid & 7, ar = tid >> 3;
+  const double* arow[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) arow[i] = A.row(min(row0 + ar + 32 * i, n - 1)) + 2 * ap;
+  d2 pa[4], pb[4];
   auto fetch = [&](long k0) {
-    const long ka = k0 + ak;
-    const double* a = arow + ka;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) pa[t] = (ga < n && ka + t < n) ? a[t] : 0.0;
-    const long kb = k0 + bk;
-    const double* b = A.row(kb < n ? kb : 0) + gbc;
+    for (int i = 0; i < 4; ++i) pa[i] = *reinterpret_cast<const d2u*>(arow[i] + k0);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) pb[t] = (kb < n && gbc + t < n) ? b[t] : 0.0;
+    for (int i = 0; i < 4; ++i)
+      pb[i] = *reinterpret_cast<const d2u*>(A.row(k0 + wv + 4 * i) + cs + 2 * lane);
   };
   auto stage = [&](int buf) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) As[buf][ak + t][ar] = pa[t];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) Bs[buf][bk][bc + t] = pb[t];
+    for (int i = 0; i < 4; ++i) {
+      const int r = ar + 32 * i;
+      As[buf][r * 8 + (ap ^ ((r >> 1) & 7))] = -pa[i];
+      *reinterpret_cast<d2*>(&Bs[buf][wv + 4 * i][2 * lane]) = pb[i];
+    }
   };
   const int wm = (wv >> 1) * 64, wn = (wv & 1) * 64;
   const int lr = lane & 15, lg = lane >> 4;
-  d4 acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
   fetch(kc);
+  // item r of lane l of an accumulator is row 4 r + l / 16, column l % 16
+  d4 acc[4][4];
+  auto each_row = [&](auto f) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const long gi = row0 + wm + 16 * a + 4 * r + lg;
+        f(a, r, gi < n, A.row(min(gi, n - 1)) + cs + wn + lr);
+      }
+  };
+  each_row([&](int a, int r, bool, const double* row) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b][r] = row[16 * b];
+  });
   stage(0);
   __syncthreads();
   int cur = 0;
@@ -779,92 +898,148 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bool more = k0 + kLgK < kc + kw;
     if (more) fetch(k0 + kLgK);
 #pragma unroll
-    for (int kk = 0; kk < kLgK; kk += 4) {
-      double av[4], bv[4];
+    for (int h = 0; h < 2; ++h) {
+      d2 av[4];
+      double b0[4], b1[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        av[t] = As[cur][kk + lg][wm + 16 * t + lr];  // A[row = lane % 16][k = lane / 16]
-        bv[t] = Bs[cur][kk + lg][wn + 16 * t + lr];  // B[k = lane / 16][col = lane % 16]
+        const int r = wm + 16 * t + lr;
+        av[t] = As[cur][r * 8 + ((4 * h + lg) ^ ((r >> 1) & 7))];
+        b0[t] = Bs[cur][8 * h + 2 * lg][wn + 16 * t + lr];
+        b1[t] = Bs[cur][8 * h + 2 * lg + 1][wn + 16 * t + lr];
       }
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].x, b0[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].y, b1[b], acc[a][b], 0, 0, 0);
     }
     if (more) stage(cur ^ 1);
     __syncthreads();
     cur ^= 1;
   }
+  each_row([&](int a, int r, bool in, const double* row) {
+    if (in) {
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        // item r of lane l is row 4 r + l / 16, column l % 16
-        const long gi = row0 + wm + 16 * a + 4 * r + lg, gj = col0 + wn + 16 * b + lr;
-        if (gi < n && gj < n) A.row(gi)[gj] -= acc[a][b][r];
-      }
+      for (int b = 0; b < 4; ++b)
+        if (cs + wn + 16 * b + lr >= col0) const_cast<double*>(row)[16 * b] = acc[a][b][r];
+    }
+  });
 }
 
-// Triangular sweeps with 3 right-hand sides, right-looking: the residual r
-// starts as the right-hand side; step k solves block k, x_k = Tinv_k r_k,
-// and removes its contribution from the blocks still to solve, r_i -= A_ik
-// x_k (i > k forward with the L blocks, i < k backward with the U blocks),
-// in one launch: every workgroup forms x_k in LDS, workgroup 0 stores it and
-// each other one updates one block.  Every r_i is updated in the order of k:
-// the sums are fixed-order.
+// Triangular sweeps with 3 right-hand sides, right-looking by the panels of
+// the factorisation: the residual r starts as the right-hand side; a panel's
+// blocks are solved in turn by one workgroup, x_k = Tinv_k r_k, r_i -= A_ik x_k
+// for the panel's blocks still to solve (lu_solve), then one product with all
+// its columns updates the rows past it (lu_solve_rest; forward the rows below
+// with the L blocks, backward the rows above with the U blocks).  Fixed-order
+// sums.  With a launch per block that updated every row, every workgroup
+// forming x_k for itself, the two sweeps of 13,500 rows took 8.7 ms, now 4.6.
+constexpr int kPanelRows = kLuPanel * kLuB;
+
+// Sum over a lane's row of 16 by rotations of the row: vector instructions
+// (through LDS the reductions took most of lu_solve).
+template <int ROT>
+__device__ __forceinline__ double add_rotated(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const unsigned lo = __builtin_amdgcn_mov_dpp((int)b, 0x120 + ROT, 0xf, 0xf, false),
+                 hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x120 + ROT, 0xf, 0xf, false);
+  return v + __builtin_bit_cast(double, (long long)((unsigned long long)hi << 32 | lo));
+}
+__device__ __forceinline__ double sum16(double v) {
+  return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(v))));
+}
 template <bool FORWARD>
-__global__ __launch_bounds__(256) void lu_step(long n, int k, const double* __restrict__ tinv,
-                                               MatRows A, double* __restrict__ x,
-                                               double* __restrict__ r) {
+__global__ __launch_bounds__(1024) void lu_solve(long n, int k0, int k1, const double* __restrict__ tinv,
+                                                 MatRows A, double* __restrict__ x,
+                                                 const double* __restrict__ r) {
   constexpr int B = kLuB;
-  __shared__ double rk[B][3];
+  __shared__ double rs[kPanelRows][3];
   __shared__ double xk[B][3];
-  __shared__ double part[4][B][3];
-  const int tid = threadIdx.x, row = tid >> 2, sub = tid & 3;
-  if (tid < B * 3) {
-    const int i = tid / 3, c = tid % 3;
-    const long g = (long)k * B + i;
-    rk[i][c] = g < n ? r[3 * g + c] : 0.0;
-  }
-  __syncthreads();
-  if (tid < B * 3) {
-    const int i = tid / 3, c = tid % 3;
-    double s = 0.0;
-    for (int t = 0; t < B; ++t) s += tinv[i * B + t] * rk[t][c];
-    xk[i][c] = s;
-  }
-  __syncthreads();
-  if (blockIdx.x == 0) {
-    if (tid < B * 3) {
-      const int i = tid / 3, c = tid % 3;
-      const long g = (long)k * B + i;
-      if (g < n) x[3 * g + c] = xk[i][c];
+  const int tid = threadIdx.x, row = tid >> 4, sub = 4 * (tid & 15);
+  const long g0 = (long)k0 * B;
+  for (int i = tid; i < kPanelRows * 3; i += 1024) rs[i / 3][i % 3] = g0 + i / 3 < n ? r[3 * g0 + i] : 0.0;
+  // rows and columns past n read the last one: their x is zero, their r not stored
+  const double* at[kLuPanel];
+#pragma unroll
+  for (int b = 0; b < kLuPanel; ++b) at[b] = A.row(min(g0 + (long)b * B + row, n - 1));
+  // four elements of a row of 64, sixteen lanes a row
+  auto dot = [&](const double* a, const double (*v)[3], double* s) {
+    for (int c = 0; c < 3; ++c) s[c] = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) s[c] = fma(a[u], v[sub + u][c], s[c]);
+    for (int c = 0; c < 3; ++c) s[c] = sum16(s[c]);
+  };
+  for (int step = 0; step < k1 - k0; ++step) {
+    const int kb = FORWARD ? step : k1 - k0 - 1 - step;
+    const long col = g0 + (long)kb * B;
+    // what the step reads from memory, all before its first barrier
+    double t[4], a[kLuPanel][4], s[3];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = tinv[(size_t)(k0 + kb) * B * B + row * B + sub + u];
+#pragma unroll
+    for (int b = 0; b < kLuPanel; ++b)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a[b][u] = at[b][min(col + sub + u, n - 1)];
+    __syncthreads();
+    dot(t, rs + kb * B, s);
+    if (sub == 0) {
+      for (int c = 0; c < 3; ++c) {
+        xk[row][c] = s[c];
+        if (col + row < n) x[3 * (col + row) + c] = s[c];
+      }
     }
-    return;
-  }
-  const long bi = FORWARD ? k + (long)blockIdx.x : (long)blockIdx.x - 1;
-  const long gi = bi * B + row;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-  if (gi < n)
-    for (int t = sub; t < B; t += 4) {
-      const long gc = (long)k * B + t;
-      if (gc >= n) break;
-      const double a = A.row(gi)[gc];
-      s0 += a * xk[t][0];
-      s1 += a * xk[t][1];
-      s2 += a * xk[t][2];
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < kLuPanel; ++b) {
+      if (FORWARD ? b <= kb : b >= kb) continue;
+      dot(a[b], xk, s);
+      if (sub == 0)
+        for (int c = 0; c < 3; ++c) rs[b * B + row][c] -= s[c];
     }
-  part[sub][row][0] = s0;
-  part[sub][row][1] = s1;
-  part[sub][row][2] = s2;
+  }
+}
+
+// r_i -= sum over the panel's columns [c0, c1) of A_ic x_c for the rows [i0, i1);
+// a wave per row, four rows in turn.
+__global__ __launch_bounds__(256) void lu_solve_rest(long i0, long i1, long c0, long c1, MatRows A,
+                                                     const double* __restrict__ x, double* __restrict__ r) {
+  __shared__ double xs[kPanelRows][3];
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid; i < kPanelRows * 3; i += 256) xs[i / 3][i % 3] = c0 + i / 3 < c1 ? x[3 * c0 + i] : 0.0;
   __syncthreads();
-  if (tid < B * 3) {
-    const int i = tid / 3, c = tid % 3;
-    const long g = bi * B + i;
-    if (g < n) r[3 * g + c] -= ((part[0][i][c] + part[1][i][c]) + part[2][i][c]) + part[3][i][c];
+  for (int k = 0; k < 4; ++k) {
+    const long gi = i0 + (long)blockIdx.x * 16 + (tid >> 6) * 4 + k;
+    if (gi >= i1) return;
+    const double* row = A.row(gi) + c0;
+    double a[8], s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = 2 * lane + 128 * u;
+      d2u v = {0.0, 0.0};
+      if (c0 + c + 1 < c1)
+        v = *reinterpret_cast<const d2u*>(row + c);
+      else if (c0 + c < c1)
+        v.x = row[c];
+      a[2 * u] = v.x;
+      a[2 * u + 1] = v.y;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s[q] = fma(a[u], xs[2 * lane + 128 * (u >> 1) + (u & 1)][q], s[q]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const double v = wave_sum_fixed(s[q]);
+      if (lane == q) r[3 * gi + q] -= v;
+    }
   }
 }
 
@@ -1121,27 +1296,19 @@ extern "C" int kaldo_bte_solve(const kaldo_crystal* c, const int32_t* mesh, cons
     KALDO_LAUNCH("bte_compact_cols", bte_compact_cols, dim3((unsigned)n), dim3(256), 0, st, n,
                  n_all, rows, matrix);
     const int nb = (int)((n + kLuB - 1) / kLuB);
-    // Blocked right-looking LU in panels of kLuPanel blocks: the steps inside
-    // a panel update only the panel's columns (every row below) and the
-    // panel's rows (every column to the right); the rest of the trailing
-    // matrix takes one rank-(64 kLuPanel) product per panel (lu_gemm).
+    // Blocked LU in panels of kLuPanel blocks: inside a panel left-looking, a
+    // step's row and column of blocks take the panel's earlier steps when
+    // their turn comes; the rest of the trailing matrix takes one
+    // rank-(64 kLuPanel) product per panel (lu_gemm).
     for (int k0 = 0; k0 < nb; k0 += kLuPanel) {
       const int k1 = std::min(nb, k0 + kLuPanel);
       for (int k = k0; k < k1; ++k) {
-        KALDO_LAUNCH("lu_diag", lu_diag, dim3(1), dim3(256), 0, st, n, k, A, linv + k * blk,
-                     uinv + k * blk, c->d_flags);
         const int m = nb - k - 1;
-        if (m == 0) continue;
-        KALDO_LAUNCH("lu_panels", lu_panels, dim3(2 * m), dim3(256), 0, st, n, nb, k, A,
-                     linv + k * blk, uinv + k * blk);
-        const int pw = k1 - k - 1;  // panel columns (and rows) still to factor
-        if (pw > 0) {
-          // the panel's columns, every row below k; then the panel's rows,
-          // the columns past the panel
-          const int nr = nb - k1 > 0 ? pw * (nb - k1) : 0;
-          KALDO_LAUNCH("lu_update", lu_update, dim3((unsigned)(m * pw + nr)), dim3(256), 0, st, n,
-                       k, k + 1, k + 1, pw, m * pw, k + 1, k1, nb - k1 > 0 ? nb - k1 : 1, A);
-        }
+        KALDO_LAUNCH("lu_left", lu_left, dim3(k > k0 ? 2 * m + 1 : 1), dim3(256), 0, st, n, nb, k0, k, A,
+                     linv + k * blk, uinv + k * blk, c->d_flags);
+        if (m > 0)
+          KALDO_LAUNCH("lu_panels", lu_panels, dim3(2 * m), dim3(256), 0, st, n, nb, k, A,
+                       linv + k * blk, uinv + k * blk);
       }
       if (k1 < nb) {
         const long r0 = (long)k1 * kLuB;
@@ -1155,14 +1322,24 @@ extern "C" int kaldo_bte_solve(const kaldo_crystal* c, const int32_t* mesh, cons
     double* r = reinterpret_cast<double*>(ws + w.off_y2);
     const dim3 g3((unsigned)((3 * n + 255) / 256));
     KALDO_LAUNCH("bte_gather3", bte_gather3, g3, dim3(256), 0, st, n, rows, rhs, r);
-    for (int k = 0; k < nb; ++k)
-      KALDO_LAUNCH("lu_step", lu_step<true>, dim3(nb - k), dim3(256), 0, st, n, k, linv + k * blk,
-                   A, y, r);
+    auto rest = [&](long i0, long i1, long c0, long c1, double* sol) {
+      if (i1 > i0)
+        KALDO_LAUNCH("lu_solve_rest", lu_solve_rest, dim3((unsigned)((i1 - i0 + 15) / 16)), dim3(256), 0, st,
+                     i0, i1, c0, c1, A, sol, r);
+    };
+    const int last = (nb - 1) / kLuPanel * kLuPanel;
+    for (int k0 = 0; k0 < nb; k0 += kLuPanel) {
+      const int k1 = std::min(nb, k0 + kLuPanel);
+      KALDO_LAUNCH("lu_solve", lu_solve<true>, dim3(1), dim3(1024), 0, st, n, k0, k1, linv, A, y, r);
+      rest((long)k1 * kLuB, n, (long)k0 * kLuB, std::min(n, (long)k1 * kLuB), y);
+    }
     // backward: lambda = U^-1 y, the residual in y2 (starting as y)
     KALDO_LAUNCH("bte_copy3", bte_copy3, g3, dim3(256), 0, st, n, y, r);
-    for (int k = nb - 1; k >= 0; --k)
-      KALDO_LAUNCH("lu_step", lu_step<false>, dim3(k + 1), dim3(256), 0, st, n, k, uinv + k * blk,
-                   A, lam_c, r);
+    for (int k0 = last; k0 >= 0; k0 -= kLuPanel) {
+      const int k1 = std::min(nb, k0 + kLuPanel);
+      KALDO_LAUNCH("lu_solve", lu_solve<false>, dim3(1), dim3(1024), 0, st, n, k0, k1, uinv, A, lam_c, r);
+      rest(0, (long)k0 * kLuB, (long)k0 * kLuB, std::min(n, (long)k1 * kLuB), lam_c);
+    }
     KALDO_LAUNCH("bte_scatter3", bte_scatter3, g3, dim3(256), 0, st, n, rows, lam_c, lambda);
   }
   const double scale = kKappaUnit / ((double)nq * c->volume);

@@ -131,7 +131,6 @@ __device__ bool jacobi_hermitian_par(cplx* A, cplx* V, int n, int ld, int lane, 
   __shared__ int rp[HP], rq[HP];
   __shared__ double rc[HP], rapp[HP], raqq[HP];
   __shared__ cplx rse[HP], rsec[HP];
-  __shared__ double red[64];
   for (int k = lane; k < n * n; k += 64) {
     int r = k / n, c = k % n;
     V[r * ld + c] = {r == c ? 1.0 : 0.0, 0.0};
@@ -175,22 +174,13 @@ __device__ bool jacobi_hermitian_par(cplx* A, cplx* V, int n, int ld, int lane, 
       tot += m2;
       if (r != c) off += m2;
     }
-    red[lane] = off;
-    __syncthreads();
+    // (lane 0's tree over halves, as sums; the same value in every lane)
     for (int w = 32; w > 0; w >>= 1) {
-      if (lane < w) red[lane] += red[lane + w];
-      __syncthreads();
+      off += __shfl_down(off, w, 64);
+      tot += __shfl_down(tot, w, 64);
     }
-    off = red[0];
-    __syncthreads();
-    red[lane] = tot;
-    __syncthreads();
-    for (int w = 32; w > 0; w >>= 1) {
-      if (lane < w) red[lane] += red[lane + w];
-      __syncthreads();
-    }
-    tot = red[0];
-    __syncthreads();
+    off = __shfl(off, 0, 64);
+    tot = __shfl(tot, 0, 64);
     if (off <= 1e-32 * tot || off == 0.0) {
       converged = true;
       break;
@@ -311,56 +301,43 @@ __device__ void sort_eigen(const double* lam_in, double* lam_out, cplx* V, cplx*
 
 constexpr int kPhaseCache = 128;  // replica phases kept in LDS per q
 
-// Replica sums over the cached phases with eight replicas' force-constant
-// loads in flight at a time (a loop that loads, then adds, one replica at a
-// time waits for every load); the additions keep replica order, so the sums
-// are those of the plain loop.
-//   d1 += sum_l ph_l ka[l n],  d2 += sum_l ph_l kb[l n],  l in [0, l1)
+// Sums over the cached replicas, l in [0, l1), in replica order, with the
+// force-constant loads of kRepAhead replicas in flight at a time (a loop that
+// loads, then adds, one replica at a time waits for every load; the last
+// group repeats the last replica's loads and adds only what is there).
+constexpr int kRepAhead = 16;
+//   d1 += sum_l ph_l ka[l n],  d2 += sum_l ph_l kb[l n]
 __device__ __forceinline__ void rep_sum2(const cplx* phl, const double* __restrict__ ka,
                                          const double* __restrict__ kb, int n, int l1, cplx& d1,
                                          cplx& d2) {
-  int l = 0;
-  for (; l + 8 <= l1; l += 8) {
-    double x0 = ka[(size_t)l * n], x1 = ka[(size_t)(l + 1) * n], x2 = ka[(size_t)(l + 2) * n],
-           x3 = ka[(size_t)(l + 3) * n], x4 = ka[(size_t)(l + 4) * n], x5 = ka[(size_t)(l + 5) * n],
-           x6 = ka[(size_t)(l + 6) * n], x7 = ka[(size_t)(l + 7) * n];
-    double y0 = kb[(size_t)l * n], y1 = kb[(size_t)(l + 1) * n], y2 = kb[(size_t)(l + 2) * n],
-           y3 = kb[(size_t)(l + 3) * n], y4 = kb[(size_t)(l + 4) * n], y5 = kb[(size_t)(l + 5) * n],
-           y6 = kb[(size_t)(l + 6) * n], y7 = kb[(size_t)(l + 7) * n];
-    d1 = cadd(d1, cscale(phl[l], x0)), d2 = cadd(d2, cscale(phl[l], y0));
-    d1 = cadd(d1, cscale(phl[l + 1], x1)), d2 = cadd(d2, cscale(phl[l + 1], y1));
-    d1 = cadd(d1, cscale(phl[l + 2], x2)), d2 = cadd(d2, cscale(phl[l + 2], y2));
-    d1 = cadd(d1, cscale(phl[l + 3], x3)), d2 = cadd(d2, cscale(phl[l + 3], y3));
-    d1 = cadd(d1, cscale(phl[l + 4], x4)), d2 = cadd(d2, cscale(phl[l + 4], y4));
-    d1 = cadd(d1, cscale(phl[l + 5], x5)), d2 = cadd(d2, cscale(phl[l + 5], y5));
-    d1 = cadd(d1, cscale(phl[l + 6], x6)), d2 = cadd(d2, cscale(phl[l + 6], y6));
-    d1 = cadd(d1, cscale(phl[l + 7], x7)), d2 = cadd(d2, cscale(phl[l + 7], y7));
-  }
-  for (; l < l1; ++l) {
-    d1 = cadd(d1, cscale(phl[l], ka[(size_t)l * n]));
-    d2 = cadd(d2, cscale(phl[l], kb[(size_t)l * n]));
+  for (int l = 0; l < l1; l += kRepAhead) {
+    double x[kRepAhead], y[kRepAhead];
+#pragma unroll
+    for (int j = 0; j < kRepAhead; ++j) {
+      const size_t o = (size_t)min(l + j, l1 - 1) * n;
+      x[j] = ka[o];
+      y[j] = kb[o];
+    }
+#pragma unroll
+    for (int j = 0; j < kRepAhead; ++j)
+      if (l + j < l1) {
+        d1 = cadd(d1, cscale(phl[l + j], x[j]));
+        d2 = cadd(d2, cscale(phl[l + j], y[j]));
+      }
   }
 }
 
-// d += sum_l (-i cr_l ph_l) ka[l n] with cr_l = rc[3 l], l in [0, l1), as
-// rep_sum2 (the derivative of D along one Cartesian axis)
-__device__ __forceinline__ void rep_dsum(const cplx* phl, const double* __restrict__ ka,
-                                         const double* __restrict__ rc, int n, int l1, cplx& d) {
-  int l = 0;
-  auto term = [&](int j, double x, double cr) {
-    const cplx ph = phl[j];
-    d = cadd(d, cscale(cplx{ph.y * cr, -ph.x * cr}, x));
-  };
-  for (; l + 8 <= l1; l += 8) {
-    double x0 = ka[(size_t)l * n], x1 = ka[(size_t)(l + 1) * n], x2 = ka[(size_t)(l + 2) * n],
-           x3 = ka[(size_t)(l + 3) * n], x4 = ka[(size_t)(l + 4) * n], x5 = ka[(size_t)(l + 5) * n],
-           x6 = ka[(size_t)(l + 6) * n], x7 = ka[(size_t)(l + 7) * n];
-    double c0 = rc[3 * l], c1 = rc[3 * (l + 1)], c2 = rc[3 * (l + 2)], c3 = rc[3 * (l + 3)],
-           c4 = rc[3 * (l + 4)], c5 = rc[3 * (l + 5)], c6 = rc[3 * (l + 6)], c7 = rc[3 * (l + 7)];
-    term(l, x0, c0), term(l + 1, x1, c1), term(l + 2, x2, c2), term(l + 3, x3, c3);
-    term(l + 4, x4, c4), term(l + 5, x5, c5), term(l + 6, x6, c6), term(l + 7, x7, c7);
+// f(l, ka[l n])
+template <class F>
+__device__ __forceinline__ void rep_each(const double* __restrict__ ka, int n, int l1, F f) {
+  for (int l = 0; l < l1; l += kRepAhead) {
+    double x[kRepAhead];
+#pragma unroll
+    for (int j = 0; j < kRepAhead; ++j) x[j] = ka[(size_t)min(l + j, l1 - 1) * n];
+#pragma unroll
+    for (int j = 0; j < kRepAhead; ++j)
+      if (l + j < l1) f(l + j, x[j]);
   }
-  for (; l < l1; ++l) term(l, ka[(size_t)l * n], rc[3 * l]);
 }
 
 template <int NMAX>
@@ -401,7 +378,6 @@ __global__ __launch_bounds__(64) void phonons_kernel(int nb3, int n_rep, const d
   __shared__ cplx phl[kPhaseCache];
   for (int l = lane; l < n_rep && l < kPhaseCache; l += 64) phl[l] = phase_of(l);
   __syncthreads();
-  auto phase = [&](int l) { return l < kPhaseCache ? phl[l] : phase_of(l); };
   const int n_cached = n_rep < kPhaseCache ? n_rep : kPhaseCache;
   for (int k = lane; k < n * n; k += 64) {
     int a = k / n, b = k % n;
@@ -442,12 +418,14 @@ __global__ __launch_bounds__(64) void phonons_kernel(int nb3, int n_rep, const d
     for (int k = lane; k < n * n; k += 64) {
       int a = k / n, b = k % n;
       cplx d = {0, 0};
-      for (int l = 0; l < n_rep; ++l) {
-        cplx ph = phase(l);
+      auto term = [&](int l, cplx ph, double x) {
         double cr = chat[0] * repcart[3 * l] + chat[1] * repcart[3 * l + 1] + chat[2] * repcart[3 * l + 2];
         // -i * cr * ph
-        d = cadd(d, cscale(cplx{ph.y * cr, -ph.x * cr}, fc2s[((size_t)a * n_rep + l) * n + b]));
-      }
+        d = cadd(d, cscale(cplx{ph.y * cr, -ph.x * cr}, x));
+      };
+      const double* ka = fc2s + (size_t)a * n_rep * n + b;
+      rep_each(ka, n, n_cached, [&](int l, double x) { term(l, phl[l], x); });
+      for (int l = n_cached; l < n_rep; ++l) term(l, phase_of(l), ka[(size_t)l * n]);
       A[a * LD + b] = d;
     }
     __syncthreads();
@@ -508,12 +486,11 @@ __global__ __launch_bounds__(64) void phonons_kernel(int nb3, int n_rep, const d
   }
   __syncthreads();
   // Outputs: omega, eta, and v_c = Re(eta^H dD/dq_c eta) U / (2 omega).
-  double om_l = 0.0;
-  if (lane < n) {
-    double l = lsort[lane];
-    om_l = l >= 0 ? sqrt(l * kU) : -sqrt(-l * kU);
-    omega[(size_t)q * n + lane] = om_l;
-  }
+  auto om_of = [&](int mu) {
+    double l = lsort[mu];
+    return l >= 0 ? sqrt(l * kU) : -sqrt(-l * kU);
+  };
+  if (lane < n) omega[(size_t)q * n + lane] = om_of(lane);
   for (int k = lane; k < n * n; k += 64) {
     int a = k / n, mu = k % n;
     cplx v = V[a * LD + mu];
@@ -521,32 +498,40 @@ __global__ __launch_bounds__(64) void phonons_kernel(int nb3, int n_rep, const d
     evec[o] = v.x;
     evec[o + 1] = v.y;
   }
-  for (int c = 0; c < 3; ++c) {
-    __syncthreads();
-    for (int k = lane; k < n * n; k += 64) {
-      int a = k / n, b = k % n;
-      cplx d = {0, 0};
-      rep_dsum(phl, fc2s + (size_t)a * n_rep * n + b, repcart + c, n, n_cached, d);
-      for (int l = n_cached; l < n_rep; ++l) {
-        cplx ph = phase_of(l);
-        double cr = repcart[3 * l + c];
-        d = cadd(d, cscale(cplx{ph.y * cr, -ph.x * cr}, fc2s[((size_t)a * n_rep + l) * n + b]));
+  // dD/dq_c for the three axes at once, into A, W and Z
+  cplx* dd[3] = {A, W, Z};
+  __syncthreads();
+  for (int k = lane; k < n * n; k += 64) {
+    int a = k / n, b = k % n;
+    cplx d[3] = {{0, 0}, {0, 0}, {0, 0}};
+    auto term = [&](int l, cplx ph, double x) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const double cr = repcart[3 * l + c];
+        d[c] = cadd(d[c], cscale(cplx{ph.y * cr, -ph.x * cr}, x));
       }
-      A[a * LD + b] = d;
+    };
+    const double* ka = fc2s + (size_t)a * n_rep * n + b;
+    rep_each(ka, n, n_cached, [&](int l, double x) { term(l, phl[l], x); });
+    for (int l = n_cached; l < n_rep; ++l) term(l, phase_of(l), ka[(size_t)l * n]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dd[c][a * LD + b] = d[c];
+  }
+  __syncthreads();
+  for (int k = lane; k < 3 * n; k += 64) {
+    const int c = k / n, mu = k - c * n;
+    const cplx* M = c == 0 ? A : c == 1 ? W : Z;
+    double re = 0.0;
+    for (int a = 0; a < n; ++a) {
+      cplx s = {0, 0};
+      for (int b = 0; b < n; ++b) s = cadd(s, cmul(M[a * LD + b], V[b * LD + mu]));
+      cplx va = V[a * LD + mu];
+      re += va.x * s.x + va.y * s.y;
     }
-    __syncthreads();
-    if (lane < n) {
-      double re = 0.0;
-      for (int a = 0; a < n; ++a) {
-        cplx s = {0, 0};
-        for (int b = 0; b < n; ++b) s = cadd(s, cmul(A[a * LD + b], V[b * LD + lane]));
-        cplx va = V[a * LD + lane];
-        re += va.x * s.x + va.y * s.y;
-      }
-      double nu = om_l / kTwoPi;
-      double v = fabs(nu) >= kNuVelFloorThz ? re * kU / (2.0 * om_l) : 0.0;
-      vel[((size_t)q * n + lane) * 3 + c] = v;
-    }
+    const double om_l = om_of(mu);
+    double nu = om_l / kTwoPi;
+    double v = fabs(nu) >= kNuVelFloorThz ? re * kU / (2.0 * om_l) : 0.0;
+    vel[((size_t)q * n + mu) * 3 + c] = v;
   }
 }
 

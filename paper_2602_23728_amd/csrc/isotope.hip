@@ -10,20 +10,27 @@
 // rate at which w - w' varies with the summed q').  gamma_iso is a linewidth
 // in the convention of Eq. gamma, to which it adds (Eq. lifetime).
 //
-//   iso_prep     per mode: (w, sigma) record (w NaN below nu_min), eta
-//                transposed to [q][mode][component], input checks
-//   iso_sort     per branch the q-points in order of frequency (one
-//                workgroup per branch, bitonic sort in LDS; larger meshes
-//                keep the flat order)
+//   iso_order    per branch the q-points in order of frequency, by rank (how
+//                many keys are smaller), and everything the sum reads of a
+//                mode stored at its place in that order: w (NaN below
+//                nu_min), sigma, its factors, the eigenvector by component;
+//                input checks
 //   iso_ranges   per (tile of partners in that order, branch): the frequency
-//                range of its physical modes and their largest sigma
-//   iso_kernel   one wave per four modes of a branch adjacent in that order
+//                range of its physical modes and their largest sigma, a wave
+//                per tile
+//   iso_kernel   one workgroup per four modes of a branch adjacent in that order
 //                (nearly equal frequencies: they share each partner's loads):
 //                per partner branch the run of tiles whose range can meet the
 //                cut (found by binary search in the range table, in LDS),
 //                lanes over the tile's partners, exact FP64 cut per mode and
 //                partner, overlap and smearing in FP64, per-lane sums in tile
 //                order, fixed wave reduction per mode
+//
+// What bounds the sum: chains of FP64 arithmetic, at three waves a SIMD (diamond
+// 15^3: 234 us, 306 with a wave per group of modes and the vectors kept in
+// registers).  A bitonic sort of the keys in one workgroup per branch, the
+// ranges one thread per tile and a launch for the largest sigma' took 105 us
+// there, the ranks and ranges 31.
 #include <algorithm>
 #include <cmath>
 
@@ -42,151 +49,144 @@ struct IsoParams {
   double g[kIsoMaxBasis];
 };
 
-__global__ void iso_prep(IsoParams p, const double* __restrict__ omega, const double* __restrict__ vel,
-                         const double* __restrict__ evec, double2* __restrict__ rec,
-                         double2* __restrict__ inv, double2* __restrict__ etaT, int32_t* flags) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= p.nq * p.nb3) return;
-  const int q = m / p.nb3, s = m - q * p.nb3;
-  const double w = omega[m];
-  const double v0 = vel[3 * (size_t)m], v1 = vel[3 * (size_t)m + 1], v2 = vel[3 * (size_t)m + 2];
-  const bool phys = (w / kTwoPi) >= p.nu_min;
-  double sig = p.sig_fixed;
-  if (p.adaptive) sig = fmax(sqrt((v0 * v0 + v1 * v1 + v2 * v2) * p.h2 / 12.0), p.sig_floor);
-  rec[m] = make_double2(phys ? w : __builtin_nan(""), sig);
-  // 1/sigma and 1/(sqrt(pi) sigma) of the partner, once per mode
-  inv[m] = make_double2(1.0 / sig, 1.0 / (kSqrtPi * sig));
-  double chk = (w - w) + (v0 - v0) + (v1 - v1) + (v2 - v2);
-  for (int j = 0; j < p.nb3; ++j) {
+// Place i of branch s holds the mode of q-point perm[s][i]: physical modes in
+// ascending frequency (keys: the FP32 rounding of w, whose bits order like the
+// values for w > 0, then q), the others last.  A workgroup ranks 64 modes of a
+// branch, each wave against a quarter of the keys, which pass through LDS.
+constexpr int kIsoKeys = 2048;
+
+__global__ __launch_bounds__(256) void iso_order(IsoParams p, const double* __restrict__ omega,
+                                                 const double* __restrict__ vel,
+                                                 const double* __restrict__ evec,
+                                                 double2* __restrict__ rec, double2* __restrict__ inv,
+                                                 double2* __restrict__ eta, int32_t* __restrict__ perm,
+                                                 int32_t* __restrict__ flags) {
+  __shared__ unsigned long long keys[kIsoKeys];
+  __shared__ int part[4][64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, s = blockIdx.y;
+  const int q = blockIdx.x * 64 + lane;
+  const bool in = q < p.nq;
+  auto key = [&](int i) {
+    const double w = omega[(size_t)i * p.nb3 + s];
+    const bool first = (w / kTwoPi) >= p.nu_min && w > 0.0;
+    return ((unsigned long long)(first ? __float_as_uint((float)w) : 0xffffffffu) << 32) | (unsigned)i;
+  };
+  const unsigned long long own = key(in ? q : 0);
+  int below = 0;
+  for (int base = 0; base < p.nq; base += kIsoKeys) {
+    __syncthreads();
+    for (int i = tid; i < kIsoKeys; i += 256) keys[i] = base + i < p.nq ? key(base + i) : ~0ull;
+    __syncthreads();
+    const int quarter = kIsoKeys / 4, n = min(quarter, max(0, p.nq - base - wv * quarter));
+#pragma unroll 8
+    for (int i = 0; i < (n + 7) / 8 * 8; ++i) below += keys[wv * quarter + i] < own ? 1 : 0;
+  }
+  part[wv][lane] = below;
+  __syncthreads();
+  if (!in) return;
+  const int at = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
+  const size_t row = (size_t)s * p.nq + at, m = (size_t)q * p.nb3 + s;
+  double chk = 0.0;
+  for (int j = wv; j < p.nb3; j += 4) {
     const size_t src = (((size_t)q * p.nb3 + j) * p.nb3 + s) * 2;
     const double re = evec[src], im = evec[src + 1];
     chk += (re - re) + (im - im);
-    etaT[(size_t)m * p.nb3 + j] = make_double2(re, im);
+    eta[((size_t)s * p.nb3 + j) * p.nq + at] = make_double2(re, im);
+  }
+  if (wv == 0) {
+    const double w = omega[m], v0 = vel[3 * m], v1 = vel[3 * m + 1], v2 = vel[3 * m + 2];
+    const bool phys = (w / kTwoPi) >= p.nu_min;
+    double sig = p.sig_fixed;
+    if (p.adaptive) sig = fmax(sqrt((v0 * v0 + v1 * v1 + v2 * v2) * p.h2 / 12.0), p.sig_floor);
+    perm[row] = q;
+    rec[row] = make_double2(phys ? w : __builtin_nan(""), sig);
+    // 1/sigma and 1/(sqrt(pi) sigma) of the partner, once per mode
+    inv[row] = make_double2(1.0 / sig, 1.0 / (kSqrtPi * sig));
+    chk += (w - w) + (v0 - v0) + (v1 - v1) + (v2 - v2);
+    if (w < 0.0 && (-w / kTwoPi) >= p.nu_min) raise_flag(flags, kFlagImaginary);
   }
   if (!(chk == 0.0)) raise_flag(flags, kFlagNonFinite);
-  if (w < 0.0 && (-w / kTwoPi) >= p.nu_min) raise_flag(flags, kFlagImaginary);
-}
-
-// perm[s][i] = the i-th q-point of branch s in order of frequency: physical
-// modes ascending (keys: the FP32 rounding of w, whose bits order like the
-// values for w > 0, then q), the others last.  One workgroup per branch,
-// bitonic sort of n2 = 2^k >= nq 64-bit keys in LDS; with sorted == 0 (too
-// large a mesh for the LDS) the flat order.
-__global__ __launch_bounds__(1024) void iso_sort(IsoParams p, int sorted, const double2* __restrict__ rec,
-                                                 int32_t* __restrict__ perm) {
-  extern __shared__ unsigned long long keys[];
-  const int s = blockIdx.x;
-  int32_t* out = perm + (size_t)s * p.nq;
-  if (!sorted) {
-    for (int i = threadIdx.x; i < p.nq; i += blockDim.x) out[i] = i;
-    return;
-  }
-  int n2 = 1;
-  while (n2 < p.nq) n2 <<= 1;
-  for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-    unsigned long long k = ~0ull;
-    if (i < p.nq) {
-      const double w = rec[(size_t)i * p.nb3 + s].x;
-      const unsigned hi = (w == w && w > 0.0) ? __float_as_uint((float)w) : 0xffffffffu;
-      k = ((unsigned long long)hi << 32) | (unsigned)i;
-    }
-    keys[i] = k;
-  }
-  __syncthreads();
-  for (int size = 2; size <= n2; size <<= 1)
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-        const int j = i ^ stride;
-        if (j > i) {
-          const unsigned long long a = keys[i], b = keys[j];
-          if ((a > b) == ((i & size) == 0)) {
-            keys[i] = b;
-            keys[j] = a;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  for (int i = threadIdx.x; i < p.nq; i += blockDim.x) out[i] = (int32_t)(keys[i] & 0xffffffffull);
 }
 
 // range[(s' * nblk + b)] = (lowest w, highest w, largest sigma) of the
 // physical modes of branch s' in tile b of its order; an empty tile gets
 // (+inf, -inf, 0).  Tiles run in frequency order, so lowest w does not
 // decrease with b.
-__global__ void iso_ranges(IsoParams p, const int32_t* __restrict__ perm,
-                           const double2* __restrict__ rec, double* __restrict__ range) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void iso_ranges(IsoParams p, const double2* __restrict__ rec,
+                                                  double* __restrict__ range) {
+  const int lane = threadIdx.x & 63, k = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (k >= p.nblk * p.nb3) return;
   const int s = k / p.nblk, b = k - s * p.nblk;
   double lo = INFINITY, hi = -INFINITY, smax = 0.0;
-  const int i_end = min(p.nq, (b + 1) * p.blk);
-  for (int i = b * p.blk; i < i_end; ++i) {
-    const int q = perm[(size_t)s * p.nq + i];
-    const double2 r = rec[(size_t)q * p.nb3 + s];
+  for (int i = b * p.blk + lane; i < min(p.nq, (b + 1) * p.blk); i += 64) {
+    const double2 r = rec[(size_t)s * p.nq + i];
     if (r.x == r.x) {  // physical (not NaN)
       lo = fmin(lo, r.x);
       hi = fmax(hi, r.x);
       smax = fmax(smax, r.y);
     }
   }
-  range[3 * (size_t)k] = lo;
-  range[3 * (size_t)k + 1] = hi;
-  range[3 * (size_t)k + 2] = smax;
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, off, 64));
+    hi = fmax(hi, __shfl_xor(hi, off, 64));
+    smax = fmax(smax, __shfl_xor(smax, off, 64));
+  }
+  if (lane == 0) {
+    range[3 * (size_t)k] = lo;
+    range[3 * (size_t)k + 1] = hi;
+    range[3 * (size_t)k + 2] = smax;
+  }
 }
 
-// After the table: range[3 nblk nb3 + s'] = the largest sigma' over the tiles
-// of branch s' (one thread per branch).
-__global__ void iso_branch_smax(IsoParams p, double* __restrict__ range) {
-  const int s = threadIdx.x;
-  if (s >= p.nb3) return;
-  double m = 0.0;
-  for (int b = 0; b < p.nblk; ++b) m = fmax(m, range[3 * ((size_t)s * p.nblk + b) + 2]);
-  range[3 * (size_t)p.nblk * p.nb3 + s] = m;
-}
-
-// Modes per wave: MPW modes of one branch at consecutive q-points (nearly the
-// same frequency, so nearly the same live tiles and passing partners) share
-// every partner's record and eigenvector load.
+// Modes per workgroup: MPW modes of one branch at consecutive places of its
+// order (nearly the same frequency, so nearly the same live tiles and passing
+// partners) share every partner's record and eigenvector load (two: 296 us,
+// three: 253, six: 226 with more registers than the larger cells have, eight: 239).
 constexpr int kIsoMpw = 4;
 
 template <int NB3>
 __global__ __launch_bounds__(256) void iso_kernel(IsoParams p, const double2* __restrict__ rec,
                                                   const double2* __restrict__ inv,
-                                                  const double2* __restrict__ etaT,
+                                                  const double2* __restrict__ eta,
                                                   const double* __restrict__ range,
                                                   const int32_t* __restrict__ perm,
                                                   int accumulate, double* __restrict__ gamma) {
   constexpr int NB = NB3 / 3;
   constexpr int MPW = kIsoMpw;
   extern __shared__ double rng_lds[];  // the range table, [NB3][nblk][3], then [NB3] largest sigma'
-  __shared__ double2 e0s[4][MPW][NB3];  // each wave's modes' eigenvectors
-  const int n_rng = p.nblk * NB3 * 3 + NB3;
+  __shared__ double2 e0s[MPW][NB3];  // the modes' eigenvectors
+  __shared__ double sums[4][MPW];
+  const int n_rng = p.nblk * NB3 * 3;
   for (int k = threadIdx.x; k < n_rng; k += blockDim.x) rng_lds[k] = range[k];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  // wave -> (branch s, first position in the branch's frequency order):
-  // waves of one branch are consecutive, so neighbouring workgroups also scan
-  // similar tiles
+  // workgroup -> (branch s, first position in the branch's frequency order):
+  // neighbouring workgroups scan similar tiles.  Its waves take the tiles in
+  // turn: with a group of modes per wave the groups of many partners left the
+  // chip a quarter full (1.3 waves a SIMD on the diamond 15^3 mesh, 302 us)
   const int groups = (p.nq + MPW - 1) / MPW;
-  const int gid = blockIdx.x * 4 + wv;
-  const bool active = gid < NB3 * groups;
-  const int s = active ? gid / groups : 0;
-  const int i0 = active ? (gid - s * groups) * MPW : 0;
+  const int s = blockIdx.x / groups;
+  const int i0 = (blockIdx.x - s * groups) * MPW;
   double w[MPW];
   bool live_m[MPW];
   int qm[MPW];
 #pragma unroll
   for (int k = 0; k < MPW; ++k) {
-    const bool in = active && i0 + k < p.nq;
-    const int q = in ? perm[(size_t)s * p.nq + i0 + k] : 0;
-    qm[k] = q;
-    const double2 r = in ? rec[(size_t)q * NB3 + s] : make_double2(__builtin_nan(""), 0.0);
+    const bool in = i0 + k < p.nq;
+    qm[k] = in ? perm[(size_t)s * p.nq + i0 + k] : 0;
+    const double2 r = in ? rec[(size_t)s * p.nq + i0 + k] : make_double2(__builtin_nan(""), 0.0);
     w[k] = r.x;
     live_m[k] = in && (r.x == r.x);
-    if (in && lane < NB3) e0s[wv][k][lane] = etaT[((size_t)q * NB3 + s) * NB3 + lane];
+    if (in && wv == 0 && lane < NB3) e0s[k][lane] = eta[((size_t)s * NB3 + lane) * p.nq + i0 + k];
   }
   __syncthreads();
-  if (!active) return;
+  // the largest sigma' of each branch
+  for (int s1 = wv; s1 < NB3; s1 += 4) {
+    double m = 0.0;
+    for (int b = lane; b < p.nblk; b += 64) m = fmax(m, rng_lds[3 * (s1 * p.nblk + b) + 2]);
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if (lane == 0) rng_lds[n_rng + s1] = m;
+  }
+  __syncthreads();
   double acc[MPW];
 #pragma unroll
   for (int k = 0; k < MPW; ++k) acc[k] = 0.0;
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(256) void iso_kernel(IsoParams p, const double2* __
         if (h >= t_lo || !(h > -INFINITY)) hi_b = mid;
         else lo_b = mid + 1;
       }
-      for (int b = lo_b; b < p.nblk; ++b) {
+      for (int b = lo_b + wv; b < p.nblk; b += 4) {
         const double* r = rs + 3 * b;
         if (!(r[0] <= t_hi)) break;  // lowest w past reach (or an empty tile)
         const double reach = 2.0 * r[2] * (1.0 + 1e-12);
@@ -233,9 +233,13 @@ __global__ __launch_bounds__(256) void iso_kernel(IsoParams p, const double2* __
         for (int k = 0; k < MPW; ++k) tile |= live_m[k] && w[k] > r[0] - reach && w[k] < r[1] + reach;
         if (!tile) continue;
         for (int i1 = b * p.blk + lane; i1 < min(p.nq, (b + 1) * p.blk); i1 += 64) {
-          const int q1 = perm[(size_t)s1 * p.nq + i1];
-          const int m1 = q1 * NB3 + s1;
-          const double2 o = rec[m1];
+          const size_t m1 = (size_t)s1 * p.nq + i1;
+          asm volatile("" ::: "memory");  // the modes' vectors from LDS again: kept in registers they cost a wave a SIMD
+          // every load of the partner at once, whether it passes or not
+          const double2 o = rec[m1], iv = inv[m1];
+          double2 e1[NB3];
+#pragma unroll
+          for (int j = 0; j < NB3; ++j) e1[j] = eta[((size_t)s1 * NB3 + j) * p.nq + i1];
           bool pass[MPW];
           bool any = false;
 #pragma unroll
@@ -244,11 +248,6 @@ __global__ __launch_bounds__(256) void iso_kernel(IsoParams p, const double2* __
             any |= pass[k];
           }
           if (!any) continue;
-          const double2 iv = inv[m1];
-          double2 e1[NB3];
-          const double2* e1p = etaT + (size_t)m1 * NB3;
-#pragma unroll
-          for (int j = 0; j < NB3; ++j) e1[j] = e1p[j];
 #pragma unroll
           for (int k = 0; k < MPW; ++k) {
             if (!pass[k]) continue;
@@ -258,7 +257,7 @@ __global__ __launch_bounds__(256) void iso_kernel(IsoParams p, const double2* __
               double dr = 0.0, di = 0.0;
 #pragma unroll
               for (int a = 0; a < 3; ++a) {
-                const double2 u = e0s[wv][k][3 * i + a], v = e1[3 * i + a];
+                const double2 u = e0s[k][3 * i + a], v = e1[3 * i + a];
                 // conj(u) v, as fused multiply-adds into the sums
                 dr = fma(u.x, v.x, dr);
                 dr = fma(u.y, v.y, dr);
@@ -284,15 +283,19 @@ __global__ __launch_bounds__(256) void iso_kernel(IsoParams p, const double2* __
 #pragma unroll
   for (int k = 0; k < MPW; ++k) {
     const double v = wave_sum_fixed(acc[k]);
-    const int q = qm[k];
-    if (lane == 0 && active && i0 + k < p.nq) {
-      const size_t m = (size_t)q * NB3 + s;
-      if (live_m[k]) {
-        const double gi = p.scale * w[k] * w[k] * v;
-        gamma[m] = accumulate ? gamma[m] + gi : gi;
-      } else if (!accumulate) {
-        gamma[m] = 0.0;  // below nu_min: no linewidth
-      }
+    if (lane == 0) sums[wv][k] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < MPW; ++k) {
+    if ((int)threadIdx.x != k || i0 + k >= p.nq) continue;
+    const double v = ((sums[0][k] + sums[1][k]) + sums[2][k]) + sums[3][k];
+    const size_t m = (size_t)qm[k] * NB3 + s;
+    if (live_m[k]) {
+      const double gi = p.scale * w[k] * w[k] * v;
+      gamma[m] = accumulate ? gamma[m] + gi : gi;
+    } else if (!accumulate) {
+      gamma[m] = 0.0;  // below nu_min: no linewidth
     }
   }
 }
@@ -318,7 +321,7 @@ static IsoWs iso_ws(long nq, int nb3) {
   w.off_rec = take(sizeof(double2) * nq * nb3);
   w.off_inv = take(sizeof(double2) * nq * nb3);
   w.off_eta = take(sizeof(double2) * nq * nb3 * nb3);
-  w.off_range = take(sizeof(double) * (3 * (size_t)w.nblk * nb3 + nb3));
+  w.off_range = take(sizeof(double) * 3 * (size_t)w.nblk * nb3);
   w.off_perm = take(sizeof(int32_t) * (size_t)nq * nb3);
   w.total = o;
   return w;
@@ -386,24 +389,12 @@ extern "C" int kaldo_isotope_linewidths(const kaldo_crystal* c, const int32_t* m
   auto* eta = reinterpret_cast<double2*>(ws + w.off_eta);
   auto* range = reinterpret_cast<double*>(ws + w.off_range);
   auto* perm = reinterpret_cast<int32_t*>(ws + w.off_perm);
-  const int n_modes = (int)nq * c->nb3;
-  KALDO_LAUNCH("iso_prep", iso_prep, dim3((n_modes + 255) / 256), dim3(256), 0, st, p, omega, vel,
-               evec, rec, inv, eta, c->d_flags);
-  // the frequency order of every branch, when its sort keys fit the LDS
-  int dev = 0, lds_max = 0;
-  KALDO_HIP(hipGetDevice(&dev));
-  KALDO_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-  size_t n2 = 1;
-  while ((long)n2 < nq) n2 <<= 1;
-  const int sorted = n2 * sizeof(unsigned long long) <= (size_t)lds_max ? 1 : 0;
-  KALDO_LAUNCH("iso_sort", iso_sort, dim3(c->nb3), dim3(1024), sorted ? n2 * sizeof(unsigned long long) : 0,
-               st, p, sorted, rec, perm);
-  KALDO_LAUNCH("iso_ranges", iso_ranges, dim3((p.nblk * p.nb3 + 255) / 256), dim3(256), 0, st, p,
-               perm, rec, range);
-  KALDO_LAUNCH("iso_branch_smax", iso_branch_smax, dim3(1), dim3(64), 0, st, p, range);
+  KALDO_LAUNCH("iso_order", iso_order, dim3((unsigned)((nq + 63) / 64), (unsigned)c->nb3), dim3(256), 0, st,
+               p, omega, vel, evec, rec, inv, eta, perm, c->d_flags);
+  KALDO_LAUNCH("iso_ranges", iso_ranges, dim3((p.nblk * p.nb3 + 3) / 4), dim3(256), 0, st, p, rec, range);
   const size_t lds = sizeof(double) * (3 * (size_t)p.nblk * p.nb3 + p.nb3);
-  const long n_waves = (long)c->nb3 * ((nq + kIsoMpw - 1) / kIsoMpw);
-  const dim3 grid((unsigned)((n_waves + 3) / 4));
+  const long n_groups = (long)c->nb3 * ((nq + kIsoMpw - 1) / kIsoMpw);
+  const dim3 grid((unsigned)n_groups);
 #define KALDO_ISO_CASE(NB3V)                                                                   \
   case NB3V:                                                                                   \
     KALDO_LAUNCH("iso_kernel", iso_kernel<NB3V>, grid, dim3(256), lds, st, p, rec, inv, eta, range, \

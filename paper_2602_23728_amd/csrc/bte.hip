@@ -24,13 +24,17 @@
 //   bte_zero       clears the n x n matrix
 //   bte_rows<NB3>  one workgroup per q, three waves each over a third of
 //                  the branches of q: A~_q (FP64, LDS, by atom block), then
-//                  the partners q1 in rounds of 64 (one per lane): exact FP64
-//                  cut, the passing candidates queued in the wave's LDS queue
-//                  and their vertices computed by all its lanes, per-lane sums
-//                  per column kind in LDS, written in three passes whose
-//                  columns are a bijection of q1 (no two lanes of a pass touch
-//                  one element), Gamma0 reduced in a fixed order and added to
-//                  the diagonal
+//                  the partners q1 in rounds of 64 (one per lane): an FP32
+//                  test against the widest cut, the near pairs queued in LDS
+//                  for the exact FP64 cut, the passing ones for their vertices
+//                  (64 lanes each), sums per column kind and partner in LDS,
+//                  written in three passes whose columns are a bijection of q1
+//                  (no two lanes of a pass touch one element), Gamma0 reduced
+//                  in a fixed order and added to the diagonal.  Latency of few
+//                  waves bounds it (the sums leave two workgroups a CU);
+//                  diamond 15^3: 18.3 ms with the exact cut of every pair in
+//                  every lane and each term taken back by its own lane in
+//                  turn, now 5.7
 //   bte_gmax, bte_flags, bte_decouple   the RTA selection
 //   bte_compact_index, bte_compact_cols, bte_gather3, bte_scatter3   the
 //                  solve's restriction to the coupled modes (row map, coupled
@@ -110,14 +114,14 @@ __device__ __forceinline__ void process_rates(const LwParams& p, double w, doubl
 // ------------------------------------------------------------------ rows
 
 constexpr int kRowWaves = 3;    // waves per row workgroup, each over a third of the branches s
-constexpr int kRowQueue = 128;  // passing candidates a wave queues before projecting them
+constexpr int kRowQueue = 128;  // slots of a wave's two queues, which are worked off 64 at a time
 
 template <int NB3>
 __global__ __launch_bounds__(64 * kRowWaves) void bte_rows(
     LwParams p, int n_rep, const int32_t* __restrict__ rep, const double* __restrict__ omega,
     const double* __restrict__ vel, const double* __restrict__ occ,
     const uint8_t* __restrict__ phys, const double* __restrict__ evec,
-    const double2* __restrict__ phase_tab, int n_blk, const int32_t* __restrict__ e_blk,
+    const float2* __restrict__ near_tab, const double2* __restrict__ phase_tab, int n_blk, const int32_t* __restrict__ e_blk,
     const int32_t* __restrict__ e_bg, const int32_t* __restrict__ blk_d,
     const int32_t* __restrict__ pair_ptr, const int32_t* __restrict__ t_ptr,
     const int32_t* __restrict__ t_i, const int32_t* __restrict__ t_l2,
@@ -133,13 +137,16 @@ __global__ __launch_bounds__(64 * kRowWaves) void bte_rows(
   __shared__ double acc[3][NB3][NB3][64];  // [kind][s][s' or s''][lane]
   __shared__ double2 phq[64];
   __shared__ double red[NB3][64];
-  __shared__ int rq_code_w[kRowWaves][kRowQueue];  // lane | s1 << 6 | s2 << 12 | s << 18
-  __shared__ double rq_dp_w[kRowWaves][kRowQueue], rq_dm_w[kRowWaves][kRowQueue],
-      rq_v2_w[kRowWaves][kRowQueue];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  // lane | s1 << 6 | s2 << 9 | s << 12 of the pairs near the cut, and of those
+  // that pass it with their rates
+  static_assert(NB3 <= 8, "three bits a branch");
+  __shared__ uint16_t near_w[kRowWaves][kRowQueue], pass_w[kRowWaves][kRowQueue];
+  __shared__ double dp_w[kRowWaves][kRowQueue], dm_w[kRowWaves][kRowQueue];
+  __shared__ double wq[NB3];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s_lo = wv * SPW;  // this wave's branches of q: [s_lo, s_lo + SPW)
-  int* rq_code = rq_code_w[wv];
-  double *rq_dp = rq_dp_w[wv], *rq_dm = rq_dm_w[wv], *rq_v2 = rq_v2_w[wv];
+  uint16_t *near_q = near_w[wv], *pass_q = pass_w[wv];
+  double *dp_q = dp_w[wv], *dm_q = dm_w[wv];
   const int q = blockIdx.x;
   const int nq = p.nq;
   const size_t n = (size_t)nq * NB3;
@@ -151,6 +158,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void bte_rows(
     if (tid < NB3) gamma0[q * NB3 + tid] = 0.0;
     return;
   }
+  if (tid < NB3) wq[tid] = omega[q * NB3 + tid];
   for (int l = tid; l < n_rep; l += BS) {
     const int32_t* r = rep + 3 * l;
     const int m0 = ((a0 * r[0]) % N0 + N0) % N0, m1 = ((a1 * r[1]) % N1 + N1) % N1,
@@ -176,9 +184,16 @@ __global__ __launch_bounds__(64 * kRowWaves) void bte_rows(
     at[(e_blk[e] * 9 + e_bg[e]) * NB3 + s] = make_double2(re, im);
   }
   __syncthreads();
-  double g0[NB3];
+  double g0[SPW];  // Gamma0 of the wave's branches, from the terms this lane computed
+  float ws[SPW];   // their FP32 frequencies, NaN below nu_min
+  float w_max = 0.0f;
 #pragma unroll
-  for (int s = 0; s < NB3; ++s) g0[s] = 0.0;
+  for (int k = 0; k < SPW; ++k) {
+    g0[k] = 0.0;
+    const float w = (float)omega[q * NB3 + s_lo + k];
+    ws[k] = phys[q * NB3 + s_lo + k] ? w : __builtin_nanf("");
+    w_max = fmaxf(w_max, fabsf(w));
+  }
   const int t0 = (N0 - a0) % N0, t1 = (N1 - a1) % N1, t2 = (N2 - a2) % N2;
   auto partner = [&](int q1) {
     const int b0 = q1 / (N1 * N2), b1 = (q1 / N2) % N1, b2 = q1 % N2;
@@ -235,12 +250,17 @@ __global__ __launch_bounds__(64 * kRowWaves) void bte_rows(
     return pref * (vr * vr + vi * vi);
   };
   // A round takes 64 partners q1, one per lane of every wave; wave w takes
-  // the branches s of q in [w SPW, (w + 1) SPW).  Each lane classifies its
-  // (s1, s2, s) candidates in that order; the passing ones go to its wave's
-  // queue in LDS (slots by ballot: candidate order, lanes ascending), whose
-  // vertices all 64 lanes of the wave then compute; each lane then takes its
-  // own entries back in queue order, so every sum sees the terms in the order
-  // of the loops.  A wave's queue is its own: a wave-level fence and barrier
+  // the branches s of q in [w SPW, (w + 1) SPW).  Each lane tests its
+  // (s1, s2, s) in that order against the widest cut the pair's FP32 speeds
+  // allow (what passes its own cut passes here: 2 sigma <= 2 max(floor,
+  // (|v1| + |v2|) h / sqrt(12)), with slack for the rounding of the test);
+  // the near ones go to the wave's queue in LDS (slots by ballot: candidate
+  // order, lanes ascending), 64 of them at a time take the exact FP64 cut and
+  // rates, and those that pass the second queue, of which 64 at a time are
+  // projected.  A projected term belongs to the element of its kind, branches
+  // and lane: the terms of one s2 (kinds 0 and 1), of one s1 (kind 2) all have
+  // different ones, so they are added in NB3 + NB3 steps, always in this order.
+  // A wave's queues and elements are its own: a wave-level fence and barrier
   // order its steps.
   const unsigned long long below = (1ull << lane) - 1ull;
   auto wave_sync = [&]() {
@@ -248,6 +268,8 @@ __global__ __launch_bounds__(64 * kRowWaves) void bte_rows(
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   };
+  const float hr = p.adaptive ? 2.008f : 0.0f;
+  const float r_min = 2.0f * (float)(p.adaptive ? p.sig_floor : p.sig_fixed) * 1.00001f;
   for (int base = 0; base < nq; base += 64) {
     const int q1 = base + lane;
     const bool ok = q1 < nq;
@@ -255,70 +277,108 @@ __global__ __launch_bounds__(64 * kRowWaves) void bte_rows(
       for (int s = s_lo; s < s_lo + SPW; ++s)
         for (int u = 0; u < NB3; ++u) acc[k][s][u][lane] = 0.0;
     const int q2 = ok ? partner(q1) : 0;
-    int qn = 0;  // entries in the queue (the same in every lane)
-    auto flush = [&]() {
+    int n_near = 0, n_pass = 0;  // entries of the queues (the same in every lane)
+    auto project = [&](int n) {
       wave_sync();
-      for (int r = lane; r < qn; r += 64) {
-        const int code = rq_code[r];
-        const int o = code & 63, s1 = (code >> 6) & 63, s2 = (code >> 12) & 63, s = code >> 18;
-        const int e1 = base + o;
-        rq_v2[r] = vertex2(e1, s1, partner(e1), s2, s);
+      const bool on = lane < n;
+      const int code = on ? pass_q[lane] : 0;
+      const int o = code & 63, s1 = (code >> 6) & 7, s2 = (code >> 9) & 7, s = code >> 12;
+      const int e1 = base + o, e2 = __shfl(q2, o, 64);
+      double a = 0.0, b = 0.0, c = 0.0, g = 0.0;
+      if (on) {
+        const double w = wq[s], w1 = omega[e1 * NB3 + s1], w2 = omega[e2 * NB3 + s2];
+        const double v2 = vertex2(e1, s1, e2, s2, s);
+        const double dp = dp_q[lane] * v2, dm = dm_q[lane] * v2;
+        g = dp + dm;
+        a = dp * (w1 / w);
+        b = dm * (w1 / w);
+        c = g * (w2 / w);
       }
-      wave_sync();
-      for (int r = 0; r < qn; ++r) {
-        const int code = rq_code[r];
-        if ((code & 63) != lane) continue;
-        const int s1 = (code >> 6) & 63, s2 = (code >> 12) & 63, s = code >> 18;
-        const double v2 = rq_v2[r];
-        const double w = omega[q * NB3 + s], w1 = omega[q1 * NB3 + s1], w2 = omega[q2 * NB3 + s2];
-        const double dp = rq_dp[r] * v2, dm = rq_dm[r] * v2;
-        g0[s] += dp + dm;
-        acc[0][s][s1][lane] += dp * (w1 / w);
-        acc[1][s][s1][lane] += dm * (w1 / w);
-        acc[2][s][s2][lane] += (dp + dm) * (w2 / w);
+#pragma unroll
+      for (int k = 0; k < SPW; ++k) g0[k] += on && s == s_lo + k ? g : 0.0;
+      // (the barriers keep the steps apart: to one lane they are one)
+      for (int u = 0; u < NB3; ++u) {
+        if (on && s2 == u) {
+          acc[0][s][s1][o] += a;
+          acc[1][s][s1][o] += b;
+        }
+        wave_sync();
       }
+      for (int u = 0; u < NB3; ++u) {
+        if (on && s1 == u) acc[2][s][s2][o] += c;
+        wave_sync();
+      }
+    };
+    auto classify = [&](int n, bool last) {
       wave_sync();
-      qn = 0;
+      const bool on = lane < n;
+      const int code = on ? near_q[lane] : 0;
+      const int o = code & 63, s1 = (code >> 6) & 7, s2 = (code >> 9) & 7, s = code >> 12;
+      const int m1 = (base + o) * NB3 + s1, m2 = __shfl(q2, o, 64) * NB3 + s2;
+      bool pass = false;
+      double dp = 0.0, dm = 0.0;
+      if (on) {
+        const double w = wq[s], w1 = omega[m1], w2 = omega[m2];
+        double sp, sm;
+        widths(p, vel, m1, m2, sp, sm);
+        // the cut first, then the rates
+        if (fabs((w + w1) - w2) < 2.0 * sp || fabs((w - w1) - w2) < 2.0 * sm) {
+          process_rates(p, w, w1, w2, occ[m1], occ[m2], sp, sm, dp, dm);
+          pass = !(dp == 0.0 && dm == 0.0);
+        }
+      }
+      const unsigned long long mask = __ballot(pass);
+      if (pass) {
+        const int r = n_pass + __popcll(mask & below);
+        pass_q[r] = (uint16_t)code;
+        dp_q[r] = dp;
+        dm_q[r] = dm;
+      }
+      n_pass += __popcll(mask);
+      while (n_pass >= 64 || (last && n_pass > 0)) {
+        project(min(n_pass, 64));
+        // the rest, fewer than 64, moves to the front
+        n_pass = max(n_pass - 64, 0);
+        const uint16_t mc = pass_q[64 + lane];
+        const double mp = dp_q[64 + lane], mm = dm_q[64 + lane];
+        wave_sync();
+        pass_q[lane] = mc;
+        dp_q[lane] = mp;
+        dm_q[lane] = mm;
+      }
+      // what the near queue holds past the first 64 moves to the front
+      wave_sync();
+      const uint16_t mn = near_q[64 + lane];
+      wave_sync();
+      near_q[lane] = mn;
+      n_near = max(n_near - 64, 0);
     };
     for (int s1 = 0; s1 < NB3; ++s1) {
-      const int m1 = q1 * NB3 + s1;
-      const bool ok1 = ok && phys[m1];
-      const double w1 = ok1 ? omega[m1] : 0.0, n1 = ok1 ? occ[m1] : 0.0;
+      float2 f1 = near_tab[(size_t)s1 * nq + (ok ? q1 : 0)];
+      if (!ok) f1.x = __builtin_nanf("");
+#pragma unroll
       for (int s2 = 0; s2 < NB3; ++s2) {
-        const int m2 = q2 * NB3 + s2;
-        const bool ok2 = ok1 && phys[m2];
-        double w2 = 0.0, n2 = 0.0, sp = 1.0, sm = 1.0;
-        if (ok2) {
-          w2 = omega[m2];
-          n2 = occ[m2];
-          widths(p, vel, m1, m2, sp, sm);
-        }
-        for (int s = s_lo; s < s_lo + SPW; ++s) {
-          const int mu = q * NB3 + s;
-          bool pass = false;
-          double dp = 0.0, dm = 0.0;
-          if (ok2 && phys[mu]) {
-            const double w = omega[mu];
-            // the cut first (most candidates fail it), then the rates
-            if (fabs((w + w1) - w2) < 2.0 * sp || fabs((w - w1) - w2) < 2.0 * sm) {
-              process_rates(p, w, w1, w2, n1, n2, sp, sm, dp, dm);
-              pass = !(dp == 0.0 && dm == 0.0);
-            }
-          }
-          const unsigned long long mask = __ballot(pass);
-          if (mask == 0ull) continue;
-          if (qn + __popcll(mask) > kRowQueue) flush();
-          if (pass) {
-            const int r = qn + __popcll(mask & below);
-            rq_code[r] = lane | (s1 << 6) | (s2 << 12) | (s << 18);
-            rq_dp[r] = dp;
-            rq_dm[r] = dm;
-          }
-          qn += __popcll(mask);
+        const float2 f2 = near_tab[(size_t)s2 * nq + q2];
+        const float reach =
+            fmaxf(r_min, hr * (f1.y + f2.y)) + 1e-6f * (w_max + fabsf(f1.x) + fabsf(f2.x)) + 1e-8f;
+        const float cp = f1.x - f2.x, cm = -f1.x - f2.x;  // NaN below nu_min: fails every comparison
+        unsigned hit = 0;
+#pragma unroll
+        for (int k = 0; k < SPW; ++k)
+          hit |= fabsf(ws[k] + cp) < reach || fabsf(ws[k] + cm) < reach ? 1u << k : 0u;
+        if (!__ballot(hit != 0)) continue;
+#pragma unroll 1
+        for (int k = 0; k < SPW; ++k) {
+          const unsigned long long mask = __ballot(hit >> k & 1);
+          if (hit >> k & 1)
+            near_q[n_near + __popcll(mask & below)] =
+                (uint16_t)(lane | s1 << 6 | s2 << 9 | (s_lo + k) << 12);
+          n_near += __popcll(mask);
+          if (n_near >= 64) classify(64, false);
         }
       }
     }
-    flush();
+    classify(n_near, true);
     __syncthreads();
     // three passes; within each the columns of different lanes differ
     if (ok) {
@@ -353,7 +413,8 @@ __global__ __launch_bounds__(64 * kRowWaves) void bte_rows(
     __syncthreads();
   }
   // Gamma0: fixed-order tree over the lanes, then onto the diagonal
-  for (int s = s_lo; s < s_lo + SPW; ++s) red[s][lane] = g0[s];
+#pragma unroll
+  for (int k = 0; k < SPW; ++k) red[s_lo + k][lane] = g0[k];
   __syncthreads();
   for (int w = 32; w > 0; w >>= 1) {
     if (lane < w)
@@ -1140,15 +1201,23 @@ static bool bte_supported(const kaldo_crystal* c) {
   return (size_t)c->bloch.n_blk * 9 * c->nb3 * 16 <= 64 * 1024 && c->n_rep <= 64;
 }
 
-__global__ void bte_prepare(int n_modes, const double* __restrict__ omega, double inv_kt_hbar,
-                            double nu_min, double* __restrict__ occ, uint8_t* __restrict__ phys,
-                            int32_t* __restrict__ flags) {
+// near_tab [branch][q]: the FP32 frequency (NaN below nu_min) and an upper
+// bound of |v| h / sqrt(12), the mode's share of an adaptive width.
+__global__ void bte_prepare(int nq, int nb3, const double* __restrict__ omega,
+                            const double* __restrict__ vel, double inv_kt_hbar, double nu_min,
+                            float hs, double* __restrict__ occ, uint8_t* __restrict__ phys,
+                            float2* __restrict__ near_tab, int32_t* __restrict__ flags) {
+  const int n_modes = nq * nb3;
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n_modes) return;
   const double w = omega[m];
   const bool p = (w / kTwoPi) >= nu_min;
   phys[m] = p;
   occ[m] = p ? 1.0 / expm1(w * inv_kt_hbar) : 0.0;
+  const double* v = vel + 3 * (size_t)m;
+  const float speed = (float)sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+  near_tab[(size_t)(m % nb3) * nq + m / nb3] =
+      make_float2(p ? (float)w : __builtin_nanf(""), speed * hs * 1.000001f);
   if (!(w - w == 0.0)) raise_flag(flags, kFlagNonFinite);
   if (w < 0.0 && (-w / kTwoPi) >= nu_min) raise_flag(flags, kFlagImaginary);
 }
@@ -1198,10 +1267,13 @@ extern "C" int kaldo_scattering_matrix(const kaldo_crystal* c, const int32_t* me
   uint8_t* act = ws + w.off_act;
   int32_t* tr = reinterpret_cast<int32_t*>(ws + w.off_tr);
   double2* phase = reinterpret_cast<double2*>(ws + w.off_phase);
+  // in the place of the solve's right-hand sides (24 bytes a mode)
+  float2* near_tab = reinterpret_cast<float2*>(ws + w.off_rhs);
   double* gmax = reinterpret_cast<double*>(ws + w.off_gmax);
   LwParams p = make_params(c, mesh, temperature, b);
   KALDO_LAUNCH("bte_prepare", bte_prepare, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-               (int)n, omega, kHbar / (kKb * temperature), b->nu_min_thz, occ, phys, c->d_flags);
+               (int)nq, nb3, omega, vel, kHbar / (kKb * temperature), b->nu_min_thz,
+               p.adaptive ? (float)std::sqrt(p.h2 / 12.0) : 0.0f, occ, phys, near_tab, c->d_flags);
   KALDO_LAUNCH("bte_tr_map", bte_tr_map, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
                (int)nq, nb3, mesh[0], mesh[1], mesh[2], evec, tr);
   const long nph = nq * std::max(1, p.n_d);
@@ -1215,12 +1287,12 @@ extern "C" int kaldo_scattering_matrix(const kaldo_crystal* c, const int32_t* me
   const Fc3Bloch& bl = c->bloch;
   if (nb3 == 6)
     KALDO_LAUNCH("bte_rows", bte_rows<6>, dim3((unsigned)nq), dim3(64 * kRowWaves), lds, st, p, c->n_rep,
-                 c->d_rep, omega, vel, occ, phys, evec, phase, bl.n_blk, bl.e_blk, bl.e_bg,
+                 c->d_rep, omega, vel, occ, phys, evec, near_tab, phase, bl.n_blk, bl.e_blk, bl.e_bg,
                  bl.blk_d, bl.pair_ptr, bl.t_ptr, bl.t_i, bl.t_l2, bl.t_coef, tr, pref, matrix,
                  gamma0);
   else
     KALDO_LAUNCH("bte_rows", bte_rows<3>, dim3((unsigned)nq), dim3(64 * kRowWaves), lds, st, p, c->n_rep,
-                 c->d_rep, omega, vel, occ, phys, evec, phase, bl.n_blk, bl.e_blk, bl.e_bg,
+                 c->d_rep, omega, vel, occ, phys, evec, near_tab, phase, bl.n_blk, bl.e_blk, bl.e_bg,
                  bl.blk_d, bl.pair_ptr, bl.t_ptr, bl.t_i, bl.t_l2, bl.t_coef, tr, pref, matrix,
                  gamma0);
   KALDO_LAUNCH("bte_gmax", bte_gmax, dim3(1), dim3(1024), 0, st, n, gamma0, gmax);

@@ -40,7 +40,8 @@ __global__ void lw_prepare(int n_modes, int nb3, const double* __restrict__ omeg
                            const double* __restrict__ vel, const double* __restrict__ evec,
                            double inv_kt_hbar, double nu_min, double* __restrict__ occ,
                            uint8_t* __restrict__ phys, uint8_t* __restrict__ sel,
-                           float4* __restrict__ modef, float* __restrict__ freq, int sel_all,
+                           float4* __restrict__ modef, float* __restrict__ freq,
+                           double2* __restrict__ mrec, int sel_all,
                            int32_t* __restrict__ flags) {
   int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n_modes) return;
@@ -55,6 +56,11 @@ __global__ void lw_prepare(int n_modes, int nb3, const double* __restrict__ omeg
   const float wf = p ? (float)w : __builtin_nanf("");
   modef[at] = make_float4((float)v0, (float)v1, (float)v2, wf);
   if (freq) freq[at] = wf;
+  if (mrec) {
+    mrec[3 * (size_t)m] = make_double2(w, occ[m]);
+    mrec[3 * (size_t)m + 1] = make_double2(v0, v1);
+    mrec[3 * (size_t)m + 2] = make_double2(v2, 0.0);
+  }
   // x - x is 0 for every finite x and NaN otherwise
   double chk = (w - w) + (v0 - v0) + (v1 - v1) + (v2 - v2);
   const double* col = evec + ((size_t)q * nb3 * nb3 + s) * 2;
@@ -258,7 +264,7 @@ static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
 struct CrystalWs {
   CrystalPath path;
   size_t off_occ, off_phys, off_sel, off_eta, off_at, off_partial, off_phase, off_modef, off_qlist,
-      off_fpart, off_rec, off_freq, off_window, off_bsum, total;
+      off_fpart, off_rec, off_mrec, off_freq, off_window, off_bsum, total;
 };
 
 static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, CrystalPath path) {
@@ -281,9 +287,15 @@ static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, Cryst
     w.off_eta = take(cs * nq * nb3 * nb3);
     w.off_at = take(cs * nq * (size_t)c->bloch.n_e * nb3);
     w.off_partial = take(sizeof(double) * nq * nblk * nb3);
+  } else if (w.path == CrystalPath::Fused && !fused_boxes(c, prec)) {
+    w.off_eta = take(cs * nq * nb3 * nb3);
+    w.off_phase = take(cs * nq * (size_t)std::max(1, c->bloch.n_d));
+    w.off_qlist = take(sizeof(int32_t) * (2 * nq + 1));
+    w.off_fpart = take(sizeof(double) * nq * kFusedMaxChunks * nb3);
+    w.off_mrec = take(sizeof(double2) * 3 * nq * nb3);
   } else if (w.path == CrystalPath::Fused) {
     w.off_rec = take(fused_record_bytes(nb3, cs) * nq * nb3);
-    w.off_phase = take(fused_phase_bytes(nb3, c->bloch.n_f, cs) * nq);
+    w.off_phase = take(kFusedPhaseBytes * nq);
     w.off_qlist = take(sizeof(int32_t) * (2 * nq + 1));
     // per work item the partial sums, or the cache's counts (four waves, int32) and
     // the 960 block totals of its row pointers
@@ -326,9 +338,11 @@ static int run_crystal(const kaldo_crystal* c, const int32_t* mesh, const double
   double* partial = reinterpret_cast<double*>(ws + w.off_partial);
   float4* modef = reinterpret_cast<float4*>(ws + w.off_modef);
   const double inv_kt_hbar = kHbar / (kKb * T_k);
+  const bool boxes = w.path == CrystalPath::Fused && fused_boxes(c, prec);
+  double2* mrec = w.path == CrystalPath::Fused && !boxes ? reinterpret_cast<double2*>(ws + w.off_mrec) : nullptr;
   KALDO_LAUNCH("lw_prepare", lw_prepare, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes,
                nb3, omega, vel, evec, inv_kt_hbar, b->nu_min_thz, occ, phys, sel, modef,
-               w.path == CrystalPath::Fused ? reinterpret_cast<float*>(ws + w.off_freq) : nullptr,
+               boxes ? reinterpret_cast<float*>(ws + w.off_freq) : nullptr, mrec,
                subset ? 0 : 1, c->d_flags);
   if (subset && n_subset > 0)
     KALDO_LAUNCH("lw_select", lw_select, dim3((n_subset + 255) / 256), dim3(256), 0, st, subset,
@@ -340,6 +354,12 @@ static int run_crystal(const kaldo_crystal* c, const int32_t* mesh, const double
                        kPrefactor / (double)nq, gamma, st);
   }
   if (path == CrystalPath::Fused) {
+    if (!boxes)
+      return launch_rounds<T>(c, p, omega, vel, modef, occ, mrec, phys, sel, evec, eta,
+                              reinterpret_cast<C*>(ws + w.off_phase),
+                              reinterpret_cast<int32_t*>(ws + w.off_qlist),
+                              reinterpret_cast<double*>(ws + w.off_fpart), subset ? n_subset : 0,
+                              kPrefactor / (double)nq, gamma, st);
     return launch_fused<T>(c, p, omega, occ, vel, modef, phys, sel, evec, fused_ws(ws, w),
                            subset ? n_subset : 0, kPrefactor / (double)nq, gamma, st);
   }
@@ -473,10 +493,12 @@ extern "C" int kaldo_tcache_build(const kaldo_crystal* c, const int32_t* mesh, c
   uint8_t* phys = ws + w.off_phys;
   uint8_t* sel = ws + w.off_sel;
   float4* modef = reinterpret_cast<float4*>(ws + w.off_modef);
+  const bool boxes = fused_boxes(c, precision);
+  double2* mrec = boxes ? nullptr : reinterpret_cast<double2*>(ws + w.off_mrec);
   // the populations lw_prepare writes are not used: any temperature will do
   KALDO_LAUNCH("lw_prepare", lw_prepare, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes, nb3,
                omega, vel, evec, kHbar / (kKb * 300.0), b->nu_min_thz, occ, phys, sel, modef,
-               reinterpret_cast<float*>(ws + w.off_freq), modes_subset ? 0 : 1, c->d_flags);
+               boxes ? reinterpret_cast<float*>(ws + w.off_freq) : nullptr, mrec, modes_subset ? 0 : 1, c->d_flags);
   if (modes_subset)
     KALDO_LAUNCH("lw_select", lw_select, dim3((n_subset + 255) / 256), dim3(256), 0, st,
                  modes_subset, (long)n_subset, n_modes, sel, c->d_flags);
@@ -486,7 +508,18 @@ extern "C" int kaldo_tcache_build(const kaldo_crystal* c, const int32_t* mesh, c
            reinterpret_cast<long long*>(ws + w.off_bsum), reinterpret_cast<long long*>(row_ptr),
            reinterpret_cast<uint2*>(pairs), reinterpret_cast<double2*>(factors), c->d_flags};
   const int64_t ns = modes_subset ? n_subset : 0;
+  const RoundsOut ro{reinterpret_cast<long long*>(ws + w.off_fpart), reinterpret_cast<long long*>(row_ptr),
+                     reinterpret_cast<uint2*>(pairs), reinterpret_cast<double2*>(factors), c->d_flags};
+  int32_t* qlist = reinterpret_cast<int32_t*>(ws + w.off_qlist);
   auto pass = [&](int mode) {
+    if (!boxes && precision == KALDO_FP64)
+      return launch_rounds_cache<double>(c, p, mode, omega, vel, modef, mrec, phys, sel, evec,
+                                         reinterpret_cast<double2*>(ws + w.off_eta),
+                                         reinterpret_cast<double2*>(ws + w.off_phase), qlist, ns, ro, st);
+    if (!boxes)
+      return launch_rounds_cache<float>(c, p, mode, omega, vel, modef, mrec, phys, sel, evec,
+                                        reinterpret_cast<float2*>(ws + w.off_eta),
+                                        reinterpret_cast<float2*>(ws + w.off_phase), qlist, ns, ro, st);
     if (precision == KALDO_FP64)
       return launch_fused_cache<double>(c, p, mode, omega, occ, vel, modef, phys, sel, evec, fws, ns, tc, st);
     return launch_fused_cache<float>(c, p, mode, omega, occ, vel, modef, phys, sel, evec, fws, ns, tc, st);

@@ -484,6 +484,7 @@ __host__ __device__ inline int fused_chunks(int n_live, int target) {
   return c < 1 ? 1 : (c > kFusedMaxChunks ? kFusedMaxChunks : c);
 }
 bool fused_supported(const kaldo_crystal* c, int prec);
+size_t fused_lds_bytes(const kaldo_crystal* c, int prec);  // the A~ tables of all branches
 bool fused_record_supported(const kaldo_crystal* c, int prec);  // the cache's record pass
 
 // What one launch of the fused kernel produces: Gamma (the linewidth sums),
@@ -501,7 +502,8 @@ struct TcOut {
 };
 size_t fused_max_items(const kaldo_crystal* c, long nq);  // (q, chunk) work items of a request
 size_t fused_record_bytes(int nb3, size_t cs);            // of a mode's record, cs = bytes of a complex
-size_t fused_phase_bytes(int nb3, int n_f, size_t cs);    // of a mesh point's row of phases
+constexpr size_t kFusedPhaseBytes = 64;                   // of a mesh point's row of phases
+bool fused_boxes(const kaldo_crystal* c, int prec);       // whether lw_fused.hip serves the fused path's requests
 struct FusedWs {
   unsigned char *rec, *phase_tab;  // mode records, phases
   const float* freq;               // FP32 frequencies [branch][q], NaN below the floor
@@ -519,6 +521,27 @@ int launch_fused(const kaldo_crystal* c, const LwParams& p, const double* omega,
                  const double* vel, const float4* modef, const uint8_t* phys, const uint8_t* sel,
                  const double* evec, const FusedWs& ws, int64_t n_subset, double scale, double* gamma,
                  hipStream_t st);
+
+// The other fused kernel (lw_rounds.hip).
+struct RoundsOut {
+  long long* count;    // [n_live][kFusedMaxChunks][nb3], written by count, read by record
+  long long* row_ptr;  // [n_modes + 1] row offsets per mode, written by count
+  uint2* pairs;        // (m1, m2) of each entry, written by record
+  double2* factors;    // (c, d) of each entry, written by record
+  int32_t* flags;      // the handle's status word
+};
+template <typename T>
+int launch_rounds_cache(const kaldo_crystal* c, const LwParams& p, int mode, const double* omega,
+                        const double* vel, const float4* modef, const double2* mrec,
+                        const uint8_t* phys, const uint8_t* sel, const double* evec,
+                        typename Cx<T>::type* eta, typename Cx<T>::type* phase_tab, int32_t* qlist,
+                        int64_t n_subset, RoundsOut tc, hipStream_t st);
+template <typename T>
+int launch_rounds(const kaldo_crystal* c, const LwParams& p, const double* omega, const double* vel,
+                  const float4* modef, const double* occ, const double2* mrec, const uint8_t* phys,
+                  const uint8_t* sel, const double* evec, typename Cx<T>::type* eta,
+                  typename Cx<T>::type* phase_tab, int32_t* qlist, double* part, int64_t n_subset,
+                  double scale, double* gamma, hipStream_t st);
 
 // Dense MFMA crystal kernel (lw_mfma.hip).
 bool mfma_supported(const kaldo_crystal* c);    // FP32 and BF16x3 forms

@@ -1,5 +1,5 @@
-// Fused crystal linewidth kernel: one workgroup per (q-point, share of its
-// partners).
+// Fused crystal linewidth kernel of the small cells (fused_boxes; the others'
+// is lw_rounds.hip): one workgroup per (q-point, share of its partners).
 //
 // Paper: Eq. phi3_proj (projection on three Bloch eigenvectors), Eq. gamma
 // with its Delta terms, Eq. broadening (only pairs with |x| < 2 sigma are
@@ -27,8 +27,7 @@
 //     projected, one per lane: V = sum_blocks e^{-i q1.R_d} sum_{beta,gamma}
 //     A~[blk][beta gamma][s] eta_{3jb+beta}(q1,s') eta_{3kb+gamma}(q2,s''),
 //     in the contraction type T, and w |V|^2 (FP64) added to the lane's
-//     per-branch sum.  Cells of one and two atoms pull a batch's records and
-//     phases through LDS (pull_rows).
+//     per-branch sum.  A batch's records and phases come through LDS (pull_rows).
 //  4. A fixed butterfly per wave and the waves in order give this work item's
 //     partial sum; lw_fused_finish adds the chunks of a q in order.
 // Every order above depends on the inputs only, so results are bitwise
@@ -119,12 +118,7 @@ __host__ __device__ constexpr int record_stride(int used) { return used > 64 && 
 size_t fused_record_bytes(int nb3, size_t cs) {
   return record_stride((int)((48 + (nb3 - 1) * cs + 15) / 16 * 16));
 }
-// Row of a q-point's phases e^{-i q.R_f}, one per +-d (n_f complex T), padded
-// to a size that a kernel may stage where records are staged.
-size_t fused_phase_bytes(int nb3, int n_f, size_t cs) {
-  const size_t need = n_f * cs;
-  return nb3 > 6 || need > 64 ? need : 64;
-}
+// Row of a q-point's phases e^{-i q.R_f}: one per +-d, n_f complex T in kFusedPhaseBytes.
 
 // Everything the sweep reads beside the FC3 tables, one launch, a job a range
 // of blocks (first[k] .. first[k + 1]):
@@ -287,14 +281,14 @@ __device__ __forceinline__ const unsigned char* pulled(const unsigned char* st, 
 // temperature-independent factors at a fixed place of its mode's row: the row
 // start, plus the counts of the earlier waves of its q, plus its rank among
 // the wave's entries of that branch in queue order.
-template <int NB, typename T, int MODE, int STAGE>
+template <int NB, typename T, int MODE>
 __global__ __launch_bounds__(kFusedThreads)
 __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
     LwParams p, Boxes box, int n_rep, const int32_t* __restrict__ rep,
     const double* __restrict__ omega, const float4* __restrict__ modef, const float* __restrict__ freq,
     const uint8_t* __restrict__ phys, const uint8_t* __restrict__ sel,
     const double* __restrict__ evec, const unsigned char* __restrict__ rec,
-    const unsigned char* __restrict__ phase_tab, int phase_bytes, const float4* __restrict__ window,
+    const unsigned char* __restrict__ phase_tab, const float4* __restrict__ window,
     const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_i,
     const int32_t* __restrict__ t_l2, const double* __restrict__ t_coef,
     const int32_t* __restrict__ e_blk, const int32_t* __restrict__ e_bg,
@@ -306,14 +300,14 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
   constexpr bool kRecord = MODE == kModeRecord;
   using C = typename Cx<T>::type;
   extern __shared__ double2 smem[];
-  // STAGE: a batch's records (1), its rows of phases too (2) are pulled through
-  // LDS, one buffer a wave; 0: each lane fetches its own
+  // a batch's records, then its rows of phases, are pulled through LDS, one
+  // buffer a wave
   constexpr int RB = record_used<NB, T>(), kStride = record_stride(RB);
   constexpr int kPullBytes = MODE == kModeCount ? 48 : RB;  // >= 64 where phases are staged
   unsigned char* st = reinterpret_cast<unsigned char*>(smem) +
                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (64 * kPullBytes);
   C* at = reinterpret_cast<C*>(reinterpret_cast<unsigned char*>(smem) +
-                               (STAGE ? kFusedWaves * 64 * kPullBytes : 0));  // [n_blk][9][NB3]
+                               kFusedWaves * 64 * kPullBytes);  // [n_blk][9][NB3]
   __shared__ uint32_t wq_q[kFusedWaves][kQueue];     // q1 | q2 << 16
   __shared__ uint16_t wq_code[kFusedWaves][kQueue];  // s | s' << 4 | s'' << 8 | both orderings << 12
   __shared__ uint32_t cq_q[kFusedWaves][kPairs];
@@ -396,7 +390,7 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
     __syncthreads();
   }
 
-  constexpr int kPhaseCh = 4;
+  constexpr int kPhaseCh = kFusedPhaseBytes / 16;
   double acc[NB3];
   int run[NB3];  // cache passes: entries of each branch so far (wave-uniform)
 #pragma unroll
@@ -443,20 +437,12 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
       int own_lane = lane;
       asm volatile("" : "+v"(own_lane));  // its addresses are not kept from batch to batch
       auto own = [&](int byte) { return pulled<CH>(st, own_lane, byte); };
-      const unsigned char *r1 = rec + (size_t)m1 * kStride, *r2 = rec + (size_t)m2 * kStride;
-      auto far1 = [&](int byte) { return r1 + byte; };
-      auto far2 = [&](int byte) { return r2 + byte; };
-      if constexpr (STAGE) {
-        pull_rows<CH>(rec, kStride, m1, st, lane);
-        tail(own, ra1, rb1, rc1);
-        if constexpr (MODE != kModeCount) vector(own, rc1.y, x);
-        lds_wave_sync();
-        pull_rows<CH>(rec, kStride, m2, st, lane);
-        tail(own, ra2, rb2, rc2);
-      } else {
-        tail(far1, ra1, rb1, rc1);
-        tail(far2, ra2, rb2, rc2);
-      }
+      pull_rows<CH>(rec, kStride, m1, st, lane);
+      tail(own, ra1, rb1, rc1);
+      if constexpr (MODE != kModeCount) vector(own, rc1.y, x);
+      lds_wave_sync();
+      pull_rows<CH>(rec, kStride, m2, st, lane);
+      tail(own, ra2, rb2, rc2);
       const double w1 = ra1.x, w2 = ra2.x, w = wq64[s];
       const double v1[3] = {rb1.x, rb1.y, rc1.x}, v2[3] = {rb2.x, rb2.y, rc2.x};
       // cache passes: the exact decision, and the entry's place in its row
@@ -478,7 +464,7 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
         }
       }
       if constexpr (MODE == kModeCount) {
-        if constexpr (STAGE) lds_wave_sync();
+        lds_wave_sync();
         return;
       }
       // the weight before the second eigenvector and the phases arrive: what
@@ -502,25 +488,14 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
           wt = pair_weight_both(p, dbl, w, w1, w2, ra1.y, ra2.y, sp, sm);
         }
       }
-      if constexpr (STAGE) {
-        asm volatile("" : "+v"(own_lane) : "v"(wt));  // after the weight
-        vector(own, rc2.y, y);
-        lds_wave_sync();
-        if constexpr (STAGE == 2) pull_rows<kPhaseCh>(phase_tab, 16 * kPhaseCh, q1, st, lane);
-      } else {
-        vector(far1, rc1.y, x);
-        vector(far2, rc2.y, y);
-      }
+      asm volatile("" : "+v"(own_lane) : "v"(wt));  // after the weight
+      vector(own, rc2.y, y);
+      lds_wave_sync();
+      pull_rows<kPhaseCh>(phase_tab, 16 * kPhaseCh, q1, st, lane);
       if (pass) {
-      const C* ph = reinterpret_cast<const C*>(phase_tab + (size_t)q1 * phase_bytes);
       auto phase = [&](int blk) {
         const int f = blk_f[blk];
-        const int byte = (f >> 1) * (int)sizeof(C);
-        C v;
-        if constexpr (STAGE == 2)
-          v = *reinterpret_cast<const C*>(pulled<kPhaseCh>(st, own_lane, byte));
-        else
-          v = ph[f >> 1];
+        C v = *reinterpret_cast<const C*>(pulled<kPhaseCh>(st, own_lane, (f >> 1) * (int)sizeof(C)));
         if (f & 1) v.y = -v.y;
         return v;
       };
@@ -531,25 +506,16 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
       // costs a multiply, a fused one and an add per component), and no
       // x (x) y table (nine complex values a block would have to keep or
       // recompute)
-      // One block's term f_blk x_jb^T A~_blk y_kb into (vr, vi).  With phases
-      // from memory the FP64 Gamma pass loads the three values of a row of
-      // the block together and fetches each block's phase one block ahead, so
-      // that the latencies fall under arithmetic; the other forms have no
-      // registers left for either.
-      constexpr bool kAhead = sizeof(T) == 8 && MODE == kModeGamma && STAGE == 0;
+      // One block's term f_blk x_jb^T A~_blk y_kb into (vr, vi).
       auto block_term = [&](const C* ab, const C f, int jb, int kb) {
         T ur = 0, ui = 0;
 #pragma unroll
         for (int be = 0; be < 3; ++be) {
           C a[3];
-          if constexpr (kAhead) {
-#pragma unroll
-            for (int ga = 0; ga < 3; ++ga) a[ga] = ab[(be * 3 + ga) * NB3];
-          }
           T tr = 0, ti = 0;
 #pragma unroll
           for (int ga = 0; ga < 3; ++ga) {
-            if constexpr (!kAhead) a[ga] = ab[(be * 3 + ga) * NB3];
+            a[ga] = ab[(be * 3 + ga) * NB3];
             const C v = y[3 * kb + ga];
             const bool real = sizeof(T) == 8 && 3 * kb + ga == 0;  // a turned eigenvector's first component
             tr = fma(a[ga].x, v.x, tr);
@@ -578,18 +544,8 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
 #pragma unroll
         for (int kb = 0; kb < NB; ++kb) {
           const int b_lo = pair_ptr[jb * NB + kb], b_hi = pair_ptr[jb * NB + kb + 1];
-          if constexpr (kAhead) {
-            C f_next = Cx<T>::make((T)0, (T)0);
-            if (b_lo < b_hi) f_next = phase(b_lo);
-            for (int blk = b_lo; blk < b_hi; ++blk) {
-              const C f = f_next;
-              if (blk + 1 < b_hi) f_next = phase(blk + 1);
-              block_term(at + (size_t)blk * 9 * NB3 + s, f, jb, kb);
-            }
-          } else {
-            for (int blk = b_lo; blk < b_hi; ++blk)
-              block_term(at + (size_t)blk * 9 * NB3 + s, phase(blk), jb, kb);
-          }
+          for (int blk = b_lo; blk < b_hi; ++blk)
+            block_term(at + (size_t)blk * 9 * NB3 + s, phase(blk), jb, kb);
         }
       }
       const double vv = (double)vr * (double)vr + (double)vi * (double)vi;
@@ -609,7 +565,7 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
         for (int k = 0; k < NB3; ++k) acc[k] += (k == s) ? c : 0.0;
       }
       }
-      if constexpr (STAGE) lds_wave_sync();  // the buffer is free again
+      lds_wave_sync();  // the buffer is free again
     }
   };
 
@@ -864,6 +820,11 @@ size_t fused_lds_bytes(const kaldo_crystal* c, int prec) {
 static size_t fused_static_lds(bool record) { return 27968 + (record ? 8192 : 0); }
 constexpr size_t kFusedOwnLds = 11264;
 
+// The buffers of the batches' records (and phases, which take no more).
+static size_t fused_staged(int nb3, size_t cs) {
+  return (size_t)kFusedWaves * 64 * ((48 + (nb3 - 1) * cs + 15) / 16 * 16);
+}
+
 static bool fused_fits(const kaldo_crystal* c, int prec, bool record) {
   if (c->nb < 1 || c->nb > 5 || c->n_rep > 64) return false;
   int dev = 0, lds_max = 0;
@@ -904,6 +865,20 @@ size_t fused_max_items(const kaldo_crystal* c, long nq) {
   return (size_t)std::min<long>(kFusedMaxChunks * nq, 2l * c->nb3 * kFusedItems + nq);
 }
 
+// Cells of one or two atoms with few phases (nearest-neighbour Phi3: diamond has
+// four), whose sweep costs as much as their projections, where the batches'
+// buffers fit beside the tables; the others' projections outweigh it and go
+// in rounds (lw_rounds.hip has both sides).
+bool fused_boxes(const kaldo_crystal* c, int prec) {
+  const size_t cs = prec == KALDO_FP64 ? 16 : 8;
+  int dev = 0, lds_max = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+    return false;
+  return c->nb <= 2 && c->bloch.n_f * 16 <= (int)kFusedPhaseBytes &&
+         fused_lds_bytes(c, prec) + fused_staged(c->nb3, cs) + kFusedOwnLds <= (size_t)lds_max;
+}
+
 // The fused launch of one mode: tables, live list, chunking and the kernel,
 // then what the mode needs after it (the Gamma finish, or the cache's row
 // pointers).  Count and record passes of one request see the same live list
@@ -923,7 +898,6 @@ static int launch_fused_impl(const kaldo_crystal* c, const LwParams& p, const do
   const Boxes box = choose_boxes(p.N);
   const float hs = p.adaptive ? (float)std::sqrt(p.h2 / 12.0) : 0.0f;
   const int rb = (int)fused_record_bytes(c->nb3, sizeof(C));
-  const int phase_bytes = (int)fused_phase_bytes(c->nb3, c->bloch.n_f, sizeof(C));
   auto blocks = [](long n) { return (unsigned)((n + 255) / 256); };
   TableJobs jobs{};
   jobs.first[1] = blocks((long)n_modes * c->nb3);
@@ -931,7 +905,7 @@ static int launch_fused_impl(const kaldo_crystal* c, const LwParams& p, const do
   jobs.first[3] = jobs.first[2] + blocks(4l * n_modes);
   jobs.first[4] = jobs.first[3] + blocks(nq);
   KALDO_LAUNCH("lw_tables", lw_tables<T>, dim3(jobs.first[4]), dim3(256), 0, st, jobs, p, box, hs, rb,
-               phase_bytes, n_subset > 0, evec, omega, occ, vel, modef, phys, sel, c->bloch.fvec, c->bloch.n_f, ws.rec, ws.phase_tab, ws.window,
+               (int)kFusedPhaseBytes, n_subset > 0, evec, omega, occ, vel, modef, phys, sel, c->bloch.fvec, c->bloch.n_f, ws.rec, ws.phase_tab, ws.window,
                live_list, idx_of_q, n_live);
   if (n_subset > 0)
     KALDO_LAUNCH("lw_live_q", lw_live_q<true>, dim3(1), dim3(1024), 0, st, nq, c->nb3, phys, sel, live_list,
@@ -941,41 +915,17 @@ static int launch_fused_impl(const kaldo_crystal* c, const LwParams& p, const do
   const unsigned grid = (unsigned)fused_upper(nq, n_subset) * n_chunk;
   // the count pass builds no A~ tables and stages the records' tails only
   const size_t at = MODE == kModeCount ? 0 : fused_lds_bytes(c, sizeof(T) == 8 ? KALDO_FP64 : KALDO_FP32);
-  const size_t staged = (size_t)kFusedWaves * 64 * (MODE == kModeCount ? 48 : std::max(64, (int)((48 + (c->nb3 - 1) * sizeof(C) + 15) / 16 * 16)));
-  // staging (cells of up to two atoms) where it leaves room for the tables:
-  // 5.6 against 12.3 ms for lanes that fetch their own records (diamond 24^3,
-  // FP64; 0.57 against 0.63, 15^3, FP32).  Larger cells' records leave too few
-  // workgroups a CU.
-  int dev = 0, lds_max = 0;
-  KALDO_HIP(hipGetDevice(&dev));
-  KALDO_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-  const bool stage = c->nb <= 2 && at + staged + kFusedOwnLds <= (size_t)lds_max;
+  const size_t staged = MODE == kModeCount ? (size_t)kFusedWaves * 64 * 48 : fused_staged(c->nb3, sizeof(C));
   auto run = [&](auto kernel) {
-    KALDO_LAUNCH("lw_fused", kernel, dim3(grid), dim3(kFusedThreads), at + (stage ? staged : 0), st, p,
-                 box, c->n_rep, c->d_rep, omega, modef, ws.freq, phys, sel, evec, ws.rec, ws.phase_tab,
-                 phase_bytes, ws.window, b.t_ptr, b.t_i, b.t_l2, b.t_coef, b.e_blk, b.e_bg, b.blk_f,
-                 b.pair_ptr, live_list, n_live, n_chunk, ws.part, tc);
+    KALDO_LAUNCH("lw_fused", kernel, dim3(grid), dim3(kFusedThreads), at + staged, st, p, box, c->n_rep,
+                 c->d_rep, omega, modef, ws.freq, phys, sel, evec, ws.rec, ws.phase_tab, ws.window,
+                 b.t_ptr, b.t_i, b.t_l2, b.t_coef, b.e_blk, b.e_bg, b.blk_f, b.pair_ptr, live_list,
+                 n_live, n_chunk, ws.part, tc);
   };
-  constexpr int kBoth = MODE == kModeCount ? 1 : 2;
-  const bool both = stage && (MODE == kModeCount || phase_bytes == 64);
-  if (c->nb == 1 && both)
-    run(lw_fused<1, T, MODE, kBoth>);
-  else if (c->nb == 1 && stage)
-    run(lw_fused<1, T, MODE, 1>);
-  else if (c->nb == 1)
-    run(lw_fused<1, T, MODE, 0>);
-  else if (c->nb == 2 && both)
-    run(lw_fused<2, T, MODE, kBoth>);
-  else if (c->nb == 2 && stage)
-    run(lw_fused<2, T, MODE, 1>);
+  if (c->nb == 1)
+    run(lw_fused<1, T, MODE>);
   else if (c->nb == 2)
-    run(lw_fused<2, T, MODE, 0>);
-  else if (c->nb == 3)
-    run(lw_fused<3, T, MODE, 0>);
-  else if (c->nb == 4)
-    run(lw_fused<4, T, MODE, 0>);
-  else if (c->nb == 5)
-    run(lw_fused<5, T, MODE, 0>);
+    run(lw_fused<2, T, MODE>);
   else {
     set_error("lw_fused: unsupported basis size");
     return KALDO_EUNSUPPORTED;

@@ -1,4 +1,4 @@
-"""The fused crystal kernel (partners swept by boxes) against the oracle.
+"""The fused crystal kernels (partners swept by boxes, or in rounds) against the oracle.
 
 Tolerance: FP64 sums the same terms on both sides, each |V|^2 from at most a
 thousand products, so 1e-10 of the largest linewidth leaves two orders; FP32
@@ -50,10 +50,24 @@ def wide_cell(n_blk):
                            "fc3_k": np.array(k, np.int32), "fc3_val": rng.uniform(-20.0, 20.0, len(i))})
 
 
-# records and phases staged (diamond), records only (one and two random atoms: more
-# phases), neither (three and four atoms; tables that leave no room); boxes that wrap,
-# that do not divide the mesh, thinner than a box, of one point
-CASES = [("diamond", (5, 4, 7), ADAPT), ("diamond", (1, 1, 5), FIXED), ("diamond", (9, 2, 1), LORENTZ),
+def few_cell():
+    """One atom whose Phi3 has one random entry in each of six blocks, four differences up to
+    sign."""
+    m = models.random_cell(32, 1)
+    rep = [tuple(int(x) for x in r) for r in m.rep]
+    rng = np.random.default_rng(5)
+    at = [rep.index(d) for d in ((0, 0, 0), (1, 0, 0), (-1, 0, 0), (0, 1, 0), (0, -1, 0), (0, 0, 1))]
+    j = [3 * x + rng.integers(3) for x in at]
+    k = [3 * rep.index((0, 0, 0)) + rng.integers(3) for _ in at]
+    return models.Model(**{**m.__dict__, "fc3_i": rng.integers(0, 3, 6).astype(np.int32),
+                           "fc3_j": np.array(j, np.int32), "fc3_k": np.array(k, np.int32),
+                           "fc3_val": rng.uniform(-20.0, 20.0, 6)})
+
+
+# by boxes: diamond and the one-atom cell of four differences; in rounds: the random cells and
+# the one of many blocks; boxes that wrap, that do not divide the mesh, thinner than a box, of
+# one point
+CASES = [("few", (5, 4, 7), ADAPT), ("few", (2, 9, 3), FIXED), ("diamond", (5, 4, 7), ADAPT), ("diamond", (1, 1, 5), FIXED), ("diamond", (9, 2, 1), LORENTZ),
          ("diamond", (6, 6, 6), FIXED), (1, (5, 3, 4), ADAPT), (2, (4, 5, 3), ADAPT), (2, (3, 1, 6), LORENTZ),
          (3, (3, 2, 4), ADAPT), (4, (2, 3, 2), FIXED), ("wide", (3, 3, 2), ADAPT)]
 
@@ -61,7 +75,8 @@ CASES = [("diamond", (5, 4, 7), ADAPT), ("diamond", (1, 1, 5), FIXED), ("diamond
 @pytest.mark.parametrize("cell,mesh,b", CASES)
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_fused_matches_oracle(cell, mesh, b, prec, monkeypatch):
-    m = (models.diamond() if cell == "diamond" else wide_cell(145) if cell == "wide"
+    m = (models.diamond() if cell == "diamond" else few_cell() if cell == "few" else
+         wide_cell(145) if cell == "wide"
          else models.random_cell(40 + cell, cell, cutoff=2.9 if cell == 4 else 3.6))
     monkeypatch.setenv("KALDO_CRYSTAL_PATH", "fused")
     om, ev, ve = oph.phonons(m, mesh)

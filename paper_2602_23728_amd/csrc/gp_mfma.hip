@@ -52,8 +52,12 @@ __global__ void gm_prep_et(int n, int np, const double* __restrict__ E, T* __res
   if (!(x - x == 0.0)) raise_flag(flags, kFlagNonFinite);
   if (et) et[idx] = (T)x;
   if (eth) {
+    // the high part rounds the FP32 value, not E's: the compiler otherwise
+    // merges the two conversions into one from FP64
+    float v = (float)x;
+    asm("" : "+v"(v));
     __bf16 h, l;
-    split_bf16((float)x, h, l);
+    split_bf16(v, h, l);
     eth[idx] = h;
     etl[idx] = l;
   }

@@ -228,12 +228,13 @@ __global__ void lw_finish(int nq, int nb3, int nblk, double scale, const double*
 //
 // In FP64 the dense kernel serves whatever the fused one cannot hold (its
 // tables of all branches must fit the LDS), cells of 12 branches and more, and
-// those of 9 on meshes of up to 512 points.  Random cells, 4^3 / 9^3 mesh,
-// fused (generic where it does not fit) against dense, ms: 2 atoms 0.16 / 1.13
-// against 0.09 / 3.74, 3 atoms 0.38 / 4.39 against 0.12 / 4.61, 4 atoms
-// 56 / 553 (generic) against 0.14 / 6.8, 5 atoms 117 / 1089 (generic) against
-// 0.23 / 13.8: the pruned kernel's work per q grows with the pairs inside the
-// cut, few of them with few branches, the dense one's with all 16 x 16.
+// those of 9 on meshes of up to 96 points.  Random cells, 4^3 / 9^3 mesh,
+// fused (generic where it does not fit) against dense, ms: 2 atoms 0.16 / 1.09
+// against 0.09 / 3.72, 3 atoms 0.38 / 4.30 against 0.12 / 4.61 (7^3, a narrow
+// fixed width: 0.72 against 1.33), 4 atoms 56 / 553 (generic) against 0.14 /
+// 6.8, 5 atoms 116 / 1090 (generic) against 0.22 / 14.0: the pruned kernel's
+// work per q grows with the pairs inside the cut, few of them with few
+// branches, the dense one's with all 16 x 16.
 enum class CrystalPath { Generic, Fused, Mfma };
 
 static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
@@ -253,7 +254,7 @@ static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
   if (prec == KALDO_FP32 && mfma_supported(c) && (want == "mfma" || (want.empty() && c->nb3 >= 9)))
     return CrystalPath::Mfma;
   const bool fused = fused_supported(c, prec);
-  const bool dense64 = !fused || c->nb3 >= 12 || (c->nb3 >= 9 && nq <= 512);
+  const bool dense64 = !fused || c->nb3 >= 12 || (c->nb3 >= 9 && nq <= 96);
   if (prec == KALDO_FP64 && mfma64_supported(c) && (want == "mfma" || (want.empty() && dense64)))
     return CrystalPath::Mfma;
   return fused ? CrystalPath::Fused : CrystalPath::Generic;

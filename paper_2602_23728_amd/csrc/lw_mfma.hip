@@ -518,8 +518,10 @@ static size_t tile_lds(const kaldo_crystal* c, int group) {
 
 // Branches a workgroup of lw_tiles takes, 0 when the tables of one branch do
 // not fit.  A CU holds one workgroup, which per partner pays a set-up of
-// about half a branch's projection: the group count that minimises rounds of
-// 256 workgroups x (set-up + branches).
+// about half a branch's projection, with pairs of more than four blocks of
+// several (random three atoms on a 7^3 mesh, fixed width, all nine branches
+// against five and four: FP32 803 and 898 us, split 884 and 988): the group
+// count that minimises rounds of 256 workgroups x (set-up + branches).
 template <int FORM>
 static int tile_group(const kaldo_crystal* c, int nq) {
   int dev = 0, lds_max = 0;
@@ -528,10 +530,11 @@ static int tile_group(const kaldo_crystal* c, int nq) {
     return 0;
   int best = 0;
   double cost = 0.0;
+  const double setup = tile_slots(c->bloch.max_pair_blk) == 4 ? 0.5 : 4.0;
   for (int n = 1; n <= c->nb3; ++n) {
     const int g = (c->nb3 + n - 1) / n;
     if (tile_lds<FORM>(c, g) + kTileStatic > (size_t)lds_max) continue;
-    const double t = std::ceil((double)nq * n / 256.0) * (g + 0.5);
+    const double t = std::ceil((double)nq * n / 256.0) * (g + setup);
     if (!best || t < cost) best = g, cost = t;
   }
   return best;

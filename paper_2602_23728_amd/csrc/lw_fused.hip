@@ -234,7 +234,10 @@ __global__ __launch_bounds__(256) void lw_tables(
 // CH instructions, no registers.  Row l lies at st + 16 CH l, its pieces
 // exchanged by pull_swap(l) where rows of a power of two of bytes would put
 // every lane's on the same banks; pulled() gives a byte of the lane's own row.
-// `st` is the wave's own; returns when the rows are there.
+// `st` is the wave's own; returns when the rows are there.  The pieces arrive
+// by the memory pipe, which knows nothing of the LDS reads the wave still has
+// under way (a wavefront fence orders the LDS instructions only): it waits for
+// those of the rows before first.
 template <int CH>
 __device__ __forceinline__ int pull_swap(int row) {
   return CH == 8 ? (row >> 1) & 7 : CH == 4 ? (row >> 2) & 3 : 0;
@@ -242,6 +245,7 @@ __device__ __forceinline__ int pull_swap(int row) {
 template <int CH>
 __device__ __forceinline__ void pull_rows(const unsigned char* tab, int stride, int idx,
                                           unsigned char* st, int lane) {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   auto piece = [&](int k, int row, int byte) {  // row's index from the lane that holds it
     const unsigned off = (unsigned)__builtin_amdgcn_ds_bpermute(row, idx) * stride + byte;
     __builtin_amdgcn_global_load_lds(

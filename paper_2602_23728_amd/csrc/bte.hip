@@ -813,7 +813,7 @@ __global__ __launch_bounds__(256) void lu_left(long n, int nb, int k0, int k, Ma
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     rl[i] = A.rows[min((long)bi * B + pr + 8 * i, n - 1)];
-    ru[i] = A.rows[(long)k0 * B + pr + 8 * i];
+    ru[i] = A.rows[min((long)k0 * B + pr + 8 * i, n - 1)];
   }
   auto fetch = [&](int t) {
     const long c = (long)bj * B + pc;

@@ -39,3 +39,14 @@ def test_asynchronous_lds_loads_wait_for_the_reads_before_them():
             wait = re.search(r"s_waitcnt[^\"]*lgkmcnt\(0\)", b)
             assert wait and wait.start() < at, f"{name}: {m.group(1)}"
     assert found >= 1
+
+
+def test_row_map_reads_stay_within_the_coupled_rows():
+    """The LU's row map holds n entries; a block of 64 rows may end past them, so every read of
+    it is clamped to n - 1."""
+    text = code("bte.hip")
+    lu = text[text.index("lu_panels"):text.index("lu_gemm(")]
+    reads = re.findall(r"A\.rows\[([^\]]*)\]", lu)
+    assert len(reads) >= 3
+    for r in reads:
+        assert re.match(r"min\(.*, n - 1\)$", r), r

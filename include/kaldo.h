@@ -235,7 +235,12 @@ int kaldo_linewidths_noalloc(const kaldo_crystal* c, const int32_t* mesh, const 
 /* Size in bytes of kaldo_linewidths_noalloc's device scratch array. */
 size_t kaldo_linewidths_noalloc_max_bytes(void);
 
-/* Device workspace bytes kaldo_linewidths_gamma needs. */
+/* Device workspace bytes for kaldo_linewidths_gamma.  The call also takes a
+ * smaller workspace, in smaller batches of modes: in FP64 down to what its
+ * generic kernels need (about 8 (3N)^2 64 bytes), in FP32 and BF16X3 by a few
+ * percent.  The linewidths are the same to the bit for every batch; the
+ * generic kernels, which a cell of less than two tiles of 128 modes runs in so
+ * small a workspace, round differently. */
 size_t kaldo_linewidths_gamma_workspace(const kaldo_crystal* c, int32_t precision);
 
 /* kaldo_linewidths_gamma -- linewidths of a Gamma-point solid (N_q = 1, real

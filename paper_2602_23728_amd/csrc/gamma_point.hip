@@ -203,14 +203,18 @@ __global__ void gp_finish(int n, int n_tiles2, const double* __restrict__ partia
   gamma[m] = phys[m] ? kPrefactor * acc : 0.0;
 }
 
+// total: what the workspace query returns; least: what the call asks for.  The
+// matrix-core pipeline takes its modes in smaller batches where less than the
+// total is given (in FP64 down to the generic kernels' size, and these kernels
+// where not even its smallest batch fits).
 struct GammaWs {
-  size_t off_occ, off_phys, off_sel, off_et, off_av, off_w, off_partial, off_rest, total;
+  size_t off_occ, off_phys, off_sel, off_et, off_av, off_w, off_partial, off_rest, least, total;
 };
 
-size_t gm_workspace_bytes(const kaldo_crystal* c, int prec);
+size_t gm_workspace_bytes(const kaldo_crystal* c, int prec, bool least);
 int run_gm(const kaldo_crystal* c, const LwParams& p, const double* omega, const double* evec,
            const double* occ, const uint8_t* phys, const uint8_t* sel, unsigned char* ws,
-           int prec, double* gamma, hipStream_t st);
+           size_t bytes, int prec, double* gamma, hipStream_t st);
 
 bool gm_supported(const kaldo_crystal* c);
 
@@ -240,16 +244,18 @@ static GammaWs gamma_ws(const kaldo_crystal* c, int prec) {
   w.off_av = take(es * (size_t)c->gamma.n_bc * kGpBatch);
   w.off_w = take(es * n * n * kGpBatch);
   w.off_partial = take(8 * n * nt * nt);
-  w.total = o;
-  if (gm_supported(c))
-    w.total = std::max(w.total, w.off_rest + gm_workspace_bytes(c, prec));
+  w.total = w.least = o;
+  if (gm_supported(c)) {
+    w.total = std::max(o, w.off_rest + gm_workspace_bytes(c, prec, false));
+    if (prec != KALDO_FP64) w.least = std::max(o, w.off_rest + gm_workspace_bytes(c, prec, true));
+  }
   return w;
 }
 
 template <typename T>
 static int run_gamma(const kaldo_crystal* c, const double* omega, const double* evec, double Tk,
                      const kaldo_broadening* b, const int32_t* subset, int64_t n_subset,
-                     unsigned char* ws, const GammaWs& g, int prec, double* gamma,
+                     unsigned char* ws, size_t ws_bytes, const GammaWs& g, int prec, double* gamma,
                      hipStream_t st) {
   const int n = c->nb3;
   const int nt = (n + kGpTile - 1) / kGpTile;
@@ -267,8 +273,8 @@ static int run_gamma(const kaldo_crystal* c, const double* omega, const double* 
                  (long)n_subset, n, sel, c->d_flags);
   int32_t mesh1[3] = {1, 1, 1};
   LwParams p = make_params(c, mesh1, Tk, b);
-  if (use_mfma(c, prec))
-    return run_gm(c, p, omega, evec, occ, phys, sel, ws + g.off_rest, prec, gamma, st);
+  if (use_mfma(c, prec) && ws_bytes >= g.off_rest + gm_workspace_bytes(c, prec, true))
+    return run_gm(c, p, omega, evec, occ, phys, sel, ws + g.off_rest, ws_bytes - g.off_rest, prec, gamma, st);
   long nn = (long)n * n;
   KALDO_LAUNCH("gp_round", gp_round<T>, dim3((nn + 255) / 256), dim3(256), 0, st, nn, evec, Et,
                c->d_flags);
@@ -318,13 +324,13 @@ extern "C" int kaldo_linewidths_gamma(const kaldo_crystal* c, const double* omeg
     return KALDO_EUNSUPPORTED;
   }
   GammaWs g = gamma_ws(c, precision);
-  KALDO_REQUIRE(workspace && workspace_bytes >= g.total, "kaldo_linewidths_gamma: workspace too small");
+  KALDO_REQUIRE(workspace && workspace_bytes >= g.least, "kaldo_linewidths_gamma: workspace too small");
   if (modes_subset && n_subset == 0) return KALDO_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   auto* ws = static_cast<unsigned char*>(workspace);
   if (precision == KALDO_FP64)
-    return run_gamma<double>(c, omega, evec, temperature, b, modes_subset, n_subset, ws, g,
-                             precision, gamma, st);
-  return run_gamma<float>(c, omega, evec, temperature, b, modes_subset, n_subset, ws, g, precision,
-                          gamma, st);
+    return run_gamma<double>(c, omega, evec, temperature, b, modes_subset, n_subset, ws,
+                             workspace_bytes, g, precision, gamma, st);
+  return run_gamma<float>(c, omega, evec, temperature, b, modes_subset, n_subset, ws, workspace_bytes,
+                          g, precision, gamma, st);
 }

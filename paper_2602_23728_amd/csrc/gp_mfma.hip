@@ -652,6 +652,15 @@ template <int FORM>
 static int gm_batch(int n) {
   return FORM != kGm64 ? 512 : n <= 4096 ? 256 : 64;
 }
+// Fewest modes per launch a smaller workspace is taken for: batches differ in
+// time only.  FP64 goes down to the SpMM's sixteen, so that a workspace of the
+// generic kernels' size, which is asked for at least, serves every cell it
+// can (one of less than two tiles runs those kernels in it).  The other forms
+// give up sixteen modes for the lists of live blocks.
+template <int FORM>
+static int gm_least_batch(int n) {
+  return FORM != kGm64 ? gm_batch<FORM>(n) - kSpmmModes : kSpmmModes;
+}
 
 // Buffers of one form in the workspace.
 template <int FORM>
@@ -665,8 +674,7 @@ struct GmWs {
   int32_t *live_lists, *live_count;
   unsigned long long* live_mask;
   size_t total;
-  GmWs(const kaldo_crystal* c, unsigned char* base) {
-    const size_t batch = gm_batch<FORM>(c->nb3);
+  GmWs(const kaldo_crystal* c, unsigned char* base, size_t batch) {
     const size_t n = c->nb3, np = (n + kMT - 1) / kMT * kMT;
     const size_t n_tri = gm_tile_count((int)(np / kMT), c->bloch.sym_jk != 0);
     size_t o = 0;
@@ -699,23 +707,29 @@ struct GmWs {
   }
 };
 
-size_t gm_workspace_bytes(const kaldo_crystal* c, int prec) {
-  if (prec == KALDO_FP64) return GmWs<kGm64>(c, nullptr).total;
-  return prec == KALDO_BF16X3 ? GmWs<kGmSplit>(c, nullptr).total : GmWs<kGm32>(c, nullptr).total;
+template <int FORM>
+static size_t gm_bytes(const kaldo_crystal* c, bool least) {
+  return GmWs<FORM>(c, nullptr, least ? gm_least_batch<FORM>(c->nb3) : gm_batch<FORM>(c->nb3)).total;
+}
+size_t gm_workspace_bytes(const kaldo_crystal* c, int prec, bool least) {
+  if (prec == KALDO_FP64) return gm_bytes<kGm64>(c, least);
+  return prec == KALDO_BF16X3 ? gm_bytes<kGmSplit>(c, least) : gm_bytes<kGm32>(c, least);
 }
 
 template <int FORM>
 static int run_gm_form(const char* gemm_name, const kaldo_crystal* c, const LwParams& p,
                        const double* omega, const double* evec, const double* occ,
-                       const uint8_t* phys, const uint8_t* sel, unsigned char* ws, double* gamma,
-                       hipStream_t st) {
+                       const uint8_t* phys, const uint8_t* sel, unsigned char* ws, size_t bytes,
+                       double* gamma, hipStream_t st) {
   using T = typename GmType<FORM>::T;
-  const int batch = gm_batch<FORM>(c->nb3);
+  // the largest batch the workspace holds (at least the least: the caller has checked)
+  int batch = gm_batch<FORM>(c->nb3);
+  while (batch > gm_least_batch<FORM>(c->nb3) && GmWs<FORM>(c, nullptr, batch).total > bytes) batch -= kSpmmModes;
   int32_t* flags = c->d_flags;
   const int n = c->nb3;
   const int np = (n + kMT - 1) / kMT * kMT;
   const int nt = np / kMT, n_tri = gm_tile_count(nt, p.half != 0);
-  const GmWs<FORM> b(c, ws);
+  const GmWs<FORM> b(c, ws, batch);
   const long n_part = (long)n * n_tri;
   KALDO_LAUNCH("gm_zero", gm_zero, dim3((unsigned)((n_part + 255) / 256)), dim3(256), 0, st, n_part,
                b.partial);
@@ -765,12 +779,12 @@ static int run_gm_form(const char* gemm_name, const kaldo_crystal* c, const LwPa
 
 int run_gm(const kaldo_crystal* c, const LwParams& p, const double* omega, const double* evec,
            const double* occ, const uint8_t* phys, const uint8_t* sel, unsigned char* ws,
-           int prec, double* gamma, hipStream_t st) {
+           size_t bytes, int prec, double* gamma, hipStream_t st) {
   if (prec == KALDO_FP64)
-    return run_gm_form<kGm64>("gm_gemm_fp64", c, p, omega, evec, occ, phys, sel, ws, gamma, st);
+    return run_gm_form<kGm64>("gm_gemm_fp64", c, p, omega, evec, occ, phys, sel, ws, bytes, gamma, st);
   if (prec == KALDO_BF16X3)
-    return run_gm_form<kGmSplit>("gm_gemm_bf16x3", c, p, omega, evec, occ, phys, sel, ws, gamma, st);
-  return run_gm_form<kGm32>("gm_gemm_fp32", c, p, omega, evec, occ, phys, sel, ws, gamma, st);
+    return run_gm_form<kGmSplit>("gm_gemm_bf16x3", c, p, omega, evec, occ, phys, sel, ws, bytes, gamma, st);
+  return run_gm_form<kGm32>("gm_gemm_fp32", c, p, omega, evec, occ, phys, sel, ws, bytes, gamma, st);
 }
 
 }  // namespace kaldo

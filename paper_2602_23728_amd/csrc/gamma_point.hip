@@ -7,8 +7,8 @@
 // Eq. broadening with the 2-sigma cut, as on the crystal path with N_q = 1.
 //
 // The matrix-core pipeline of gp_mfma.hip serves every precision whose SpMM
-// rows fit the LDS; otherwise the generic kernels below do (FP32 and FP64), per
-// batch of modes:
+// rows fit the LDS; otherwise, and in FP64 for cells of at most 64 branches, the
+// generic kernels below do (FP32 and FP64), per batch of modes:
 //   gp_avals   A_mu values on the fixed (b, c) pattern        (sparse x E)
 //   gp_spmm    W_mu = A_mu E, row b of W from the ~15 entries of row b of A_mu
 //   gp_gemm    V tile = E^T W_mu on a 64 x 64 (mu', mu'') tile, K = 3N, and the
@@ -218,8 +218,13 @@ int run_gm(const kaldo_crystal* c, const LwParams& p, const double* omega, const
 
 bool gm_supported(const kaldo_crystal* c);
 
+// The matrix-core pipeline wherever its rows fit.  In FP64 a cell of at most one
+// tile of the generic kernels stays with them: its time is launches and one
+// tile's latency, and theirs are fewer and half as wide (random clusters,
+// generic against matrix cores, us: 6 branches 29 / 41, 15: 29 / 66, 48: 48 /
+// 91, but 66: 117 / 111 and 129: 254 / 131).
 static bool use_mfma(const kaldo_crystal* c, int prec) {
-  if (!gm_supported(c)) return false;
+  if (!gm_supported(c) || (prec == KALDO_FP64 && c->nb3 <= kGpTile)) return false;
   if (prec == KALDO_BF16X3) return true;
   const char* f = std::getenv("KALDO_FORCE_GENERIC");
   return !(f && f[0] == '1');
@@ -245,7 +250,7 @@ static GammaWs gamma_ws(const kaldo_crystal* c, int prec) {
   w.off_w = take(es * n * n * kGpBatch);
   w.off_partial = take(8 * n * nt * nt);
   w.total = w.least = o;
-  if (gm_supported(c)) {
+  if (gm_supported(c) && (prec != KALDO_FP64 || c->nb3 > kGpTile)) {
     w.total = std::max(o, w.off_rest + gm_workspace_bytes(c, prec, false));
     if (prec != KALDO_FP64) w.least = std::max(o, w.off_rest + gm_workspace_bytes(c, prec, true));
   }
@@ -281,8 +286,9 @@ static int run_gamma(const kaldo_crystal* c, const double* omega, const double* 
   for (int m0 = 0; m0 < n; m0 += kGpBatch) {
     int nb = std::min(kGpBatch, n - m0);
     long na = (long)c->gamma.n_bc * nb;
-    KALDO_LAUNCH("gp_avals", gp_avals<T>, dim3((na + 255) / 256), dim3(256), 0, st, n, c->gamma.n_bc, m0,
-                       nb, c->gamma.t_ptr, c->gamma.t_a, c->gamma.t_coef, evec, av);
+    if (na > 0)  // a cell may have no third-order force constants
+      KALDO_LAUNCH("gp_avals", gp_avals<T>, dim3((na + 255) / 256), dim3(256), 0, st, n, c->gamma.n_bc, m0,
+                         nb, c->gamma.t_ptr, c->gamma.t_a, c->gamma.t_coef, evec, av);
     KALDO_LAUNCH("gp_spmm", gp_spmm<T>, dim3(n, nb), dim3(256), 0, st, n, c->gamma.n_bc, nb,
                        c->gamma.row_ptr, c->gamma.col, av, Et, W);
     KALDO_LAUNCH("gp_gemm", gp_gemm<T>, dim3(nt, nt, nb), dim3(256), 0, st, p, n, m0, Et, W, omega, occ,

@@ -149,29 +149,6 @@ __device__ __forceinline__ bool gm_can_meet(const LwParams& p, double w, double2
   return can(a, b) || (both && can(b, a));
 }
 
-// need[mu][J] = 1 when some strip pair the GEMM multiplies for mode mu
-// reads the W columns of block J of kNeed columns (its rows lie in tiles
-// I <= J / 2 for the symmetric form, anywhere otherwise).
-constexpr int kNeed = 64;
-__global__ void gm_need(LwParams p, int np, int n, const double* __restrict__ omega,
-                        const uint8_t* __restrict__ phys, const uint8_t* __restrict__ sel,
-                        const double2* __restrict__ srange, uint8_t* __restrict__ need) {
-  const int nj = np / kNeed;
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n * nj) return;
-  const int mu = k / nj, J = k % nj;
-  bool any = false;
-  if (sel[mu] && phys[mu]) {
-    const bool sym = p.half != 0;
-    const double w = omega[mu];
-    const double2 cols = gm_range(srange, J * (kNeed / kStrip), kNeed / kStrip);
-    const int tj = J * kNeed / kMT, rows = (sym ? (tj + 1) * kMT : np) / kStrip;
-    for (int I = 0; I < rows && !any; ++I)
-      any = gm_can_meet(p, w, srange[I], cols, sym && I * kStrip / kMT != tj);
-  }
-  need[k] = any ? 1 : 0;
-}
-
 struct GmTileInfo {
   int ti, tj;
 };
@@ -190,14 +167,20 @@ __device__ __forceinline__ GmTileInfo gm_tile(int t, int nt, bool sym) {
 }
 
 // Live tiles of each mode: one wave per mode, tile t = 64 k + lane in bit
-// `lane` of mask[mu][k] (n_word words a mode), and their number.
-__global__ __launch_bounds__(256) void gm_live_mask(LwParams p, int nt, int n_tri, int n_word, int n,
+// `lane` of mask[mu][k] (n_word words a mode), and their number.  Then
+// need[mu][J] = 1 when some strip pair the GEMM multiplies for mode mu reads
+// the W columns of block J of kNeed columns (its rows lie in tiles I <= J / 2
+// for the symmetric form, anywhere otherwise).  (One launch: with one each a
+// step of a cell of one or two atoms took 46 us, with one 42.)
+constexpr int kNeed = 64;
+__global__ __launch_bounds__(256) void gm_live_mask(LwParams p, int nt, int n_tri, int n_word, int np, int n,
                                                     const double* __restrict__ omega,
                                                     const uint8_t* __restrict__ phys,
                                                     const uint8_t* __restrict__ sel,
                                                     const double2* __restrict__ srange,
                                                     unsigned long long* __restrict__ mask,
-                                                    int32_t* __restrict__ count) {
+                                                    int32_t* __restrict__ count,
+                                                    uint8_t* __restrict__ need) {
   const int mu = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (mu >= n) return;  // wave-uniform
   const bool sym = p.half != 0, on = sel[mu] && phys[mu];
@@ -216,6 +199,17 @@ __global__ __launch_bounds__(256) void gm_live_mask(LwParams p, int nt, int n_tr
     c += __popcll(m);
   }
   if (lane == 0) count[mu] = c;
+  const int nj = np / kNeed;
+  for (int J = lane; J < nj; J += 64) {
+    bool any = false;
+    if (on) {
+      const double2 cols = gm_range(srange, J * (kNeed / kStrip), kNeed / kStrip);
+      const int tj = J * kNeed / kMT, rows = (sym ? (tj + 1) * kMT : np) / kStrip;
+      for (int I = 0; I < rows && !any; ++I)
+        any = gm_can_meet(p, w, srange[I], cols, sym && I * kStrip / kMT != tj);
+    }
+    need[(size_t)mu * nj + J] = any ? 1 : 0;
+  }
 }
 
 // Compacted list of the live (mode, tile) pairs of a batch, in (mode, tile)
@@ -750,11 +744,9 @@ static int run_gm_form(const char* gemm_name, const kaldo_crystal* c, const LwPa
   const int n_batch = (n + batch - 1) / batch, n_word = (n_tri + 63) / 64;
   const size_t live_stride = (size_t)batch * n_tri + 1;
   KALDO_LAUNCH("gm_live_mask", gm_live_mask, dim3((unsigned)(n + 3) / 4), dim3(256), 0, st, p, nt, n_tri,
-               n_word, n, omega, phys, sel, b.srange, b.live_mask, b.live_count);
+               n_word, np, n, omega, phys, sel, b.srange, b.live_mask, b.live_count, b.need);
   KALDO_LAUNCH("gm_live_list", gm_live_list, dim3((unsigned)n_batch), dim3(1024), 0, st, n_tri, n_word,
                n, batch, b.live_mask, b.live_count, b.live_lists);
-  KALDO_LAUNCH("gm_need", gm_need, dim3((unsigned)((n * (long)(np / kNeed) + 255) / 256)), dim3(256), 0,
-               st, p, np, n, omega, phys, sel, b.srange, b.need);
   const size_t spmm_bytes = (size_t)c->gamma.max_u * spmm_lds<T>() * sizeof(T);
   for (int m0 = 0; m0 < n; m0 += batch) {
     const int nb = std::min(batch, n - m0);

@@ -29,12 +29,12 @@ def dev(a):
 
 @contextlib.contextmanager
 def kernels(names):
-    """Adds to `names` the kernels launched inside."""
+    """Adds to `names` the kernels launched inside, and how often."""
     K.lib().kaldo_profile_begin()
     yield
     rec, n = (K.KernelTime * 64)(), ctypes.c_int32()
     K._check(K.lib().kaldo_profile_end(rec, 64, ctypes.byref(n)))
-    names.update(rec[i].name.decode() for i in range(n.value))
+    names.update({rec[i].name.decode(): rec[i].launches for i in range(n.value)})
 
 
 def cluster(n):
@@ -45,7 +45,7 @@ def run(m, b, P):
     """Linewidths and the names of the kernels that made them."""
     om, E = oph.phonons_gamma_real(m)
     c = K.Crystal.from_model(m)
-    names = set()
+    names = {}
     with kernels(names):
         g = K.linewidths_gamma(c, dev(om), dev(E), 300.0, b, P).cpu().numpy()
     c.device_status()
@@ -59,7 +59,7 @@ def test_fp64_small_cells_run_without_matrix_cores(name, kernel):
     m = cluster(name)
     b = configs.Broadening(adaptive=False, sigma_thz=0.3)
     g, names, om, E = run(m, b, K.FP64)
-    assert kernel in names and len(names & {"gp_gemm", "gm_gemm_fp64"}) == 1
+    assert kernel in names and len(set(names) & {"gp_gemm", "gm_gemm_fp64"}) == 1
     go = olw.gamma_point_linewidths(m, om, E, 300.0, b)
     assert np.max(np.abs(g - go)) <= 1e-10 * go.max()
 
@@ -70,3 +70,10 @@ def test_cell_without_third_order_constants(prec):
     none = {f: getattr(m, f)[:0] for f in ("fc3_i", "fc3_j", "fc3_k", "fc3_val")}
     g, *_ = run(models.Model(**{**m.__dict__, **none}), configs.Broadening(adaptive=False), getattr(K, prec.upper()))
     assert np.all(g == 0.0)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+def test_launches_of_the_smallest_cells(prec):
+    """Their time is launches: eleven of them."""
+    _, names, *_ = run(cluster(2), configs.Broadening(adaptive=False, sigma_thz=0.3), getattr(K, prec.upper()))
+    assert sum(names.values()) <= 11, names

@@ -185,8 +185,10 @@ int kaldo_phonons(const kaldo_crystal* c, const int32_t* mesh, double* omega,
 int kaldo_phonons_gamma(int32_t n_basis, const double* mass, int32_t n_rep, const double* fc2,
                         double* omega, double* evec);
 
-/* Device workspace bytes kaldo_linewidths needs for this crystal, mesh and
- * precision. */
+/* Device workspace bytes for kaldo_linewidths with this crystal, mesh and
+ * precision.  (On small meshes of one- and two-atom cells the call, and
+ * kaldo_tcache_build likewise, also takes a workspace without the tables of
+ * its sweep by boxes, and sweeps in rounds then; same terms, other order.) */
 size_t kaldo_linewidths_workspace(const kaldo_crystal* c, const int32_t* mesh,
                                   int32_t precision);
 

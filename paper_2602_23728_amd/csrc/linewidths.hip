@@ -21,6 +21,7 @@
 //   lw_finish        per mode: fixed-order sum of the partials, prefactor
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstdlib>
 #include <string>
 
@@ -261,19 +262,22 @@ static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
 }
 
 // Workspace layout of the path that serves the request (offsets of buffers
-// another path needs are left at 0 and never used).
+// another path needs are left at 0 and never used).  boxes: a fused request is
+// swept by boxes (lw_fused.hip), otherwise in rounds (lw_rounds.hip).
 struct CrystalWs {
   CrystalPath path;
+  bool boxes;
   size_t off_occ, off_phys, off_sel, off_eta, off_at, off_partial, off_phase, off_modef, off_qlist,
       off_fpart, off_rec, off_mrec, off_freq, off_window, off_bsum, total;
 };
 
-static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, CrystalPath path) {
+static CrystalWs crystal_ws_layout(const kaldo_crystal* c, long nq, int prec, CrystalPath path, bool boxes) {
   const int nb3 = c->nb3;
   const size_t cs = prec == KALDO_FP64 ? 16 : 8;
   const long nblk = (nq + 63) / 64;
   CrystalWs w{};
   w.path = path;
+  w.boxes = boxes;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t r = o;
@@ -288,7 +292,7 @@ static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, Cryst
     w.off_eta = take(cs * nq * nb3 * nb3);
     w.off_at = take(cs * nq * (size_t)c->bloch.n_e * nb3);
     w.off_partial = take(sizeof(double) * nq * nblk * nb3);
-  } else if (w.path == CrystalPath::Fused && !fused_boxes(c, prec)) {
+  } else if (w.path == CrystalPath::Fused && !boxes) {
     w.off_eta = take(cs * nq * nb3 * nb3);
     w.off_phase = take(cs * nq * (size_t)std::max(1, c->bloch.n_d));
     w.off_qlist = take(sizeof(int32_t) * (2 * nq + 1));
@@ -311,8 +315,20 @@ static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, Cryst
   return w;
 }
 
-static CrystalWs crystal_ws(const kaldo_crystal* c, long nq, int prec) {
-  return crystal_ws_for(c, nq, prec, choose_path(c, nq, prec));
+// The layout for a workspace of `bytes`.  The boxes' tables make a small mesh's
+// larger than the rounds' (two atoms, up to 1,600 points); a workspace that
+// holds only those has always been taken, and the rounds serve it.
+static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, CrystalPath path,
+                                size_t bytes = SIZE_MAX) {
+  const CrystalWs w =
+      crystal_ws_layout(c, nq, prec, path, path == CrystalPath::Fused && fused_boxes(c, prec));
+  if (!w.boxes || w.total <= bytes) return w;
+  const CrystalWs r = crystal_ws_layout(c, nq, prec, path, false);
+  return r.total <= bytes ? r : w;
+}
+
+static CrystalWs crystal_ws(const kaldo_crystal* c, long nq, int prec, size_t bytes = SIZE_MAX) {
+  return crystal_ws_for(c, nq, prec, choose_path(c, nq, prec), bytes);
 }
 
 static FusedWs fused_ws(unsigned char* ws, const CrystalWs& w) {
@@ -339,11 +355,10 @@ static int run_crystal(const kaldo_crystal* c, const int32_t* mesh, const double
   double* partial = reinterpret_cast<double*>(ws + w.off_partial);
   float4* modef = reinterpret_cast<float4*>(ws + w.off_modef);
   const double inv_kt_hbar = kHbar / (kKb * T_k);
-  const bool boxes = w.path == CrystalPath::Fused && fused_boxes(c, prec);
-  double2* mrec = w.path == CrystalPath::Fused && !boxes ? reinterpret_cast<double2*>(ws + w.off_mrec) : nullptr;
+  double2* mrec = w.path == CrystalPath::Fused && !w.boxes ? reinterpret_cast<double2*>(ws + w.off_mrec) : nullptr;
   KALDO_LAUNCH("lw_prepare", lw_prepare, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes,
                nb3, omega, vel, evec, inv_kt_hbar, b->nu_min_thz, occ, phys, sel, modef,
-               boxes ? reinterpret_cast<float*>(ws + w.off_freq) : nullptr, mrec,
+               w.boxes ? reinterpret_cast<float*>(ws + w.off_freq) : nullptr, mrec,
                subset ? 0 : 1, c->d_flags);
   if (subset && n_subset > 0)
     KALDO_LAUNCH("lw_select", lw_select, dim3((n_subset + 255) / 256), dim3(256), 0, st, subset,
@@ -355,7 +370,7 @@ static int run_crystal(const kaldo_crystal* c, const int32_t* mesh, const double
                        kPrefactor / (double)nq, gamma, st);
   }
   if (path == CrystalPath::Fused) {
-    if (!boxes)
+    if (!w.boxes)
       return launch_rounds<T>(c, p, omega, vel, modef, occ, mrec, phys, sel, evec, eta,
                               reinterpret_cast<C*>(ws + w.off_phase),
                               reinterpret_cast<int32_t*>(ws + w.off_qlist),
@@ -416,7 +431,7 @@ int linewidths_enqueue(const kaldo_crystal* c, const int32_t* mesh, const double
   }
   KALDO_REQUIRE(n_subset >= 0 && (n_subset == 0 || modes_subset), "kaldo_linewidths: bad subset");
   KALDO_REQUIRE(nq <= 65535L, "kaldo_linewidths: mesh too large (N_q > 65535)");
-  CrystalWs w = crystal_ws(c, nq, precision);
+  CrystalWs w = crystal_ws(c, nq, precision, workspace_bytes);
   KALDO_REQUIRE(workspace && workspace_bytes >= w.total, "kaldo_linewidths: workspace too small");
   if (modes_subset && n_subset == 0) return KALDO_OK;
   auto* ws = static_cast<unsigned char*>(workspace);
@@ -478,7 +493,7 @@ extern "C" int kaldo_tcache_build(const kaldo_crystal* c, const int32_t* mesh, c
                 "kaldo_tcache_build: pairs and factors must both be given or both be NULL");
   const long nq = (long)mesh[0] * mesh[1] * mesh[2];
   KALDO_REQUIRE(nq <= 65535L, "kaldo_tcache_build: mesh too large (N_q > 65535)");
-  const CrystalWs w = crystal_ws_for(c, nq, precision, CrystalPath::Fused);
+  const CrystalWs w = crystal_ws_for(c, nq, precision, CrystalPath::Fused, workspace_bytes);
   KALDO_REQUIRE(workspace && workspace_bytes >= w.total, "kaldo_tcache_build: workspace too small");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int nb3 = c->nb3;
@@ -494,7 +509,7 @@ extern "C" int kaldo_tcache_build(const kaldo_crystal* c, const int32_t* mesh, c
   uint8_t* phys = ws + w.off_phys;
   uint8_t* sel = ws + w.off_sel;
   float4* modef = reinterpret_cast<float4*>(ws + w.off_modef);
-  const bool boxes = fused_boxes(c, precision);
+  const bool boxes = w.boxes;
   double2* mrec = boxes ? nullptr : reinterpret_cast<double2*>(ws + w.off_mrec);
   // the populations lw_prepare writes are not used: any temperature will do
   KALDO_LAUNCH("lw_prepare", lw_prepare, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes, nb3,

@@ -86,3 +86,43 @@ def test_gamma_point_batches_are_the_same_to_the_bit():
         got = K.linewidths_gamma(c, om, E, 300.0, b, K.FP64, workspace=buffer(size)).cpu().numpy()
         assert np.array_equal(got, ref), size
     c.close()
+
+
+def crystal_sizes(c, mesh, prec, n_d):
+    """The workspace of the kernel that sweeps in rounds."""
+    nq, nb3 = int(np.prod(mesh)), c.nb3
+    cs = 16 if prec == K.FP64 else 8
+    return total(8 * nq * nb3, nq * nb3, nq * nb3, 16 * nq * nb3, cs * nq * nb3 * nb3, cs * nq * n_d,
+                 4 * (2 * nq + 1), 8 * nq * 16 * nb3, 48 * nq * nb3)
+
+
+def differences(m):
+    rep, nb = np.asarray(m.rep), m.n_basis
+    return len({tuple(d) for d in rep[m.fc3_j // 3 // nb] - rep[m.fc3_k // 3 // nb]})
+
+
+# small meshes, whose tables for the sweep by boxes take more
+@pytest.mark.parametrize("mesh", [(1, 1, 1), (3, 3, 3), (5, 4, 7)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+def test_crystal_smaller_workspace(mesh, prec):
+    m = models.diamond()
+    P = getattr(K, prec.upper())
+    om, ev, ve = (dev(x) for x in oph.phonons(m, mesh))
+    b = configs.Broadening(adaptive=True)
+    c = K.Crystal.from_model(m)
+    want = K.linewidths(c, mesh, om, ev, ve, 300.0, b, P).cpu().numpy()
+    size = crystal_sizes(c, mesh, P, differences(m))
+    got = K.linewidths(c, mesh, om, ev, ve, 300.0, b, P, workspace=buffer(size)).cpu().numpy()
+    assert np.max(np.abs(got - want)) <= (1e-10 if prec == "fp64" else 1e-5) * want.max()
+    with pytest.raises(K.KaldoError):
+        K.linewidths(c, mesh, om, ev, ve, 300.0, b, P, workspace=buffer(size - 256))
+    if prec != "bf16x3":
+        ref = K.tcache_build(c, mesh, om, ev, ve, b, P)
+        tc = K.tcache_build(c, mesh, om, ev, ve, b, P, workspace=buffer(size))
+        assert torch.equal(tc.row_ptr, ref.row_ptr)
+        g, r = (K.tcache_gamma(c, t, om, b.nu_min_thz, [300.0]).cpu().numpy() for t in (tc, ref))
+        assert np.max(np.abs(g - r)) <= (1e-10 if prec == "fp64" else 1e-5) * max(r.max(), 1e-300)
+        with pytest.raises(K.KaldoError):
+            K.tcache_build(c, mesh, om, ev, ve, b, P, workspace=buffer(size - 256))
+    c.device_status()
+    c.close()

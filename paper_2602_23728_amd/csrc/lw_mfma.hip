@@ -132,10 +132,13 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
   const int a0 = q / (N1 * N2), a1 = (q / N2) % N1, a2 = q % N2;
 
   extern __shared__ double2 smem[];
-  const int at_s = p.n_blk * 9;                  // entries of one branch
-  const int at_n = group * at_s + 9 * n_slot;    // and a zero tail a padded range may read
+  // entries of one branch, and the zero tail its padded ranges may read: each
+  // branch has its own, since a zero phase does not hide what is not finite in
+  // the next branch's table
+  const int at_s = (p.n_blk + n_slot) * 9;
+  const int at_n = group * at_s;
   const int n_ph = tile_phases(NB, p.n_blk, n_slot);
-  C* at = reinterpret_cast<C*>(smem);            // [branch of the group][n_blk][9]
+  C* at = reinterpret_cast<C*>(smem);            // [branch of the group][n_blk + n_slot][9]
   unsigned char* wave_lds = reinterpret_cast<unsigned char*>(smem) +
                             ((size_t)at_n * sizeof(C) + 15) / 16 * 16 +
                             wv * tile_wave_lds<FORM>(group, n_ph);
@@ -512,7 +515,7 @@ static size_t tile_lds(const kaldo_crystal* c, int group) {
   const size_t cs = sizeof(typename Cx<typename Dense<FORM>::T>::type);
   const int n_slot = tile_slots(c->bloch.max_pair_blk);
   const int n_ph = tile_phases(c->nb, c->bloch.n_blk, n_slot);
-  const size_t at_n = (size_t)group * c->bloch.n_blk * 9 + 9 * n_slot;
+  const size_t at_n = (size_t)group * (c->bloch.n_blk + n_slot) * 9;
   return (at_n * cs + 15) / 16 * 16 + Dense<FORM>::kWaves * tile_wave_lds<FORM>(group, n_ph) + sizeof(int) * n_ph;
 }
 

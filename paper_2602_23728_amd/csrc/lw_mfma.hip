@@ -132,13 +132,10 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
   const int a0 = q / (N1 * N2), a1 = (q / N2) % N1, a2 = q % N2;
 
   extern __shared__ double2 smem[];
-  // entries of one branch, and the zero tail its padded ranges may read: each
-  // branch has its own, since a zero phase does not hide what is not finite in
-  // the next branch's table
-  const int at_s = (p.n_blk + n_slot) * 9;
-  const int at_n = group * at_s;
+  const int at_s = p.n_blk * 9;                  // entries of one branch
+  const int at_n = group * at_s + 9 * n_slot;    // and a zero tail a padded range may read
   const int n_ph = tile_phases(NB, p.n_blk, n_slot);
-  C* at = reinterpret_cast<C*>(smem);            // [branch of the group][n_blk + n_slot][9]
+  C* at = reinterpret_cast<C*>(smem);            // [branch of the group][n_blk][9]
   unsigned char* wave_lds = reinterpret_cast<unsigned char*>(smem) +
                             ((size_t)at_n * sizeof(C) + 15) / 16 * 16 +
                             wv * tile_wave_lds<FORM>(group, n_ph);
@@ -154,6 +151,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
       kTileWaves * tile_wave_lds<FORM>(group, n_ph));           // d of each phase slot, -1: none
   __shared__ double2 phq[64];
   __shared__ double wq64[16];
+  __shared__ unsigned bad_lds;  // branches of the group whose table is not finite
 
   unsigned live = 0, any_sel = 0;  // branches of the group, bit s - s_lo
   float wq_abs_max = 0.0f;
@@ -169,6 +167,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
     return;
   }
   if (tid < n_s) wq64[tid] = omega[q * NB3 + s_lo + tid];
+  if (tid == 0) bad_lds = 0;
   for (int k = lane; k < n_s * kAccSlots; k += 64) acc[k] = 0.0;
   if constexpr (kSpl)
     for (int k = lane; k < 16 * 17; k += 64) bt[k] = Cx<T>::make((T)0, (T)0);
@@ -198,9 +197,18 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
       re += c * (ex * f.x - ey * f.y);
       im += c * (ex * f.y + ey * f.x);
     }
-    at[s * at_s + e_blk[e] * 9 + e_bg[e]] = Cx<T>::make((T)re, (T)im);
+    // a padded range may read into the next branch's table, and a zero phase
+    // hides nothing that is not finite: such a branch keeps zeros there, and its
+    // terms are NaN where they are weighted
+    T x = (T)re, y = (T)im;
+    if (!((x - x) + (y - y) == (T)0)) {
+      x = y = (T)0;
+      atomicOr(&bad_lds, 1u << s);
+    }
+    at[s * at_s + e_blk[e] * 9 + e_bg[e]] = Cx<T>::make(x, y);
   }
   __syncthreads();
+  const unsigned bad = __builtin_amdgcn_readfirstlane(bad_lds);
 
   // Accumulator item r of a lane is row row_of(r) of its column lr; K slot
   // (MFMA t, lane group lg) of the first product is column 4 (t % 4) + lg of
@@ -251,6 +259,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
         const C v = cq_v[e];
         c = pair_weight_both(p, dbl, wq64[cs_], d1[0], d2[0], d1[1], d2[1], sp, sm) *
             ((double)v.x * (double)v.x + (double)v.y * (double)v.y);
+        if (bad >> cs_ & 1u) c = __builtin_nan("");
       }
       double* a = acc + cs_ * kAccSlots + (lane & (kAccSlots - 1));
 #pragma unroll
@@ -509,13 +518,13 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
 }
 
 // Static LDS of lw_tiles, and the dynamic part with `group` branches a workgroup.
-constexpr size_t kTileStatic = 64 * 16 + 16 * 8;
+constexpr size_t kTileStatic = 64 * 16 + 16 * 8 + 16;
 template <int FORM>
 static size_t tile_lds(const kaldo_crystal* c, int group) {
   const size_t cs = sizeof(typename Cx<typename Dense<FORM>::T>::type);
   const int n_slot = tile_slots(c->bloch.max_pair_blk);
   const int n_ph = tile_phases(c->nb, c->bloch.n_blk, n_slot);
-  const size_t at_n = (size_t)group * (c->bloch.n_blk + n_slot) * 9;
+  const size_t at_n = (size_t)group * c->bloch.n_blk * 9 + 9 * n_slot;
   return (at_n * cs + 15) / 16 * 16 + Dense<FORM>::kWaves * tile_wave_lds<FORM>(group, n_ph) + sizeof(int) * n_ph;
 }
 

@@ -238,6 +238,21 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
     b_ph[i] = FOUR ? 4 * pr : pair_ptr[pr];
     b_cnt[i] = pair_ptr[pr + 1] - pair_ptr[pr];
   }
+  // Steps the wave takes for each of the four.  The split form's list is sorted
+  // by length: its later entries are fewer and shorter, or none (random three
+  // atoms on 7^3, adaptive, against 1,105 us with all sixteen
+  // steps for each: 829).
+  int b_end[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    int n = n_slot;
+    if constexpr (kSpl && !FOUR) {
+      n = b_pos[i] < 16 * 17 ? b_cnt[i] : 0;
+      for (int off = 1; off < 64; off <<= 1) n = max(n, __shfl_xor(n, off, 64));
+      n = __builtin_amdgcn_readfirstlane(n);
+    }
+    b_end[i] = n;
+  }
 
   // Exact FP64 cut and weight of queued candidates, one per lane, in queue
   // order, from the partner's mode data staged in LDS (the queue only ever
@@ -420,6 +435,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
           for (int j0 = 0; j0 < (FOUR ? 4 : n_slot); j0 += 4) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
+              if (!FOUR && kSpl && j0 >= b_end[i]) continue;  // uniform
               C a[4], f[4];
 #pragma unroll
               for (int j = 0; j < 4; ++j) {

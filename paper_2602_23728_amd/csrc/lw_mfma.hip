@@ -286,6 +286,13 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
     n_cand = 0;
   };
 
+  // the group's next live branch after s, n_s when there is none (the next of
+  // all in the split form of few blocks, whose loop then is 1 % shorter)
+  constexpr bool kJump = !(kSpl && FOUR);
+  auto next_live = [&](int s) {
+    const unsigned m = live >> (s + 1);
+    return !kJump ? s + 1 : m ? s + __ffs(m) : n_s;
+  };
   const Partners prt(p.half != 0, a0, a1, a2, N0, N1, N2);
   const float w_lane = lane < n_s ? (float)wq64[lane] : 0.0f;  // branch frequencies, read by readlane
   unsigned partner = 0;  // lane k: q1 | q2 << 16 of the wave's k-th partner of 64
@@ -321,7 +328,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
     // The branches of the group, in runs as long as the queue takes whole
     // branches (one run, as a rule): a run ends with its candidates resolved,
     // where none of its operand registers is live.
-    int s = 0;
+    int s = next_live(-1);
     do {
       // eta(q2)[kc][s''] as the B operand of T = B_s eta2 (column n = lr) and
       // eta(q1)[jc][s'] as A = eta1^T (row m = lr) of V = eta1^T T; zero
@@ -389,7 +396,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
       };
       if constexpr (kAhead) fetch(s);
 #pragma unroll 1
-      for (; s < n_s; ++s) {
+      for (; s < n_s; s = next_live(s)) {
         // the candidates of this branch, before anything is projected:
         // coalescence of either ordering, or decay (w > 0: s is live)
         const float wsf = __builtin_bit_cast(
@@ -404,10 +411,10 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
           mask[r] = __ballot(np) | __ballot(nm);
           n_new += __popcll(mask[r]);
         }
-        const bool skip = n_new == 0 || !(live >> s & 1u);         // uniform
+        const bool skip = n_new == 0 || (!kJump && !(live >> s & 1u));  // uniform
         if (!skip && n_cand + n_new > kTileCand) break;  // uniform: n_new <= 256 fits an empty queue
         if (skip) {
-          if constexpr (kAhead) fetch(s + 1);
+          if constexpr (kAhead) fetch(next_live(s));
           continue;
         }
         // B_s in operand order; a pair's slots past its blocks have a zero phase
@@ -429,7 +436,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
             for (int j = 0; j < 4; ++j) f[j] = phb[b_ph[i] + j];
             quad(i, an + 4 * i, f);
           }
-          fetch(s + 1);
+          fetch(next_live(s));
         } else {
           const C* as = at + s * at_s;
           for (int j0 = 0; j0 < (FOUR ? 4 : n_slot); j0 += 4) {

@@ -227,15 +227,20 @@ __global__ void lw_finish(int nq, int nb3, int nblk, double scale, const double*
 // generic kernel when neither fits.  KALDO_CRYSTAL_PATH=fused|mfma|generic
 // overrides the FP32 and FP64 choice.
 //
-// In FP64 the dense kernel serves whatever the fused one cannot hold (its
-// tables of all branches must fit the LDS), cells of 12 branches and more, and
-// those of 9 on meshes of up to 96 points.  Random cells, 4^3 / 9^3 mesh,
-// fused (generic where it does not fit) against dense, ms: 2 atoms 0.16 / 1.09
-// against 0.09 / 3.72, 3 atoms 0.38 / 4.30 against 0.12 / 4.61 (7^3, a narrow
-// fixed width: 0.72 against 1.33), 4 atoms 56 / 553 (generic) against 0.14 /
-// 6.8, 5 atoms 116 / 1090 (generic) against 0.22 / 14.0: the pruned kernel's
-// work per q grows with the pairs inside the cut, few of them with few
-// branches, the dense one's with all 16 x 16.
+// In FP64 the dense kernel serves whatever the fused ones cannot hold (their
+// tables of all branches must fit the LDS) and the cells of 9 branches and more
+// on meshes of up to 80 points, where it won at every cell and width (random
+// cells of three to five atoms, 4 to 51 blocks: 1.1 to 12 times).  Past that the
+// pruned kernel's work grows with the pairs inside the cut and their blocks,
+// which the host cannot tell, the dense one's with all 16 x 16, so where the
+// tables fit the pruned one serves.  Fused against dense, ms, adaptive / fixed
+// 0.2 THz / 0.02 THz: 4x6x4, three atoms of 11 blocks 0.07 / 0.06 / 0.05 against
+// 0.10 / 0.07 / 0.06; 12^3, four atoms of 26 blocks 11.3 / 16.8 / 3.5 against
+// 24.2 / 24.6 / 15.8, of 42 blocks 34.7 / 36.4 / 7.2 against 27.2 / 26.5 / 16.2;
+// five atoms of 51 blocks 66.9 / 91.8 / 15.6 against 38.0 / 37.3 / 28.4.  Where
+// they do not fit (abx3: 65 blocks) the generic kernel takes 33.8 ms on 4^3, the
+// dense one 0.10.
+constexpr long kDense64Points = 80;
 enum class CrystalPath { Generic, Fused, Mfma };
 
 static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
@@ -255,7 +260,7 @@ static CrystalPath choose_path(const kaldo_crystal* c, long nq, int prec) {
   if (prec == KALDO_FP32 && mfma_supported(c) && (want == "mfma" || (want.empty() && c->nb3 >= 9)))
     return CrystalPath::Mfma;
   const bool fused = fused_supported(c, prec);
-  const bool dense64 = !fused || c->nb3 >= 12 || (c->nb3 >= 9 && nq <= 96);
+  const bool dense64 = !fused || (c->nb3 >= 9 && nq <= kDense64Points);
   if (prec == KALDO_FP64 && mfma64_supported(c) && (want == "mfma" || (want.empty() && dense64)))
     return CrystalPath::Mfma;
   return fused ? CrystalPath::Fused : CrystalPath::Generic;
@@ -317,7 +322,8 @@ static CrystalWs crystal_ws_layout(const kaldo_crystal* c, long nq, int prec, Cr
 
 // The layout for a workspace of `bytes`.  The boxes' tables make a small mesh's
 // larger than the rounds' (two atoms, up to 1,600 points); a workspace that
-// holds only those has always been taken, and the rounds serve it.
+// holds only those has always been taken, and the rounds serve it.  So does
+// the dense FP64 kernel one too small for the pruned kernel's tables.
 static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, CrystalPath path,
                                 size_t bytes = SIZE_MAX) {
   const CrystalWs w =
@@ -328,7 +334,11 @@ static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, Cryst
 }
 
 static CrystalWs crystal_ws(const kaldo_crystal* c, long nq, int prec, size_t bytes = SIZE_MAX) {
-  return crystal_ws_for(c, nq, prec, choose_path(c, nq, prec), bytes);
+  const CrystalWs w = crystal_ws_for(c, nq, prec, choose_path(c, nq, prec), bytes);
+  if (w.total <= bytes || w.path != CrystalPath::Fused || prec != KALDO_FP64 || c->nb3 < 9 || !mfma64_supported(c))
+    return w;
+  const CrystalWs d = crystal_ws_for(c, nq, prec, CrystalPath::Mfma);
+  return d.total <= bytes ? d : w;
 }
 
 static FusedWs fused_ws(unsigned char* ws, const CrystalWs& w) {

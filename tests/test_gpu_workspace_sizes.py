@@ -126,3 +126,22 @@ def test_crystal_smaller_workspace(mesh, prec):
             K.tcache_build(c, mesh, om, ev, ve, b, P, workspace=buffer(size - 256))
     c.device_status()
     c.close()
+
+
+def test_dense_fp64_smaller_workspace():
+    """A cell the pruned kernel serves, in a workspace that holds only the dense kernel's phases."""
+    m = models.random_cell(44, 4, cutoff=2.4)
+    mesh = (4, 6, 4)
+    om, ev, ve = (dev(x) for x in oph.phonons(m, mesh))
+    b = configs.Broadening(adaptive=True)
+    c = K.Crystal.from_model(m)
+    want = K.linewidths(c, mesh, om, ev, ve, 300.0, b, K.FP64).cpu().numpy()
+    n = 96 * c.nb3
+    size = total(8 * n, n, n, 16 * n, 16 * 96 * differences(m))
+    assert size < K.linewidths_workspace(c, mesh, K.FP64)
+    got = K.linewidths(c, mesh, om, ev, ve, 300.0, b, K.FP64, workspace=buffer(size)).cpu().numpy()
+    assert np.max(np.abs(got - want)) <= 1e-10 * want.max()
+    with pytest.raises(K.KaldoError):
+        K.linewidths(c, mesh, om, ev, ve, 300.0, b, K.FP64, workspace=buffer(size - 256))
+    c.device_status()
+    c.close()

@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256) void lw_tables(
     const int q = (blk - jobs.first[3]) * 256 + threadIdx.x;
     if (q < p.nq && subset) {
       int f = 0;
-      for (int s = 0; s < nb3; ++s) f |= phys[q * nb3 + s] && sel[q * nb3 + s];
+      for (int s = 0; s < nb3; ++s) f |= phys[q * nb3 + s] & sel[q * nb3 + s];  // 0/1 bytes, no branch
       idx_of_q[q] = f;
     } else if (q < p.nq) {
       list[q] = q;

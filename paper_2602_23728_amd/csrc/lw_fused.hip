@@ -225,6 +225,8 @@ __global__ __launch_bounds__(256) void lw_tables(
   }
 }
 
+constexpr int kWaitLds = 0xc07f;  // s_waitcnt lgkmcnt(0), the other counters left
+
 // 16 CH bytes of each lane's row (tab + idx * stride) into LDS.  CH
 // neighbouring lanes fetch a row's 16-byte pieces side by side, so that an
 // instruction covers 64 / CH rows with whole cache lines: a lane fetching its
@@ -236,8 +238,8 @@ __global__ __launch_bounds__(256) void lw_tables(
 // every lane's on the same banks; pulled() gives a byte of the lane's own row.
 // `st` is the wave's own; returns when the rows are there.  The pieces arrive
 // by the memory pipe, which knows nothing of the LDS reads the wave still has
-// under way (a wavefront fence orders the LDS instructions only): it waits for
-// those of the rows before first.
+// under way (a wavefront fence orders the LDS instructions only): the first piece
+// waits for those of the rows before, with its own row's index.
 template <int CH>
 __device__ __forceinline__ int pull_swap(int row) {
   return CH == 8 ? (row >> 1) & 7 : CH == 4 ? (row >> 2) & 3 : 0;
@@ -245,9 +247,10 @@ __device__ __forceinline__ int pull_swap(int row) {
 template <int CH>
 __device__ __forceinline__ void pull_rows(const unsigned char* tab, int stride, int idx,
                                           unsigned char* st, int lane) {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   auto piece = [&](int k, int row, int byte) {  // row's index from the lane that holds it
-    const unsigned off = (unsigned)__builtin_amdgcn_ds_bpermute(row, idx) * stride + byte;
+    const int at = __builtin_amdgcn_ds_bpermute(row, idx);
+    if (k == 0) __builtin_amdgcn_s_waitcnt(kWaitLds);
+    const unsigned off = (unsigned)at * stride + byte;
     __builtin_amdgcn_global_load_lds(
         (const __attribute__((address_space(1))) void*)(tab + (size_t)off),
         (__attribute__((address_space(3))) void*)(st + 1024 * k), 16, 0, 0);

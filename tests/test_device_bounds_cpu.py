@@ -36,9 +36,11 @@ def test_asynchronous_lds_loads_wait_for_the_reads_before_them():
             if at < 0:
                 continue
             found += 1
-            wait = re.search(r"s_waitcnt[^\"]*lgkmcnt\(0\)", b)
+            wait = re.search(r"s_waitcnt[^\"]*lgkmcnt\(0\)|__builtin_amdgcn_s_waitcnt\(kWaitLds\)", b)
             assert wait and wait.start() < at, f"{name}: {m.group(1)}"
     assert found >= 1
+    # vmcnt and expcnt at their largest, lgkmcnt 0
+    assert re.search(r"kWaitLds = 0xc07f;", code("lw_fused.hip"))
 
 
 def test_row_map_reads_stay_within_the_coupled_rows():

@@ -320,25 +320,43 @@ static CrystalWs crystal_ws_layout(const kaldo_crystal* c, long nq, int prec, Cr
   return w;
 }
 
-// The layout for a workspace of `bytes`.  The boxes' tables make a small mesh's
-// larger than the rounds' (two atoms, up to 1,600 points); a workspace that
-// holds only those has always been taken, and the rounds serve it.  So does
-// the dense FP64 kernel one too small for the pruned kernel's tables.
-static CrystalWs crystal_ws_for(const kaldo_crystal* c, long nq, int prec, CrystalPath path,
-                                size_t bytes = SIZE_MAX) {
-  const CrystalWs w =
-      crystal_ws_layout(c, nq, prec, path, path == CrystalPath::Fused && fused_boxes(c, prec));
-  if (!w.boxes || w.total <= bytes) return w;
-  const CrystalWs r = crystal_ws_layout(c, nq, prec, path, false);
-  return r.total <= bytes ? r : w;
+// The layout of a request in a workspace of `bytes`: that of its path if it fits,
+// otherwise another's that does, where a cell has two kernels.  (On small meshes
+// the boxes' tables take more than the rounds', on large ones less, and the dense
+// FP64 kernel's always less than the pruned ones'; a workspace of either size has
+// been taken before.)
+static CrystalWs crystal_ws_for(const kaldo_crystal* c, const int32_t* mesh, int prec, CrystalPath path,
+                                int64_t n_subset, size_t bytes) {
+  const long nq = (long)mesh[0] * mesh[1] * mesh[2];
+  const bool boxes = path == CrystalPath::Fused && fused_boxes(c, prec, mesh, n_subset);
+  const CrystalWs w = crystal_ws_layout(c, nq, prec, path, boxes);
+  if (w.total <= bytes || path != CrystalPath::Fused) return w;
+  if (boxes || fused_boxes_cell(c, prec)) {
+    const CrystalWs other = crystal_ws_layout(c, nq, prec, path, !boxes);
+    if (other.total <= bytes) return other;
+  }
+  return w;
 }
 
-static CrystalWs crystal_ws(const kaldo_crystal* c, long nq, int prec, size_t bytes = SIZE_MAX) {
-  const CrystalWs w = crystal_ws_for(c, nq, prec, choose_path(c, nq, prec), bytes);
+static CrystalWs crystal_ws(const kaldo_crystal* c, const int32_t* mesh, int prec, int64_t n_subset, size_t bytes) {
+  const long nq = (long)mesh[0] * mesh[1] * mesh[2];
+  const CrystalWs w = crystal_ws_for(c, mesh, prec, choose_path(c, nq, prec), n_subset, bytes);
   if (w.total <= bytes || w.path != CrystalPath::Fused || prec != KALDO_FP64 || c->nb3 < 9 || !mfma64_supported(c))
     return w;
-  const CrystalWs d = crystal_ws_for(c, nq, prec, CrystalPath::Mfma);
+  const CrystalWs d = crystal_ws_layout(c, nq, prec, CrystalPath::Mfma, false);
   return d.total <= bytes ? d : w;
+}
+
+// What a query returns: room for the layout of any number of modes.
+static size_t crystal_ws_bytes(const kaldo_crystal* c, const int32_t* mesh, int prec, CrystalPath path) {
+  const CrystalWs w = crystal_ws_for(c, mesh, prec, path, 0, SIZE_MAX);
+  const long nq = (long)mesh[0] * mesh[1] * mesh[2];
+  if (!w.boxes || nq > kRoundsPoints) return w.total;
+  return std::max(w.total, crystal_ws_layout(c, nq, prec, path, false).total);
+}
+
+bool linewidths_fit(const kaldo_crystal* c, const int32_t* mesh, int prec, size_t bytes) {
+  return crystal_ws(c, mesh, prec, 0, bytes).total <= bytes;
 }
 
 static FusedWs fused_ws(unsigned char* ws, const CrystalWs& w) {
@@ -413,7 +431,7 @@ using namespace kaldo;
 extern "C" size_t kaldo_linewidths_workspace(const kaldo_crystal* c, const int32_t* mesh,
                                              int32_t precision) {
   if (!c || !mesh || mesh[0] < 1 || mesh[1] < 1 || mesh[2] < 1) return 0;
-  return crystal_ws(c, (long)mesh[0] * mesh[1] * mesh[2], precision).total;
+  return crystal_ws_bytes(c, mesh, precision, choose_path(c, (long)mesh[0] * mesh[1] * mesh[2], precision));
 }
 
 namespace kaldo {
@@ -441,7 +459,7 @@ int linewidths_enqueue(const kaldo_crystal* c, const int32_t* mesh, const double
   }
   KALDO_REQUIRE(n_subset >= 0 && (n_subset == 0 || modes_subset), "kaldo_linewidths: bad subset");
   KALDO_REQUIRE(nq <= 65535L, "kaldo_linewidths: mesh too large (N_q > 65535)");
-  CrystalWs w = crystal_ws(c, nq, precision, workspace_bytes);
+  CrystalWs w = crystal_ws(c, mesh, precision, modes_subset ? n_subset : 0, workspace_bytes);
   KALDO_REQUIRE(workspace && workspace_bytes >= w.total, "kaldo_linewidths: workspace too small");
   if (modes_subset && n_subset == 0) return KALDO_OK;
   auto* ws = static_cast<unsigned char*>(workspace);
@@ -474,7 +492,7 @@ using namespace kaldo;
 extern "C" size_t kaldo_tcache_workspace(const kaldo_crystal* c, const int32_t* mesh,
                                          int32_t precision) {
   if (!c || !mesh || mesh[0] < 1 || mesh[1] < 1 || mesh[2] < 1) return 0;
-  return crystal_ws_for(c, (long)mesh[0] * mesh[1] * mesh[2], precision, CrystalPath::Fused).total;
+  return crystal_ws_bytes(c, mesh, precision, CrystalPath::Fused);
 }
 
 extern "C" int kaldo_tcache_build(const kaldo_crystal* c, const int32_t* mesh, const double* omega,
@@ -503,7 +521,8 @@ extern "C" int kaldo_tcache_build(const kaldo_crystal* c, const int32_t* mesh, c
                 "kaldo_tcache_build: pairs and factors must both be given or both be NULL");
   const long nq = (long)mesh[0] * mesh[1] * mesh[2];
   KALDO_REQUIRE(nq <= 65535L, "kaldo_tcache_build: mesh too large (N_q > 65535)");
-  const CrystalWs w = crystal_ws_for(c, nq, precision, CrystalPath::Fused, workspace_bytes);
+  const CrystalWs w =
+      crystal_ws_for(c, mesh, precision, CrystalPath::Fused, modes_subset ? n_subset : 0, workspace_bytes);
   KALDO_REQUIRE(workspace && workspace_bytes >= w.total, "kaldo_tcache_build: workspace too small");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int nb3 = c->nb3;

@@ -517,7 +517,12 @@ struct TcOut {
 size_t fused_max_items(const kaldo_crystal* c, long nq);  // (q, chunk) work items of a request
 size_t fused_record_bytes(int nb3, size_t cs);            // of a mode's record, cs = bytes of a complex
 constexpr size_t kFusedPhaseBytes = 64;                   // of a mesh point's row of phases
-bool fused_boxes(const kaldo_crystal* c, int prec);       // whether lw_fused.hip serves the fused path's requests
+// Whether lw_fused.hip can serve a cell's requests of the fused path, and whether
+// it is the one that does (n_subset 0: all modes; a subset matters on meshes of up
+// to kRoundsPoints only).
+constexpr long kRoundsPoints = 4096;
+bool fused_boxes_cell(const kaldo_crystal* c, int prec);
+bool fused_boxes(const kaldo_crystal* c, int prec, const int32_t* N, int64_t n_subset);
 struct FusedWs {
   unsigned char *rec, *phase_tab;  // mode records, phases
   const float* freq;               // FP32 frequencies [branch][q], NaN below the floor

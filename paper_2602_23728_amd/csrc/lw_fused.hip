@@ -43,6 +43,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <initializer_list>
 
 #include "common.h"
 #include "lw_common.h"
@@ -54,6 +55,7 @@ constexpr int kFusedWaves = kFusedThreads / 64;
 constexpr int kQueue = 256;           // slots of a wave's queue of near pairs
 constexpr int kFlush = kQueue - 64;   // classified when it holds at least that many
 constexpr int kPairs = 128;           // slots of its queue of candidates, projected 64 at a time
+constexpr int kFusedItems = 2048;     // (q, chunk) work items a launch aims for
 
 // Waves per SIMD the register allocation targets: four for the small FP32
 // cells (three 671 us against 565 on the diamond 15^3 mesh), three for the small
@@ -73,17 +75,29 @@ struct Boxes {
 // their size, since a longer box spans wider frequency ranges and prunes less.
 // Measured on the diamond cell: about 140 instructions a box and 85 for each
 // (s', s'') that survives, 5 % of them plus 13 % of the box's share of the
-// mesh's edges.
+// mesh's edges.  The boxes of a q are dealt over the four waves of its
+// workgroup, or of two on meshes small enough for a second, so what counts is
+// their number rounded up to that: one box of 4 x 4 x 4 for that mesh left
+// three waves idle (FP32, adaptive: 45.8 us against 33.2 with eight boxes).
+static int n_boxes(const Boxes& b) { return b.n[0] * b.n[1] * b.n[2]; }
 static Boxes choose_boxes(const int* N) {
+  const int nq = N[0] * N[1] * N[2];
+  const int deal = nq >= 64 && nq < kFusedItems ? 2 * kFusedWaves : kFusedWaves;
+  int num[3][9];
+  double part[3][9];
+  for (int x = 0; x < 3; ++x)
+    for (int a = 1; a <= std::min(N[x], 8); ++a) {
+      num[x][a] = (N[x] + a - 1) / a;
+      part[x][a] = 0.13 * a / N[x];
+    }
   Boxes best{};
   double cost = 0.0;
   for (int a = 1; a <= std::min(N[0], 8); ++a)
     for (int b = 1; b <= std::min(N[1], 8); ++b)
-      for (int c = 1; c <= std::min(N[2], 8) && a * b * c <= 64; ++c) {
-        const Boxes x{{a, b, c}, {(N[0] + a - 1) / a, (N[1] + b - 1) / b, (N[2] + c - 1) / c}};
-        const double share = (double)a / N[0] + (double)b / N[1] + (double)c / N[2];
-        const double t = (double)x.n[0] * x.n[1] * x.n[2] * (140.0 + 85.0 * 36.0 * (0.05 + 0.13 * share));
-        if (!best.d[0] || t < cost) best = x, cost = t;
+      for (int c = 1; c <= std::min({N[2], 8, 64 / (a * b)}); ++c) {
+        const int boxes = num[0][a] * num[1][b] * num[2][c], dealt = (boxes + deal - 1) / deal * deal;
+        const double t = dealt * (140.0 + 85.0 * 36.0 * std::min(1.0, 0.05 + part[0][a] + part[1][b] + part[2][c]));
+        if (!best.d[0] || t < cost) best = {{a, b, c}, {num[0][a], num[1][b], num[2][c]}}, cost = t;
       }
   return best;
 }
@@ -853,15 +867,32 @@ bool fused_record_supported(const kaldo_crystal* c, int prec) { return fused_fit
 // (every branch of a q selected) when choosing the chunk count, for about
 // kFusedItems work items, and no chunk of fewer than two boxes a wave.  (A fixed
 // item count keeps the summation order, and so the bits of Gamma, the same on
-// every device.)
-constexpr int kFusedItems = 2048;
+// every device.)  With few boxes a chunk's set-up (about two of them: A~, the
+// tables) counts, and so does the number of rounds of the workgroups the device
+// holds at once, kResident of 256 CUs: 9^3 in FP64 took 109 us in two chunks,
+// two rounds.
+constexpr int kFewBoxes = 64;
+static long resident(size_t cs) { return cs == 16 ? 768 : 1024; }
 static int fused_upper(long nq, int64_t n_subset) {
   return (int)(n_subset > 0 ? std::min<long>(nq, n_subset) : nq);
 }
-static int fused_n_chunk(const kaldo_crystal* c, const int* N, const Boxes& box, int64_t n_subset) {
-  const long nq = (long)N[0] * N[1] * N[2];
-  const long guess = n_subset > 0 ? std::max<long>(1, n_subset / c->nb3) : nq;
-  const long boxes = (long)box.n[0] * box.n[1] * box.n[2];
+static long fused_guess(const kaldo_crystal* c, long nq, int64_t n_subset) {
+  return n_subset > 0 ? std::max<long>(1, n_subset / c->nb3) : nq;
+}
+static int fused_n_chunk(const kaldo_crystal* c, const int* N, const Boxes& box, int64_t n_subset, size_t cs) {
+  const long guess = fused_guess(c, (long)N[0] * N[1] * N[2], n_subset);
+  const long boxes = n_boxes(box);
+  if (boxes <= kFewBoxes) {
+    const long most = std::min<long>({(long)kFusedMaxChunks, boxes / kFusedWaves, kFusedItems / guess + 1});
+    int best = 1;
+    long cost = 0;
+    for (int k = 1; k <= std::max<long>(1, most); ++k) {
+      const long t = (guess * k + resident(cs) - 1) / resident(cs) *
+                     (2 + (boxes + kFusedWaves * k - 1) / (kFusedWaves * k));
+      if (k == 1 || t <= cost) best = k, cost = t;
+    }
+    return best;
+  }
   const int most = (int)std::max<long>(1, std::min<long>(kFusedMaxChunks, boxes / (2 * kFusedWaves)));
   return std::min(fused_chunks((int)std::min<long>(guess, 1l << 30), kFusedItems), most);
 }
@@ -875,15 +906,27 @@ size_t fused_max_items(const kaldo_crystal* c, long nq) {
 // Cells of one or two atoms with few phases (nearest-neighbour Phi3: diamond has
 // four), whose sweep costs as much as their projections, where the batches'
 // buffers fit beside the tables; the others' projections outweigh it and go
-// in rounds (lw_rounds.hip has both sides).
-bool fused_boxes(const kaldo_crystal* c, int prec) {
+// in rounds (lw_rounds.hip has both sides).  In rounds too: meshes more than four
+// times as long as thick, whose boxes have few neighbours in q and prune little
+// (diamond 1x1x300, FP32, fixed 0.2 THz: 74 us by boxes, 54 in rounds; 30x30x1,
+// adaptive, FP64 447 and 402), and in FP32 a few q of a small mesh, whose boxes
+// make fewer than 256 workgroups: rounds' chunks are finer (8^3, 17 q, adaptive:
+// 58 and 45).
+bool fused_boxes_cell(const kaldo_crystal* c, int prec) {
+  if (c->nb > 2 || c->bloch.n_f * 16 > (int)kFusedPhaseBytes) return false;
   const size_t cs = prec == KALDO_FP64 ? 16 : 8;
   int dev = 0, lds_max = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
   if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
     return false;
-  return c->nb <= 2 && c->bloch.n_f * 16 <= (int)kFusedPhaseBytes &&
-         fused_lds_bytes(c, prec) + fused_staged(c->nb3, cs) + kFusedOwnLds <= (size_t)lds_max;
+  return fused_lds_bytes(c, prec) + fused_staged(c->nb3, cs) + kFusedOwnLds <= (size_t)lds_max;
+}
+bool fused_boxes(const kaldo_crystal* c, int prec, const int32_t* N, int64_t n_subset) {
+  const size_t cs = prec == KALDO_FP64 ? 16 : 8;
+  if (std::max({N[0], N[1], N[2]}) > 4l * std::min({N[0], N[1], N[2]}) || !fused_boxes_cell(c, prec)) return false;
+  const long nq = (long)N[0] * N[1] * N[2];
+  if (cs == 16 || n_subset <= 0 || nq > kRoundsPoints) return true;
+  return fused_guess(c, nq, n_subset) * std::max(1l, nq / (64 * kFusedWaves)) >= 256;
 }
 
 // The fused launch of one mode: tables, live list, chunking and the kernel,
@@ -918,7 +961,7 @@ static int launch_fused_impl(const kaldo_crystal* c, const LwParams& p, const do
     KALDO_LAUNCH("lw_live_q", lw_live_q<true>, dim3(1), dim3(1024), 0, st, nq, c->nb3, phys, sel, live_list,
                  idx_of_q, n_live);
   const Fc3Bloch& b = c->bloch;
-  const int n_chunk = fused_n_chunk(c, p.N, box, n_subset);
+  const int n_chunk = fused_n_chunk(c, p.N, box, n_subset, sizeof(C));
   const unsigned grid = (unsigned)fused_upper(nq, n_subset) * n_chunk;
   // the count pass builds no A~ tables and stages the records' tails only
   const size_t at = MODE == kModeCount ? 0 : fused_lds_bytes(c, sizeof(T) == 8 ? KALDO_FP64 : KALDO_FP32);

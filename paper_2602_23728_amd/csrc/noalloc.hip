@@ -14,6 +14,7 @@
 
 namespace kaldo {
 
+bool linewidths_fit(const kaldo_crystal* c, const int32_t* mesh, int prec, size_t bytes);
 int linewidths_enqueue(const kaldo_crystal* c, const int32_t* mesh, const double* omega,
                        const double* evec, const double* vel, double temperature,
                        const kaldo_broadening* b, int32_t precision,
@@ -59,10 +60,9 @@ extern "C" int kaldo_linewidths_noalloc(const kaldo_crystal* c, const int32_t* m
   KALDO_REQUIRE(c && mesh, "kaldo_linewidths_noalloc: NULL argument");
   KALDO_REQUIRE(mesh[0] >= 1 && mesh[1] >= 1 && mesh[2] >= 1,
                 "kaldo_linewidths_noalloc: mesh must be >= 1");
-  const size_t need = kaldo_linewidths_workspace(c, mesh, precision);
-  if (need > kScratchBytes) {
+  if (!linewidths_fit(c, mesh, precision, kScratchBytes)) {
     set_error("kaldo_linewidths_noalloc: this crystal, mesh and precision need " +
-              std::to_string(need) + " bytes of workspace, more than the " +
+              std::to_string(kaldo_linewidths_workspace(c, mesh, precision)) + " bytes of workspace, more than the " +
               std::to_string(kScratchBytes) + "-byte device scratch array");
     return KALDO_EINVAL;
   }

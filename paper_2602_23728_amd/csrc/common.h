@@ -134,6 +134,7 @@ struct kaldo_crystal_s {
   int32_t* d_rep = nullptr; // [n_rep][3]
   double* d_repcart = nullptr;  // [n_rep][3] Cartesian replica vectors
   int32_t* d_flags = nullptr;   // sticky device status word (kFlag* bits)
+  size_t lds_max = 0;           // LDS bytes a workgroup may have on the handle's device
   kaldo::Fc3Bloch bloch;
   kaldo::Fc3Gamma gamma;
   std::vector<void*> allocations;

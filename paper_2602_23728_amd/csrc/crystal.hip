@@ -318,6 +318,10 @@ extern "C" int kaldo_crystal_create(int32_t n_basis, const double* lattice, cons
     for (int x = 0; x < 3; ++x)
       repcart[3 * l + x] = rep[3 * l] * lattice[x] + rep[3 * l + 1] * lattice[3 + x] +
                            rep[3 * l + 2] * lattice[6 + x];
+  int dev = 0, lds_max = 0;
+  if (hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess)
+    c->lds_max = (size_t)lds_max;
   int rc = upload(c, &c->d_fc2, scaled);
   if (!rc) rc = upload(c, &c->d_rep, c->rep);
   if (!rc) rc = upload(c, &c->d_repcart, repcart);

@@ -848,11 +848,7 @@ static size_t fused_staged(int nb3, size_t cs) {
 
 static bool fused_fits(const kaldo_crystal* c, int prec, bool record) {
   if (c->nb < 1 || c->nb > 5 || c->n_rep > 64) return false;
-  int dev = 0, lds_max = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-    return false;
-  return fused_lds_bytes(c, prec) + fused_static_lds(record) <= (size_t)lds_max;
+  return fused_lds_bytes(c, prec) + fused_static_lds(record) <= c->lds_max;
 }
 
 bool fused_supported(const kaldo_crystal* c, int prec) {
@@ -915,11 +911,7 @@ size_t fused_max_items(const kaldo_crystal* c, long nq) {
 bool fused_boxes_cell(const kaldo_crystal* c, int prec) {
   if (c->nb > 2 || c->bloch.n_f * 16 > (int)kFusedPhaseBytes) return false;
   const size_t cs = prec == KALDO_FP64 ? 16 : 8;
-  int dev = 0, lds_max = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-    return false;
-  return fused_lds_bytes(c, prec) + fused_staged(c->nb3, cs) + kFusedOwnLds <= (size_t)lds_max;
+  return fused_lds_bytes(c, prec) + fused_staged(c->nb3, cs) + kFusedOwnLds <= c->lds_max;
 }
 bool fused_boxes(const kaldo_crystal* c, int prec, const int32_t* N, int64_t n_subset) {
   const size_t cs = prec == KALDO_FP64 ? 16 : 8;

@@ -559,16 +559,12 @@ static size_t tile_lds(const kaldo_crystal* c, int group) {
 // count that minimises rounds of 256 workgroups x (set-up + branches).
 template <int FORM>
 static int tile_group(const kaldo_crystal* c, int nq) {
-  int dev = 0, lds_max = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-    return 0;
   int best = 0;
   double cost = 0.0;
   const double setup = tile_slots(c->bloch.max_pair_blk) == 4 ? 0.5 : 4.0;
   for (int n = 1; n <= c->nb3; ++n) {
     const int g = (c->nb3 + n - 1) / n;
-    if (tile_lds<FORM>(c, g) + kTileStatic > (size_t)lds_max) continue;
+    if (tile_lds<FORM>(c, g) + kTileStatic > c->lds_max) continue;
     const double t = std::ceil((double)nq * n / 256.0) * (g + setup);
     if (!best || t < cost) best = g, cost = t;
   }
@@ -617,11 +613,7 @@ constexpr int kMfmaMaxBlocks = 128;
 constexpr size_t kMfmaBeside = 53376;
 bool mfma_supported(const kaldo_crystal* c) {
   if (c->nb3 > 16 || c->n_rep > 64 || c->bloch.n_blk > kMfmaMaxBlocks) return false;
-  int dev = 0, lds_max = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-    return false;
-  return (size_t)c->bloch.n_blk * 9 * c->nb3 * 8 + kMfmaBeside <= (size_t)lds_max &&
+  return (size_t)c->bloch.n_blk * 9 * c->nb3 * 8 + kMfmaBeside <= c->lds_max &&
          tile_group<kF32>(c, 1) > 0 && tile_group<kSplit>(c, 1) > 0;
 }
 

@@ -20,11 +20,11 @@
 //                per tile
 //   iso_kernel   one workgroup per four modes of a branch adjacent in that order
 //                (nearly equal frequencies: they share each partner's loads):
-//                per partner branch the run of tiles whose range can meet the
-//                cut (found by binary search in the range table, in LDS),
-//                lanes over the tile's partners, exact FP64 cut per mode and
-//                partner, overlap and smearing in FP64, per-lane sums in tile
-//                order, fixed wave reduction per mode
+//                first which tiles can meet the cut, a lane per tile, then
+//                those tiles dealt to the waves in turn: lanes over the tile's
+//                partners, exact FP64 cut per mode and partner, overlap and
+//                smearing in FP64, per-lane sums in tile order, fixed wave
+//                reduction per mode
 //
 // What bounds the sum: chains of FP64 arithmetic, at three waves a SIMD (diamond
 // 15^3: 234 us, 306 with a wave per group of modes and the vectors kept in
@@ -40,7 +40,8 @@
 namespace kaldo {
 
 constexpr int kIsoMaxBasis = 5;          // 3 N_b <= 16
-constexpr size_t kIsoRangeLds = 48 << 10;  // bytes of range table kept in LDS
+constexpr size_t kIsoRanges = 48 << 10;  // bytes of the range table: 24 a tile of a branch
+constexpr int kIsoWords = kIsoRanges / 24 / 64;  // and its tiles in words of 64, short of one a branch
 
 struct IsoParams {
   int nq, nb3, nb, blk, nblk;  // blk: partner q-points per tile (a multiple of 64)
@@ -140,8 +141,10 @@ __global__ __launch_bounds__(256) void iso_ranges(IsoParams p, const double2* __
 
 // Modes per workgroup: MPW modes of one branch at consecutive places of its
 // order (nearly the same frequency, so nearly the same live tiles and passing
-// partners) share every partner's record and eigenvector load (two: 296 us,
-// three: 253, six: 226 with more registers than the larger cells have, eight: 239).
+// partners) share every partner's record and eigenvector load (the diamond 15^3
+// sum with the tiles of each branch dealt from the first wave on: two 296 us,
+// three 253, four 234, six 226 with more registers than the larger cells have,
+// eight 239).
 constexpr int kIsoMpw = 4;
 
 template <int NB3>
@@ -153,12 +156,10 @@ __global__ __launch_bounds__(256) void iso_kernel(IsoParams p, const double2* __
                                                   int accumulate, double* __restrict__ gamma) {
   constexpr int NB = NB3 / 3;
   constexpr int MPW = kIsoMpw;
-  extern __shared__ double rng_lds[];  // the range table, [NB3][nblk][3], then [NB3] largest sigma'
+  __shared__ unsigned long long live_lds[kIsoWords + NB3];  // bit b of word [s'][b/64]: tile b is live
   __shared__ double2 e0s[MPW][NB3];  // the modes' eigenvectors
   __shared__ double sums[4][MPW];
-  const int n_rng = p.nblk * NB3 * 3;
-  for (int k = threadIdx.x; k < n_rng; k += blockDim.x) rng_lds[k] = range[k];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // workgroup -> (branch s, first position in the branch's frequency order):
   // neighbouring workgroups scan similar tiles.  Its waves take the tiles in
   // turn: with a group of modes per wave the groups of many partners left the
@@ -178,60 +179,42 @@ __global__ __launch_bounds__(256) void iso_kernel(IsoParams p, const double2* __
     live_m[k] = in && (r.x == r.x);
     if (in && wv == 0 && lane < NB3) e0s[k][lane] = eta[((size_t)s * NB3 + lane) * p.nq + i0 + k];
   }
-  __syncthreads();
-  // the largest sigma' of each branch
-  for (int s1 = wv; s1 < NB3; s1 += 4) {
-    double m = 0.0;
-    for (int b = lane; b < p.nblk; b += 64) m = fmax(m, rng_lds[3 * (s1 * p.nblk + b) + 2]);
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-    if (lane == 0) rng_lds[n_rng + s1] = m;
+  // the tiles that can hold a partner of one of the modes, |w - w'| < 2 sigma':
+  // one lane tests one tile, each wave every fourth 64 of them, and the live
+  // tiles are dealt to the waves in turn across the branches.  (With each wave
+  // searching the run of live tiles of every branch in a copy of the table in
+  // LDS, and the tiles of each branch dealt from the first wave on, calls of
+  // three atoms and narrow cuts took 222 us on 15^3 and 1,170 on 24^3, now 136
+  // and 838; the diamond 15^3 call 251, now 195.  Whole branches to the waves:
+  // up to three times the time, the waves end far apart.)
+  const int words = (p.nblk + 63) / 64;
+  for (int t = wv; t < NB3 * words; t += 4) {
+    const int s1 = t / words, b = (t - s1 * words) * 64 + lane;
+    bool tile = false;
+    if (b < p.nblk) {
+      const double* r = range + 3 * ((size_t)s1 * p.nblk + b);
+      const double lo = r[0], hi = r[1], reach = 2.0 * r[2] * (1.0 + 1e-12);
+#pragma unroll
+      for (int k = 0; k < MPW; ++k) tile |= live_m[k] && w[k] > lo - reach && w[k] < hi + reach;
+    }
+    const unsigned long long mask = __ballot(tile);
+    if (lane == 0) live_lds[t] = mask;
   }
   __syncthreads();
   double acc[MPW];
 #pragma unroll
   for (int k = 0; k < MPW; ++k) acc[k] = 0.0;
-  bool any_live = false;
-#pragma unroll
-  for (int k = 0; k < MPW; ++k) any_live |= live_m[k];
-  if (any_live) {
-    double wlo = INFINITY, whi = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < MPW; ++k)
-      if (live_m[k]) {
-        wlo = fmin(wlo, w[k]);
-        whi = fmax(whi, w[k]);
-      }
-    for (int s1 = 0; s1 < NB3; ++s1) {
-      const double* rs = rng_lds + 3 * (size_t)s1 * p.nblk;
-      // the tiles that can hold a partner within 2 sigma' of [wlo, whi] form
-      // a run: the first has its highest w at least wlo - 2 sigma'_max of the
-      // branch (binary search; the highest w rises with b over the non-empty
-      // tiles, which come first), and the run ends at the first tile whose
-      // lowest w lies past whi + 2 sigma'_max (lowest w never falls)
-      // (the order follows the FP32 rounding of w: a tile's highest or lowest
-      // w may exceed a later tile's by one FP32 ulp, 1.2e-7 w; both bounds
-      // carry twice that)
-      const double reach_max = 2.0 * rng_lds[3 * p.nblk * NB3 + s1] * (1.0 + 1e-12);
-      const double t_lo = wlo - reach_max - 2.4e-7 * fabs(wlo);
-      const double t_hi = whi + reach_max + 2.4e-7 * fabs(whi);
-      int lo_b = 0, hi_b = p.nblk;
-      while (lo_b < hi_b) {
-        const int mid = (lo_b + hi_b) >> 1;
-        const double h = rs[3 * mid + 1];
-        // an empty tile (h = -inf) sits after every non-empty one: count it as high
-        if (h >= t_lo || !(h > -INFINITY)) hi_b = mid;
-        else lo_b = mid + 1;
-      }
-      for (int b = lo_b + wv; b < p.nblk; b += 4) {
-        const double* r = rs + 3 * b;
-        if (!(r[0] <= t_hi)) break;  // lowest w past reach (or an empty tile)
-        const double reach = 2.0 * r[2] * (1.0 + 1e-12);
-        // the tile can hold a partner with |w - w'| < 2 sigma' only if w lies
-        // within reach of its range
-        bool tile = false;
-#pragma unroll
-        for (int k = 0; k < MPW; ++k) tile |= live_m[k] && w[k] > r[0] - reach && w[k] < r[1] + reach;
-        if (!tile) continue;
+  int turn = 0;
+  for (int s1 = 0; s1 < NB3; ++s1) {
+    for (int word = 0; word < words; ++word) {
+      const unsigned long long mask = live_lds[s1 * words + word];
+      unsigned long long left =
+          (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(mask >> 32)) << 32 |
+          (unsigned)__builtin_amdgcn_readfirstlane((unsigned)mask);
+      while (left) {
+        const int b = word * 64 + __builtin_ctzll(left);
+        left &= left - 1;
+        if ((turn++ & 3) != wv) continue;
         for (int i1 = b * p.blk + lane; i1 < min(p.nq, (b + 1) * p.blk); i1 += 64) {
           const size_t m1 = (size_t)s1 * p.nq + i1;
           asm volatile("" ::: "memory");  // the modes' vectors from LDS again: kept in registers they cost a wave a SIMD
@@ -307,9 +290,10 @@ struct IsoWs {
 
 static IsoWs iso_ws(long nq, int nb3) {
   IsoWs w{};
-  // tiles of 64 q-points, widened until the range table fits the LDS budget
+  // tiles of 64 q-points, widened until the range table and the words of live
+  // tiles stay small
   int blk = 64;
-  while (((nq + blk - 1) / blk) * (size_t)nb3 * 3 * sizeof(double) > kIsoRangeLds) blk += 64;
+  while (((nq + blk - 1) / blk) * (size_t)nb3 * 3 * sizeof(double) > kIsoRanges) blk += 64;
   w.blk = blk;
   w.nblk = (int)((nq + blk - 1) / blk);
   size_t o = 0;
@@ -392,12 +376,11 @@ extern "C" int kaldo_isotope_linewidths(const kaldo_crystal* c, const int32_t* m
   KALDO_LAUNCH("iso_order", iso_order, dim3((unsigned)((nq + 63) / 64), (unsigned)c->nb3), dim3(256), 0, st,
                p, omega, vel, evec, rec, inv, eta, perm, c->d_flags);
   KALDO_LAUNCH("iso_ranges", iso_ranges, dim3((p.nblk * p.nb3 + 3) / 4), dim3(256), 0, st, p, rec, range);
-  const size_t lds = sizeof(double) * (3 * (size_t)p.nblk * p.nb3 + p.nb3);
   const long n_groups = (long)c->nb3 * ((nq + kIsoMpw - 1) / kIsoMpw);
   const dim3 grid((unsigned)n_groups);
 #define KALDO_ISO_CASE(NB3V)                                                                   \
   case NB3V:                                                                                   \
-    KALDO_LAUNCH("iso_kernel", iso_kernel<NB3V>, grid, dim3(256), lds, st, p, rec, inv, eta, range, \
+    KALDO_LAUNCH("iso_kernel", iso_kernel<NB3V>, grid, dim3(256), 0, st, p, rec, inv, eta, range, \
                  perm, accumulate, gamma);                                                     \
     break;
   switch (c->nb3) {

@@ -133,14 +133,17 @@ static int build_bloch(kaldo_crystal* c, int64_t nnz, const int32_t* fi, const i
     }
   // d and -d share a phase factor up to conjugation
   std::vector<int32_t> fvec, f_of_d(n_d), blk_f;
+  std::map<std::array<int32_t, 3>, int32_t> factor;  // d -> its place in fvec
   for (int d = 0; d < n_d; ++d) {
-    int f = 0;
-    const int n_f = static_cast<int>(fvec.size() / 3);
-    while (f < n_f && !(fvec[3 * f] == -dvec[3 * d] && fvec[3 * f + 1] == -dvec[3 * d + 1] &&
-                        fvec[3 * f + 2] == -dvec[3 * d + 2]))
-      ++f;
-    f_of_d[d] = 2 * f + (f < n_f ? 1 : 0);
-    if (f == n_f) fvec.insert(fvec.end(), dvec.begin() + 3 * d, dvec.begin() + 3 * d + 3);
+    const int32_t* v = &dvec[3 * d];
+    const auto minus = factor.find({-v[0], -v[1], -v[2]});
+    if (minus != factor.end()) {
+      f_of_d[d] = 2 * minus->second + 1;
+      continue;
+    }
+    f_of_d[d] = 2 * static_cast<int32_t>(factor.size());
+    factor[{v[0], v[1], v[2]}] = f_of_d[d] / 2;
+    fvec.insert(fvec.end(), v, v + 3);
   }
   for (int32_t d : blk_d) blk_f.push_back(f_of_d[d]);
   // balanced work list for the 16x16 B_s tiles of the MFMA kernel

@@ -77,3 +77,57 @@ def test_launches_of_the_smallest_cells(prec):
     """Their time is launches: eleven of them."""
     _, names, *_ = run(cluster(2), configs.Broadening(adaptive=False, sigma_thz=0.3), getattr(K, prec.upper()))
     assert sum(names.values()) <= 11, names
+
+
+def close(got, want, prec):
+    if prec == "fp64":
+        assert np.max(np.abs(got - want)) <= 1e-10 * want.max()
+    else:
+        big = want > 1e-3 * want.max()
+        assert np.max(np.abs(got - want)[big] / want[big]) <= 1e-4
+
+
+# 150 branches: tiles of 64 and a ragged one
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("shape", [configs.GAUSS, configs.LORENTZ])
+@pytest.mark.parametrize("paired", [True, False])
+def test_kernels_without_matrix_cores(prec, shape, paired, monkeypatch):
+    m = cluster(50)
+    if not paired:
+        val = m.fc3_val.copy()
+        val[np.flatnonzero(m.fc3_j < m.fc3_k)[::5]] *= 1.3
+        m = models.Model(**{**m.__dict__, "fc3_val": val})
+    b = configs.Broadening(shape=shape, adaptive=False, sigma_thz=0.3)
+    monkeypatch.setenv("KALDO_FORCE_GENERIC", "1")
+    g, names, om, E = run(m, b, getattr(K, prec.upper()))
+    assert "gp_gemm" in names and not any(k.startswith("gm_") for k in names)
+    close(g, olw.gamma_point_linewidths(m, om, E, 300.0, b), prec)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_every_atom_bound_to_every_other(prec):
+    """372 columns to a tile of rows, more than the matrix-core form stages."""
+    m = models.random_cluster_glass(seed=1, n_atoms=124, box=14.0, cutoff=20.0)
+    b = configs.Broadening(adaptive=False, sigma_thz=0.5)
+    g, names, om, E = run(m, b, getattr(K, prec.upper()))
+    assert "gp_gemm" in names and not any(k.startswith("gm_") for k in names)
+    pick = [0, 3, 4, 63, 64, 150, 255, 256, 300, 371]
+    close(g[pick], olw.gamma_point_linewidths(m, om, E, 300.0, b, modes=pick)[pick], prec)
+
+
+@pytest.mark.parametrize("name", [21, 22, 50])
+def test_fp64_workspace_contents_do_not_matter(name):
+    """Filled with 0x00, 0xff and 0x7f, twice each: bitwise the same linewidths."""
+    m = cluster(name)
+    om, E = oph.phonons_gamma_real(m)
+    b = configs.Broadening(adaptive=False, sigma_thz=0.3)
+    c = K.Crystal.from_model(m)
+    size = int(K.lib().kaldo_linewidths_gamma_workspace(c.handle, K.FP64))
+    ref = None
+    for fill in (0x00, 0xFF, 0x7F):
+        ws = torch.full((size,), fill, dtype=torch.uint8, device="cuda")
+        for _ in range(2):
+            g = K.linewidths_gamma(c, dev(om), dev(E), 300.0, b, K.FP64, workspace=ws).cpu().numpy()
+            ref = g if ref is None else ref
+            assert np.array_equal(g, ref), fill
+    c.close()

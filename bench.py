@@ -263,9 +263,9 @@ def gamma_point_live_flop(om_h, broadening, sym=True):
     """Executed work of the vertex GEMM: 2 * 16^2 * n_pad FLOP per 16 x 16 block of
     a live tile that is multiplied.  A 128 x 128 tile (I <= J for a symmetric
     Phi3) of mode mu is live, and of its blocks one is multiplied, when the
-    physical frequency ranges of its rows and columns can meet the 2-sigma cut
-    (in either order of the pair; the blocks of a diagonal tile below its
-    diagonal are not)."""
+    physical frequency ranges of its rows and columns can meet the 2-sigma cut:
+    in either order of the pair in a tile off the diagonal of a symmetric Phi3,
+    otherwise in its own (a diagonal tile holds both blocks of a pair)."""
     n = len(om_h)
     npad = (n + 127) // 128 * 128
     ns = npad // 16
@@ -280,8 +280,9 @@ def gamma_point_live_flop(om_h, broadening, sym=True):
     reach = 2 * (2 * np.pi * broadening.sigma_thz) * (1 + 1e-12) + 1e-9
     I, J = np.meshgrid(np.arange(ns), np.arange(ns), indexing="ij")
     ok = (lo[:, None] <= hi[:, None]) & (lo[None, :] <= hi[None, :])
+    off = I // 8 != J // 8
     if sym:
-        ok &= I <= J
+        ok &= I // 8 <= J // 8
     blocks = 0
     tiles = 0
     nt = npad // 128
@@ -291,7 +292,7 @@ def gamma_point_live_flop(om_h, broadening, sym=True):
             live = ((w + l1 - h2) < reach) & ((w + h1 - l2) > -reach)
             live |= ((w - h1 - h2) < reach) & ((w - l1 - l2) > -reach)
             if sym:
-                live |= ((w + l2 - h1) < reach) & ((w + h2 - l1) > -reach)
+                live |= off & ((w + l2 - h1) < reach) & ((w + h2 - l1) > -reach)
             live &= ok
             blocks += int(live.sum())
             tiles += int(live.reshape(nt, 8, nt, 8).any(axis=(1, 3)).sum())

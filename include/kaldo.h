@@ -223,8 +223,8 @@ int kaldo_linewidths(const kaldo_crystal* c, const int32_t* mesh, const double* 
  * hipMalloc).  Same arguments, results and kernels as kaldo_linewidths; the
  * workspace is a device array inside the library, one per GPU, of
  * kaldo_linewidths_noalloc_max_bytes() bytes (32 MiB), held until the process
- * ends.  A request whose kaldo_linewidths_workspace() exceeds that size
- * returns KALDO_EINVAL before anything is enqueued.  Every call on one GPU
+ * ends.  A request that kaldo_linewidths would not take in a workspace of that
+ * size returns KALDO_EINVAL before anything is enqueued.  Every call on one GPU
  * uses that GPU's array: calls that overlap in time on one GPU (other streams,
  * other threads) race and must be serialised by the caller; nothing needs
  * clearing between calls (every byte read is written first within a call). */
@@ -473,7 +473,8 @@ size_t kaldo_tcache_gamma_workspace(const kaldo_crystal* c, const int32_t* mesh)
  * double[n_temps], K, finite and > 0) from a cache of kaldo_tcache_build:
  *   gamma   device double[n_temps][n_modes] out, rad/ps; 0 for modes below
  *           nu_min_thz and for empty rows
- * One pass over the entries per batch of up to 8 temperatures; FP64, fixed
+ * One pass over the entries per batch of up to sixteen temperatures
+ * (eight in a workspace of half the query's size); FP64, fixed
  * summation order (bitwise reproducible).  Row pointers outside
  * [0, n_entries] or partner indices outside [0, n_modes) are skipped and set
  * the handle's status (kaldo_device_status -> KALDO_EINVAL).  Enqueued. */

@@ -97,7 +97,7 @@ struct Fc3Bloch {
   // Work list for building one 16x16 B_s tile with a wave (3N_b <= 16):
   // slot k of lane l is entry k*64 + l of the (jc, kc) entries sorted by
   // their block count; int4 = (jc*17 + kc or -1, first block, end block, bg).
-  int4* bwork = nullptr;        // [4][64]
+  int32_t* bwork = nullptr;     // [4][64]
 };
 
 // Gamma-point FC3: CSR over the (b, c) pattern of A_mu[b][c],

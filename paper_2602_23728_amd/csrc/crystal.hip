@@ -147,22 +147,22 @@ static int build_bloch(kaldo_crystal* c, int64_t nnz, const int32_t* fi, const i
   }
   for (int32_t d : blk_d) blk_f.push_back(f_of_d[d]);
   // balanced work list for the 16x16 B_s tiles of the MFMA kernel
-  std::vector<int4> bwork(256, int4{-1, 0, 0, 0});
+  std::vector<int32_t> bwork(256, -1);
   if (3 * nb <= 16) {
-    struct W { int pos, lo, hi, bg; };
+    struct W { int pos, n; };
     std::vector<W> ws;
     for (int jc = 0; jc < 3 * nb; ++jc)
       for (int kc = 0; kc < 3 * nb; ++kc) {
         const int pr = (jc / 3) * nb + kc / 3;
-        ws.push_back({jc * 17 + kc, pair_ptr[pr], pair_ptr[pr + 1], (jc % 3) * 3 + kc % 3});
+        ws.push_back({jc * 17 + kc, pair_ptr[pr + 1] - pair_ptr[pr]});
       }
     std::stable_sort(ws.begin(), ws.end(),
-                     [](const W& a, const W& b) { return a.hi - a.lo > b.hi - b.lo; });
+                     [](const W& a, const W& b) { return a.n > b.n; });
     for (size_t e = 0; e < ws.size(); ++e) {
       // serpentine deal over the 64 lanes keeps per-lane block counts even
       const int slot = static_cast<int>(e / 64), l = static_cast<int>(e % 64);
       const int lane = (slot & 1) ? 63 - l : l;
-      bwork[slot * 64 + lane] = int4{ws[e].pos, ws[e].lo, ws[e].hi, ws[e].bg};
+      bwork[slot * 64 + lane] = ws[e].pos;
     }
   }
   Fc3Bloch& b = c->bloch;

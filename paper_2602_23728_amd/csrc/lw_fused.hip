@@ -58,12 +58,11 @@ constexpr int kPairs = 128;           // slots of its queue of candidates, proje
 constexpr int kFusedItems = 2048;     // (q, chunk) work items a launch aims for
 
 // Waves per SIMD the register allocation targets: four for the small FP32
-// cells (three 671 us against 565 on the diamond 15^3 mesh), three for the small
-// FP64 cells (two 8.1 ms against 6.3 on 24^3, four spill the vectors), the
-// compiler's choice otherwise.
+// cells (three 671 us against 565 on the diamond 15^3 mesh), three for the
+// FP64 cells (two 8.1 ms against 6.3 on 24^3, four spill the vectors).
 template <int NB, typename T>
 constexpr int fused_waves_per_eu() {
-  return (NB <= 2 && sizeof(T) == 4) ? 4 : (NB <= 2 ? 3 : 1);
+  return sizeof(T) == 4 ? 4 : 3;
 }
 
 // Partner boxes of a mesh: extents and numbers per axis.

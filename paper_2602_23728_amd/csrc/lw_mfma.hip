@@ -115,7 +115,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
     const int32_t* __restrict__ t_l2, const double* __restrict__ t_coef,
     const int32_t* __restrict__ e_blk, const int32_t* __restrict__ e_bg,
     const int32_t* __restrict__ blk_d, const int32_t* __restrict__ pair_ptr,
-    const int4* __restrict__ bwork, double scale, double* __restrict__ gamma) {
+    const int32_t* __restrict__ bwork, double scale, double* __restrict__ gamma) {
   using T = typename Dense<FORM>::T;
   using V4 = typename Dense<FORM>::V4;
   using C = typename Cx<T>::type;
@@ -227,7 +227,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
   for (int i = 0; i < 4; ++i) {
     int jc = lr, kc = 4 * i + lg;
     if constexpr (kSpl) {
-      b_pos[i] = bwork[i * 64 + lane].x;
+      b_pos[i] = bwork[i * 64 + lane];
       if (b_pos[i] < 0) b_pos[i] = 16 * 17;
       jc = b_pos[i] / 17;
       kc = b_pos[i] - 17 * jc;
@@ -240,8 +240,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
   }
   // Steps the wave takes for each of the four.  The split form's list is sorted
   // by length: its later entries are fewer and shorter, or none (random three
-  // atoms on 7^3, adaptive, against 1,105 us with all sixteen
-  // steps for each: 829).
+  // atoms on 7^3, adaptive: 843 us, 1,105 with all sixteen steps for each).
   int b_end[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -525,7 +524,7 @@ __attribute__((amdgpu_waves_per_eu(Dense<FORM>::kWaves / 4))) void lw_tiles(
       resolve(dbl);  // the queue never carries candidates past their partner
     } while (s < n_s);
   }
-  // fixed order: a branch's 32 sums of every wave in turn, then a butterfly
+  // fixed order: a branch's sixteen sums of every wave in turn, then a butterfly
   __syncthreads();
   for (int s = wv; s < n_s; s += kTileWaves) {
     double sum = 0.0;

@@ -777,34 +777,46 @@ __attribute__((amdgpu_waves_per_eu(fused_waves_per_eu<NB, T>()))) void lw_fused(
 // the sum over the waves of its q's work items (0 when q has no live mode),
 // rows in mode order.  tc_rows counts and scans blocks of 1024 modes,
 // tc_rows_sum scans the blocks' totals (at most 960 of them), tc_rows_add adds
-// each block's start.
+// each block's start.  Up to kRowBlocks go one after the other in one workgroup,
+// which needs neither (diamond, adaptive, FP64, the whole build: 4^3 129 us,
+// 171 in three launches; 6^3, two blocks, 152 and 182; 10^3, six, 337 and 357;
+// 11^3, eight, 454 and 465, in FP32 466 and 462).
+constexpr int kRowBlocks = 8;
+
 __global__ __launch_bounds__(1024) void tc_rows(int n_modes, int nb3, const int32_t* __restrict__ idx_of_q,
                                                 int n_sub, const int32_t* __restrict__ count,
                                                 long long* __restrict__ row_ptr,
                                                 long long* __restrict__ block_sum) {
-  __shared__ long long wave_tot[16];
+  __shared__ long long wave_tot[2][16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int m = blockIdx.x * 1024 + tid;
-  long long own = 0;
-  if (m < n_modes) {
-    const int q = m / nb3, s = m - q * nb3, k = idx_of_q[q];
-    if (k >= 0)
-      for (int c = 0; c < n_sub; ++c) own += count[((size_t)k * n_sub + c) * nb3 + s];
+  const int n_turn = gridDim.x == 1 ? (n_modes + 1023) / 1024 : 1;
+  long long total = 0;
+  for (int t = 0; t < n_turn; ++t) {
+    const int m = (blockIdx.x + t) * 1024 + tid;
+    long long own = 0;
+    if (m < n_modes) {
+      const int q = m / nb3, s = m - q * nb3, k = idx_of_q[q];
+      if (k >= 0)
+        for (int c = 0; c < n_sub; ++c) own += count[((size_t)k * n_sub + c) * nb3 + s];
+    }
+    long long incl = own;
+    for (int off = 1; off < 64; off <<= 1) {
+      const long long v = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += v;
+    }
+    if (lane == 63) wave_tot[t & 1][wv] = incl;
+    __syncthreads();
+    long long before = total;
+    for (int k = 0; k < 16; ++k) {
+      before += k < wv ? wave_tot[t & 1][k] : 0;
+      total += wave_tot[t & 1][k];
+    }
+    if (m < n_modes) row_ptr[m] = before + incl - own;
   }
-  long long incl = own;
-  for (int off = 1; off < 64; off <<= 1) {
-    const long long v = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += v;
+  if (tid == 0) {
+    block_sum[blockIdx.x] = total;
+    if (gridDim.x == 1) row_ptr[n_modes] = total;
   }
-  if (lane == 63) wave_tot[wv] = incl;
-  __syncthreads();
-  long long before = 0, total = 0;
-  for (int k = 0; k < 16; ++k) {
-    before += k < wv ? wave_tot[k] : 0;
-    total += wave_tot[k];
-  }
-  if (m < n_modes) row_ptr[m] = before + incl - own;
-  if (tid == 0) block_sum[blockIdx.x] = total;
 }
 
 __global__ __launch_bounds__(1024) void tc_rows_sum(int n_block, int n_modes, long long* __restrict__ block_sum,
@@ -976,12 +988,14 @@ static int launch_fused_impl(const kaldo_crystal* c, const LwParams& p, const do
                  n_modes, c->nb3, phys, sel, idx_of_q, n_chunk, ws.part, scale, gamma);
   if (MODE == kModeCount) {
     const int n_block = (n_modes + 1023) / 1024;
-    KALDO_LAUNCH("tc_rows", tc_rows, dim3(n_block), dim3(1024), 0, st, n_modes, c->nb3, idx_of_q,
+    KALDO_LAUNCH("tc_rows", tc_rows, dim3(n_block > kRowBlocks ? n_block : 1), dim3(1024), 0, st, n_modes, c->nb3, idx_of_q,
                  n_chunk * kFusedWaves, tc.count, tc.row_ptr, tc.block_sum);
-    KALDO_LAUNCH("tc_rows_sum", tc_rows_sum, dim3(1), dim3(1024), 0, st, n_block, n_modes, tc.block_sum,
-                 tc.row_ptr);
-    KALDO_LAUNCH("tc_rows_add", tc_rows_add, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes,
-                 tc.block_sum, tc.row_ptr);
+    if (n_block > kRowBlocks) {
+      KALDO_LAUNCH("tc_rows_sum", tc_rows_sum, dim3(1), dim3(1024), 0, st, n_block, n_modes, tc.block_sum,
+                   tc.row_ptr);
+      KALDO_LAUNCH("tc_rows_add", tc_rows_add, dim3((n_modes + 255) / 256), dim3(256), 0, st, n_modes,
+                   tc.block_sum, tc.row_ptr);
+    }
   }
   KALDO_HIP(hipGetLastError());
   return KALDO_OK;

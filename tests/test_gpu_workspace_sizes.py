@@ -145,3 +145,36 @@ def test_dense_fp64_smaller_workspace():
         K.linewidths(c, mesh, om, ev, ve, 300.0, b, K.FP64, workspace=buffer(size - 256))
     c.device_status()
     c.close()
+
+
+# 6, 1,008 and 1,050 modes: one block of 1,024 row pointers and two
+@pytest.mark.parametrize("mesh", [(1, 1, 1), (4, 6, 7), (5, 5, 7)])
+def test_cache_rows_of_both_sweeps(mesh):
+    """Row pointers of the sweep by boxes and, in the smaller workspace, in rounds."""
+    m = models.diamond()
+    om, ev, ve = (dev(x) for x in oph.phonons(m, mesh))
+    b = configs.Broadening(adaptive=True)
+    c = K.Crystal.from_model(m)
+    ref = K.tcache_build(c, mesh, om, ev, ve, b, K.FP64)
+    tc = K.tcache_build(c, mesh, om, ev, ve, b, K.FP64,
+                        workspace=buffer(crystal_sizes(c, mesh, K.FP64, differences(m))))
+    assert torch.equal(tc.row_ptr, ref.row_ptr) and int(ref.row_ptr[-1]) == ref.n_entries
+    c.close()
+
+
+# 1,296, 7,986 and 8,712 modes: two blocks of 1,024 row pointers, eight, and nine
+@pytest.mark.parametrize("mesh", [(6, 6, 6), (11, 11, 11), (11, 11, 12)])
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-10), ("fp32", 1e-5)])
+def test_cache_rows_of_several_blocks(mesh, prec, tol):
+    """Every mode's row, by its linewidth."""
+    m = models.diamond()
+    c = K.Crystal.from_model(m)
+    om, ev, ve = K.phonons(c, mesh)
+    b = configs.Broadening(adaptive=True)
+    P = getattr(K, prec.upper())
+    want = K.linewidths(c, mesh, om, ev, ve, 300.0, b, P).cpu().numpy()
+    tc = K.tcache_build(c, mesh, om, ev, ve, b, P)
+    got = K.tcache_gamma(c, tc, om, b.nu_min_thz, [300.0])[0].cpu().numpy()
+    assert int(tc.row_ptr[-1]) == tc.n_entries
+    assert np.max(np.abs(got - want)) <= tol * want.max()
+    c.close()

@@ -365,9 +365,9 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 3, sizeof(T) == 8 ? 2 : 
 // strips of 16 columns, only those whose modes can meet the cut with its rows:
 // the band of live pairs is narrower than a tile, and each wave crosses it
 // alike; strips of rows or columns no wave multiplies are not fetched.  What
-// bounds it is the operands' way in (W streams from HBM once per tile row; the
-// matrix units are busy a fifth of the time in FP32), hence two slices in
-// flight.  Measured, us a step, whole tiles by four waves -> this: FP32 on 512
+// bounds it is the operands' way in (W streams from HBM once per tile row:
+// 5.5 GB a step on 512 atoms, 1.1 ms of 1.7 at the rate of a copy; the matrix
+// units are busy a fifth of the time in FP32), hence two slices in flight.  Measured, us a step, whole tiles by four waves -> this: FP32 on 512
 // atoms 3676 -> 1698, split on 384 atoms 835 -> 666; FP64 on 216 atoms 2444
 // (generic VALU tiles of 64 x 64) -> 488.  A block's products keep their K
 // order, so V is the same to the bit as with whole tiles.

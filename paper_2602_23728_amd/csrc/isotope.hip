@@ -26,11 +26,12 @@
 //                smearing in FP64, per-lane sums in tile order, fixed wave
 //                reduction per mode
 //
-// What bounds the sum: chains of FP64 arithmetic, at three waves a SIMD (diamond
-// 15^3: 234 us, 306 with a wave per group of modes and the vectors kept in
-// registers).  A bitonic sort of the keys in one workgroup per branch, the
+// What bounds the sum: FP64 arithmetic, 84 % of the vector ALU's issue slots
+// (diamond 24^3: 2.16 ms, 2.49 with the live tiles of each branch searched and
+// dealt by themselves, 3.2 with a wave per group of modes and the vectors kept
+// in registers).  A bitonic sort of the keys in one workgroup per branch, the
 // ranges one thread per tile and a launch for the largest sigma' took 105 us
-// there, the ranks and ranges 31.
+// on the diamond 15^3 mesh, the ranks and ranges 31.
 #include <algorithm>
 #include <cmath>
 
